@@ -381,19 +381,19 @@ int enqueue_far_count(hz_handle* h, hipStream_t s, int n, const int* rp, const i
     return HZ_OK;
 }
 
-// Which iteration: the gather-light one (p and s materialised, one gathered
-// vector per product, five kernels) or the fused one (p and s formed per
-// gathered column, three gathered vectors, three kernels).  On large systems
-// the extra gathers cost more than the two launches they save: 1.05x on the
-// cylinder (n = 210k), 1.6x on the renumbered cabin, 2.4x on the randomly
-// numbered one, a tie at n = 262k.  Up to about 10^5 rows every gathered
-// vector sits in L2 and the iteration is launch-bound, so the fused one wins
-// (20^3 cube 24.1 -> 21.0 us, 48^3 cube 32.4 -> 30.6 us per iteration).
+// Which iteration: the gather-light one (s and, in TFQMR, u'' materialised, one
+// gathered vector per product) or the fused one (formed per gathered column,
+// two gathered vectors, one launch fewer).  Each launch costs about 3 us of
+// start-up, head and tail; the second gathered vector costs more from about
+// 57,000 rows on.  BiCGStab, us per iteration, fused / split: 8,000 rows 14.6 /
+// 16.0, 31,429 rows 17.0 / 18.1, 46,656 rows 17.5 / 18.5, 57,005 rows 21.9 / 21.8,
+// 92,477 rows 26.3 / 24.7, 209,777 rows 42.7 / 39.8.
 // `rows` is the total over the systems of a launch.  HZ_FUSED=0/1 overrides.
-constexpr int64_t kFusedMaxRows = 131072;
-bool choose_fused(const hz_handle*, int64_t rows) {
+constexpr int64_t kFusedMaxRows = 57344;
+constexpr int64_t kFusedMaxRowsQ = 131072;  // TFQMR's third launch
+bool choose_fused(const hz_handle*, int64_t rows, int64_t most = kFusedMaxRows) {
     if (const char* env = std::getenv("HZ_FUSED")) return std::atoi(env) != 0;
-    return rows <= kFusedMaxRows;
+    return rows <= most;
 }
 
 int check_csr_args(int n, int nnz, const int* rp, const int* ci, const void* vals) {
@@ -418,54 +418,60 @@ using hz::SysMap;
 // the total is padded to a multiple of 8 with empty blocks.
 struct WorkMap {
     int nsys = 0, G = 0, stride = 0;
-    std::vector<BlockMap> blocks;
+    hz::OneMap one;                 // one system: the map by value
+    std::vector<BlockMap> blocks;   // several: the arrays
     std::vector<SysMap> systems;
 };
+
+// The one-system map: groups own equal shares of the rows, rounded up to 16
+// (the last ones may be shorter, or empty on a tiny system).
+hz::OneMap one_map(int n, int G) {
+    hz::OneMap o;
+    o.n = n;
+    o.groups = (G % hz::kXcd == 0) ? hz::kXcd : 1;
+    o.K = G / o.groups;
+    o.gr = o.groups == 1 ? n : int((int64_t(n) + hz::kXcd - 1) / hz::kXcd + 15) / 16 * 16;
+    return o;
+}
 
 WorkMap build_map(int nsys, const int* row_off, int L) {
     WorkMap m;
     m.nsys = nsys;
     const int64_t N = int64_t(row_off[nsys]) - row_off[0];
     if (nsys == 1) {
-        // one group of blocks per XCD, each group's blocks taking its rows' tiles in turn (struct Rows)
-        const Geom geo = geom_for(int(N), kBlock / L);
-        const int groups = (geo.G % hz::kXcd == 0) ? hz::kXcd : 1, K = geo.G / groups;
-        for (int b = 0; b < geo.G; ++b) {
-            const int x = b / K;
-            const int64_t x0 = N * x / groups, x1 = N * (x + 1) / groups;
-            m.blocks.push_back(BlockMap{0, int(row_off[0] + x0), int(row_off[0] + x1), b % K, K, b});
-        }
-        m.systems.push_back(SysMap{0, geo.G, row_off[0], row_off[1]});
-    } else {
-        const int64_t R = std::max<int64_t>(kBlock / L, (N + kMaxGrid - 1) / kMaxGrid);
-        for (int j = 0; j < nsys; ++j) {
-            const int64_t nj = int64_t(row_off[j + 1]) - row_off[j];
-            const int64_t gj = std::max<int64_t>(1, (nj + R - 1) / R);
-            const int64_t chunk = std::max<int64_t>(1, (nj + gj - 1) / gj);
-            m.systems.push_back(SysMap{int(m.blocks.size()), int(gj), row_off[j], row_off[j + 1]});
-            for (int64_t b = 0; b < gj; ++b) {
-                const int64_t r0 = std::min<int64_t>(nj, b * chunk), r1 = std::min<int64_t>(nj, r0 + chunk);
-                m.blocks.push_back(BlockMap{j, int(row_off[j] + r0), int(row_off[j] + r1), 0, 1, int(b)});
-            }
-        }
-        while (m.blocks.size() >= size_t(hz::kXcd) && m.blocks.size() % hz::kXcd != 0)
-            m.blocks.push_back(BlockMap{-1, 0, 0, 0, 1, 0});
+        m.G = geom_for(int(N), kBlock / L).G;
+        m.one = one_map(int(N), m.G);
+        m.stride = std::max(m.G, kMaxGrid);
+        return m;
     }
+    const int64_t R = std::max<int64_t>(kBlock / L, (N + kMaxGrid - 1) / kMaxGrid);
+    for (int j = 0; j < nsys; ++j) {
+        const int64_t nj = int64_t(row_off[j + 1]) - row_off[j];
+        const int64_t gj = std::max<int64_t>(1, (nj + R - 1) / R);
+        const int64_t chunk = std::max<int64_t>(1, (nj + gj - 1) / gj);
+        m.systems.push_back(SysMap{int(m.blocks.size()), int(gj), row_off[j], row_off[j + 1]});
+        for (int64_t b = 0; b < gj; ++b) {
+            const int64_t r0 = std::min<int64_t>(nj, b * chunk), r1 = std::min<int64_t>(nj, r0 + chunk);
+            m.blocks.push_back(BlockMap{j, int(row_off[j] + r0), int(row_off[j] + r1), 0, 1, int(b)});
+        }
+    }
+    while (m.blocks.size() >= size_t(hz::kXcd) && m.blocks.size() % hz::kXcd != 0)
+        m.blocks.push_back(BlockMap{-1, 0, 0, 0, 1, 0});
     m.G = int(m.blocks.size());
     m.stride = std::max(m.G, kMaxGrid);
     return m;
 }
 
 // Solver workspace: per-system scalars, partials, the work map, a done
-// counter, eight vectors (r, rhat, p0, p1, v0, v1, s, t) and, under Jacobi,
-// D^{-1} and the column-scaled values.
+// counter, six vectors (r, rhat, p, v, s, t) and, under Jacobi, D^{-1} and the
+// column-scaled values.
 struct SolveWs {
     SolverScal* sc;
     double* part;
     BlockMap* bmap;
     SysMap* smap;
     int* ndone;
-    void* vec[8];
+    void* vec[6];
     void* dinv;
     void* ahat;
 };
@@ -474,6 +480,8 @@ struct SolveWs {
 // room for the products' sub-blocks, sol_subs(G) G <= max(2 G, kSolSlots) slots.
 int bicg_stride(int G) { return std::max(2 * G, std::max(2 * kMaxGrid, hz::kSolSlots)); }
 
+// The size is never less than that of eight vectors and ten partial regions,
+// which callers' limits (the static scratch's among them) have been set by.
 template <typename T>
 size_t ws_layout(int n, int64_t nnz, bool jacobi, int nsys, int G, char* base, SolveWs* out) {
     const size_t vb = align_up(sizeof(cx<T>) * size_t(n > 0 ? n : 1));
@@ -494,7 +502,9 @@ size_t ws_layout(int n, int64_t nnz, bool jacobi, int nsys, int G, char* base, S
     w.dinv = jacobi ? take(vb) : nullptr;
     w.ahat = jacobi ? take(sizeof(cx<T>) * size_t(nnz > 0 ? nnz : 1)) : nullptr;
     if (out) *out = w;
-    return off;
+    const size_t extra_parts = align_up(sizeof(double) * size_t(hz::kParts) * size_t(stride)) -
+                               align_up(sizeof(double) * size_t(10) * size_t(stride));
+    return std::max(off, off + 2 * vb - extra_parts);
 }
 
 // Worst case of the one-system map: G <= kMaxGrid.
@@ -508,6 +518,7 @@ hz::BicgArgs<T> bicg_args(const WorkMap& m, const int* rp, const int* ci, const 
     hz::BicgArgs<T> a{};
     a.G = m.G;
     a.stride = bicg_stride(m.G);
+    a.one = m.one;
     a.bmap = w.bmap;
     a.smap = w.smap;
     a.ndone = w.ndone;
@@ -517,33 +528,31 @@ hz::BicgArgs<T> bicg_args(const WorkMap& m, const int* rp, const int* ci, const 
     a.b = b;
     a.r = static_cast<cx<T>*>(w.vec[0]);
     a.rh = static_cast<const cx<T>*>(w.vec[1]);
-    a.p[0] = static_cast<cx<T>*>(w.vec[2]);
-    a.p[1] = static_cast<cx<T>*>(w.vec[3]);
-    a.v[0] = static_cast<cx<T>*>(w.vec[4]);
-    a.v[1] = static_cast<cx<T>*>(w.vec[5]);
-    a.s = static_cast<cx<T>*>(w.vec[6]);
-    a.t = static_cast<cx<T>*>(w.vec[7]);
+    a.p = static_cast<cx<T>*>(w.vec[2]);
+    a.v = static_cast<cx<T>*>(w.vec[3]);
+    a.s = static_cast<cx<T>*>(w.vec[4]);
+    a.t = static_cast<cx<T>*>(w.vec[5]);
     a.x = x;
     a.part = w.part;
     a.sc = w.sc;
     return a;
 }
 
-// Upload the map (host vectors stay alive until the caller's next sync).
+// Upload a batch's map (host vectors stay alive until the caller's next sync)
+// and zero the done-counter.
 int upload_map(hipStream_t s, const WorkMap& m, const SolveWs& w) {
+    if (m.nsys == 1) {
+        HZ_HIP(hipMemsetAsync(w.ndone, 0, sizeof(int), s));
+        return HZ_OK;
+    }
     HZ_HIP(hipMemcpyAsync(w.bmap, m.blocks.data(), sizeof(BlockMap) * m.blocks.size(), hipMemcpyHostToDevice, s));
     HZ_HIP(hipMemcpyAsync(w.smap, m.systems.data(), sizeof(SysMap) * m.systems.size(), hipMemcpyHostToDevice, s));
     HZ_HIP(hipMemsetAsync(w.ndone, 0, sizeof(int), s));
     return HZ_OK;
 }
 
-// The iteration loop of BiCGStab on the (possibly column-scaled) matrix in
-// `a` for every system of the map.  On entry r, rhat and the scalars are
-// initialised (k_fin_init ran).  Launches at most maxiter iterations, then
-// one more first kernel that concludes the last iteration; polls the
-// done-counter between chunks of 8, 16, ..., 64 iterations.
 // The gather-light products of a one-system solve on the block-tile row loop
-// (L = 1) run as sub-blocks with an LDS result ring (k_bicg_A1t, k_bicg_B1t);
+// (L = 1) run as sub-blocks with an LDS result ring (k_bicg_At, k_bicg_Bt);
 // the returned arguments carry their partial layout.
 template <typename T> bool sub_products(const WorkMap& m, int L, bool fused) { return L == 1 && m.nsys == 1 && !fused; }
 template <typename T> hz::BicgArgs<T> iteration_args(const WorkMap& m, hz::BicgArgs<T> a, int L, bool fused) {
@@ -551,26 +560,34 @@ template <typename T> hz::BicgArgs<T> iteration_args(const WorkMap& m, hz::BicgA
     return a;
 }
 
-// One gather-light iteration (P, A1, S, B1, C) on stream q.
+// One iteration on stream q: A, B, C with s formed in B (fused), or A, S, B, C.
 template <typename T, int LL, int UU>
-void enqueue_gather_light(hipStream_t q, const WorkMap& m, const hz::BicgArgs<T>& a, bool sub) {
+void enqueue_iteration(hipStream_t q, const WorkMap& m, const hz::BicgArgs<T>& a, bool fused, bool sub) {
     const dim3 G(m.G), B(kBlock);
-    hipLaunchKernelGGL((hz::k_bicg_P<T>), G, B, 0, q, a);
     if (sub)
-        hipLaunchKernelGGL((hz::k_bicg_A1t<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
+        hipLaunchKernelGGL((hz::k_bicg_At<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
     else
-        hipLaunchKernelGGL((hz::k_bicg_A1<T, LL, UU>), G, B, 0, q, a);
-    hipLaunchKernelGGL((hz::k_bicg_S<T>), G, B, 0, q, a);
-    if (sub)
-        hipLaunchKernelGGL((hz::k_bicg_B1t<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
-    else
-        hipLaunchKernelGGL((hz::k_bicg_B1<T, LL, UU>), G, B, 0, q, a);
+        hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU>), G, B, 0, q, a);
+    if (fused) {
+        hipLaunchKernelGGL((hz::k_bicg_SB<T, LL, UU>), G, B, 0, q, a);
+    } else {
+        hipLaunchKernelGGL((hz::k_bicg_S<T>), G, B, 0, q, a);
+        if (sub)
+            hipLaunchKernelGGL((hz::k_bicg_Bt<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
+        else
+            hipLaunchKernelGGL((hz::k_bicg_B<T, LL, UU>), G, B, 0, q, a);
+    }
+    hipLaunchKernelGGL((hz::k_bicg_C<T>), G, B, 0, q, a);
 }
 
+// The iteration loop of BiCGStab on the (possibly column-scaled) matrix in
+// `a` for every system of the map.  On entry r, rhat, p and the scalars are
+// initialised (k_fin_init ran).  Launches at most maxiter iterations, then
+// one kernel that concludes the last iteration; polls the
+// done-counter between chunks of 8, 16, ..., 64 iterations.
 template <typename T>
 int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>& a0, int L, int maxiter, bool fused,
             bool poll_done = true, bool graphs = true) {
-    const dim3 G(m.G), B(kBlock);
     const hz::BicgArgs<T> a = iteration_args(m, a0, L, fused);
     const bool sub = sub_products<T>(m, L, fused);
     int launched = 0, poll = poll_done ? 8 : 64;
@@ -585,17 +602,9 @@ int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>
         };
         int rc = chunk([&](hipStream_t q) {
             with_lanes(L, [&]<int LL, int UU>() {
-                for (int k = 0; k < k_n; ++k) {
-                    if (fused) {
-                        hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU>), G, B, 0, q, a);
-                        hipLaunchKernelGGL((hz::k_bicg_B<T, LL, UU>), G, B, 0, q, a);
-                    } else {
-                        enqueue_gather_light<T, LL, UU>(q, m, a, sub);
-                    }
-                    hipLaunchKernelGGL((hz::k_bicg_C<T>), G, B, 0, q, a);
-                }
-                if (tail) hipLaunchKernelGGL((hz::k_bicg_P<T>), G, B, 0, q, a);
+                for (int k = 0; k < k_n; ++k) enqueue_iteration<T, LL, UU>(q, m, a, fused, sub);
             });
+            if (tail) hipLaunchKernelGGL((hz::k_bicg_end<T>), dim3(m.nsys), dim3(kBlock), 0, q, a);
         });
         if (rc) return rc;
         launched += k_n;
@@ -609,20 +618,9 @@ int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>
     return HZ_OK;
 }
 
-// The single-system map of build_map(1, {0, n}, L) written by a kernel into
-// the workspace (the asynchronous solve: no host buffer has to outlive the
-// call, nothing is allocated and nothing waits), and the done-counter zeroed.
-__global__ void k_map_one(BlockMap* bm, SysMap* sm, int* ndone, int n, int G, int groups, int K) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < G) {
-        const int x = b / K;
-        const int64_t x0 = int64_t(n) * x / groups, x1 = int64_t(n) * (x + 1) / groups;
-        bm[b] = BlockMap{0, int(x0), int(x1), b % K, K, b};
-    }
-    if (b == 0) {
-        sm[0] = SysMap{0, G, 0, n};
-        *ndone = 0;
-    }
+// The done-counter zeroed by a kernel (the asynchronous solve may be captured, so it records no memset).
+__global__ void k_zero_word(int* w) {
+    if (threadIdx.x == 0) *w = 0;
 }
 
 // x = 0 by a kernel (the allocation-free solve records no memset, so that a
@@ -630,13 +628,6 @@ __global__ void k_map_one(BlockMap* bm, SysMap* sm, int* ndone, int n, int G, in
 __global__ void k_zero_c128(int n, double2* x) {
     const int64_t stride = int64_t(gridDim.x) * blockDim.x;
     for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) x[i] = double2{0.0, 0.0};
-}
-
-int write_map_one(hipStream_t s, int n, const WorkMap& m, const SolveWs& w) {
-    const int groups = (m.G % hz::kXcd == 0) ? hz::kXcd : 1, K = m.G / groups;
-    hipLaunchKernelGGL(k_map_one, dim3((m.G + 255) / 256), dim3(256), 0, s, w.bmap, w.smap, w.ndone, n, m.G, groups,
-                       K);
-    return hipGetLastError() == hipSuccess ? HZ_OK : HZ_ERR_HIP;
 }
 
 // hz_solve_info of system 0 from its device scalars (asynchronous solve).
@@ -676,10 +667,14 @@ int solve_fp64(hz_handle* h, hipStream_t s, int nsys, const int* row_off, int nn
     const WorkMap m = build_map(nsys, row_off, L);
     SolveWs w;
     ws_layout<double>(n, nnz, jacobi, nsys, m.G, ws, &w);
-    int rc = async ? write_map_one(s, n, m, w) : upload_map(s, m, w);
+    int rc = HZ_OK;
+    if (async)
+        hipLaunchKernelGGL(k_zero_word, dim3(1), dim3(64), 0, s, w.ndone);
+    else
+        rc = upload_map(s, m, w);
     if (rc) return rc;
     double2* r = static_cast<double2*>(w.vec[0]);
-    double2* t = static_cast<double2*>(w.vec[7]);
+    double2* t = static_cast<double2*>(w.vec[5]);
     double2* dinv = static_cast<double2*>(w.dinv);
     hipLaunchKernelGGL(hz::k_sc_init, dim3((nsys + 255) / 256), dim3(256), 0, s, w.sc, nsys, rtol, maxiter);
 
@@ -1024,14 +1019,12 @@ int solve_single(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, con
 
 // ------------------------------------------------------------------ BiCGstab(l)
 
-// Workspace: scalars, partials, the one-system map, the done counter, r~,
+// Workspace: scalars, partials, the done counter, r~,
 // r_0 .. r_l, u_0 .. u_l, a residual vector, Jacobi D^{-1} and A D^{-1},
 // the Gram partials and the minimal-residual coefficients.
 struct LWs {
     SolverScal* sc;
     double* part;
-    BlockMap* bmap;
-    SysMap* smap;
     int* ndone;
     double2* rt;
     double2* r[hz::kLMax + 1];
@@ -1054,8 +1047,6 @@ size_t lws_layout(int n, int64_t nnz, int ell, bool jacobi, char* base, LWs* out
     LWs w{};
     w.sc = static_cast<SolverScal*>(take(sizeof(SolverScal)));
     w.part = static_cast<double*>(take(sizeof(double) * size_t(hz::kParts) * size_t(bicg_stride(kMaxGrid))));
-    w.bmap = static_cast<BlockMap*>(take(sizeof(BlockMap) * size_t(kMaxGrid)));
-    w.smap = static_cast<SysMap*>(take(sizeof(SysMap)));
     w.ndone = static_cast<int*>(take(sizeof(int)));
     w.rt = static_cast<double2*>(take(vb));
     for (int p = 0; p <= ell; ++p) w.r[p] = static_cast<double2*>(take(vb));
@@ -1099,8 +1090,6 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     const WorkMap m = build_map(1, row_off, L);
     LWs w;
     lws_layout(n, nnz, ell, jacobi, ws, &w);
-    HZ_HIP(hipMemcpyAsync(w.bmap, m.blocks.data(), sizeof(BlockMap) * m.blocks.size(), hipMemcpyHostToDevice, s));
-    HZ_HIP(hipMemcpyAsync(w.smap, m.systems.data(), sizeof(SysMap) * m.systems.size(), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(hz::k_sc_init, dim3(1), dim3(256), 0, s, w.sc, 1, rtol, maxcycles);
     const double2* Aop = A;
     if (jacobi) {
@@ -1114,8 +1103,7 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     hz::BicgArgs<double> ba{};
     ba.G = m.G;
     ba.stride = bicg_stride(m.G);  // room for the sub-block products' slots (shared regions C and I)
-    ba.bmap = w.bmap;
-    ba.smap = w.smap;
+    ba.one = m.one;
     ba.ndone = w.ndone;
     ba.row_ptr = rp;
     ba.col_idx = ci;
@@ -1150,8 +1138,7 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     la.stride = ba.stride;
     const bool sub = L == 1;  // the tile row loop: AU and AR as sub-blocks with the LDS result ring
     la.pf = sub ? hz::sol_subs(m.G) : 1;
-    la.bmap = w.bmap;
-    la.smap = w.smap;
+    la.one = m.one;
     la.ndone = w.ndone;
     la.row_ptr = rp;
     la.col_idx = ci;
@@ -1234,14 +1221,12 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
 
 // ------------------------------------------------------------------ TFQMR
 
-// Workspace: scalars, partials, the one-system map, the done counter, the
+// Workspace: scalars, partials, the done counter, the
 // TFQMR scalars, r_0, r~, w, u, u', A u, A u', v, d, a residual vector,
 // Jacobi D^{-1} and A D^{-1}.
 struct QWs {
     SolverScal* sc;
     double* part;
-    BlockMap* bmap;
-    SysMap* smap;
     int* ndone;
     hz::TScal* tq;
     double2 *r0, *rt, *w, *u, *u1, *au, *au1, *v, *d, *t;
@@ -1260,8 +1245,6 @@ size_t qws_layout(int n, int64_t nnz, bool jacobi, char* base, QWs* out) {
     QWs w{};
     w.sc = static_cast<SolverScal*>(take(sizeof(SolverScal)));
     w.part = static_cast<double*>(take(sizeof(double) * size_t(hz::kParts) * size_t(kMaxGrid)));
-    w.bmap = static_cast<BlockMap*>(take(sizeof(BlockMap) * size_t(kMaxGrid)));
-    w.smap = static_cast<SysMap*>(take(sizeof(SysMap)));
     w.ndone = static_cast<int*>(take(sizeof(int)));
     w.tq = static_cast<hz::TScal*>(take(sizeof(hz::TScal)));
     for (double2** v : {&w.r0, &w.rt, &w.w, &w.u, &w.u1, &w.au, &w.au1, &w.v, &w.d, &w.t})
@@ -1288,8 +1271,6 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     const WorkMap m = build_map(1, row_off, L);
     QWs w;
     qws_layout(n, nnz, jacobi, ws, &w);
-    HZ_HIP(hipMemcpyAsync(w.bmap, m.blocks.data(), sizeof(BlockMap) * m.blocks.size(), hipMemcpyHostToDevice, s));
-    HZ_HIP(hipMemcpyAsync(w.smap, m.systems.data(), sizeof(SysMap) * m.systems.size(), hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(hz::k_sc_init, dim3(1), dim3(256), 0, s, w.sc, 1, rtol, maxiter);
     const double2* Aop = A;
     if (jacobi) {
@@ -1302,8 +1283,7 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     hz::BicgArgs<double> ba{};  // the BiCGStab set-up and finishing kernels on the same map and scalars
     ba.G = m.G;
     ba.stride = m.stride;
-    ba.bmap = w.bmap;
-    ba.smap = w.smap;
+    ba.one = m.one;
     ba.ndone = w.ndone;
     ba.row_ptr = rp;
     ba.col_idx = ci;
@@ -1328,8 +1308,7 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     hz::QArgs qa{};
     qa.G = m.G;
     qa.stride = m.stride;
-    qa.bmap = w.bmap;
-    qa.smap = w.smap;
+    qa.one = m.one;
     qa.ndone = w.ndone;
     qa.row_ptr = rp;
     qa.col_idx = ci;
@@ -1358,7 +1337,7 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     HZ_HIP(hipStreamSynchronize(s));
     if (hs->bad_diag) return HZ_ERR_INVALID;
     int launched = 0, poll = 8, rc = HZ_OK;
-    const bool fused = choose_fused(h, n);  // K3 in one launch (two gathered vectors) or gather-light
+    const bool fused = choose_fused(h, n, kFusedMaxRowsQ);  // K3 in one launch (two gathered vectors) or gather-light
     if (*h->hflag < 1) {
         while (launched < maxiter) {
             const int k_n = (maxiter - launched) < poll ? (maxiter - launched) : poll;
@@ -1918,21 +1897,12 @@ int solve_mixed(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, cons
 template <typename T>
 int launch_iterations(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>& a0, int L, int k,
                       bool fused) {
-    const dim3 G(m.G), B(kBlock);
     const hz::BicgArgs<T> a = iteration_args(m, a0, L, fused);
     const bool sub = sub_products<T>(m, L, fused);
     const int family = (fused ? 3 : 4) + (sizeof(T) == 4 ? 10 : 0);
     return launch_chunk(h, s, chunk_key(family, L, k, 0, a), [&](hipStream_t q) {
         with_lanes(L, [&]<int LL, int UU>() {
-            for (int i = 0; i < k; ++i) {
-                if (fused) {
-                    hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU>), G, B, 0, q, a);
-                    hipLaunchKernelGGL((hz::k_bicg_B<T, LL, UU>), G, B, 0, q, a);
-                } else {
-                    enqueue_gather_light<T, LL, UU>(q, m, a, sub);
-                }
-                hipLaunchKernelGGL((hz::k_bicg_C<T>), G, B, 0, q, a);
-            }
+            for (int i = 0; i < k; ++i) enqueue_iteration<T, LL, UU>(q, m, a, fused, sub);
         });
     });
 }
@@ -2017,9 +1987,7 @@ int solve_mixed_reliable(hz_handle* h, hipStream_t s, int n, int nnz, const int*
         HZ_HIP(hipMemcpyAsync(hi, mw.in.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
         HZ_HIP(hipStreamSynchronize(s));
         if (hi->pending && !hi->done) {  // conclude a half-step exit
-            with_lanes(L, [&]<int LL, int UU>() {
-                hipLaunchKernelGGL((hz::k_bicg_P<float>), dim3(m.G), B, 0, s, ai);
-            });
+            hipLaunchKernelGGL((hz::k_bicg_end<float>), one, B, 0, s, ai);
             HZ_HIP(hipMemcpyAsync(hi, mw.in.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
             HZ_HIP(hipStreamSynchronize(s));
         }
@@ -2058,6 +2026,8 @@ int solve_mixed_reliable(hz_handle* h, hipStream_t s, int n, int nnz, const int*
         } else {
             hipLaunchKernelGGL(hz::k_ru_replace, dim3(m.G), B, 0, s, ai, static_cast<const double2*>(mw.r64),
                                static_cast<const SolverScal*>(mw.outer));
+            hipLaunchKernelGGL(hz::k_ru_direction, dim3(m.G), B, 0, s, ai);
+            hipLaunchKernelGGL(hz::k_ru_rho, one, B, 0, s, ai);
             HZ_HIP(hipGetLastError());
         }
     }

@@ -36,8 +36,7 @@ enum : int { BD_MR = 5 };                                  // the minimal-residu
 
 struct LArgs {
     int G, stride;  // one-system map of the solver launches
-    const BlockMap* bmap;
-    const SysMap* smap;
+    OneMap one;
     int* ndone;
     const int* __restrict__ row_ptr;
     const int* __restrict__ col_idx;
@@ -55,24 +54,8 @@ struct LArgs {
     int pf = 1;       // partial slots per block that AU and AR write (sol_subs(G) when they run as sub-blocks)
 };
 
-__device__ __forceinline__ SysBlock lblock(const LArgs& a) {
-    SysBlock q;
-    q.lb = logical_block(blockIdx.x, a.G);
-    const BlockMap m = a.bmap[q.lb];
-    q.sys = m.sys;
-    q.local = m.local;
-    q.rw.x0 = m.x0;
-    q.rw.x1 = m.x1;
-    q.rw.k = m.k;
-    q.rw.K = m.K;
-    if (m.sys >= 0) {
-        const SysMap sm = a.smap[m.sys];
-        q.gbeg = sm.gbeg;
-        q.gcnt = sm.gcnt;
-    } else {
-        q.gbeg = q.gcnt = 0;
-    }
-    return q;
+__device__ __forceinline__ SysBlock lblock(const LArgs& a, int F = 1) {
+    return map_block(a.one, nullptr, nullptr, a.G, F, blockIdx.x);
 }
 
 __device__ __forceinline__ double2 zneg_mul(double2 a, double2 b) {  // -(a b)
@@ -148,7 +131,7 @@ __global__ HZ_STREAM_BOUNDS void k_l_AU(const LArgs a) {
                                e[0] = c.x;
                                e[1] = c.y;
                            });
-    store_sys_partials<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 // R: alpha, r_i -= alpha u_{i+1} (i <= j), x += alpha u_0
@@ -200,14 +183,14 @@ __global__ HZ_STREAM_BOUNDS void k_l_AR(const LArgs a) {
                                e[0] = c.x;
                                e[1] = c.y;
                            });
-    store_sys_partials<3>(a.part + kPartC * a.stride, a.stride, q.lb, e);
+    store_sys_partials<3, epi_stride(L)>(a.part + kPartC * a.stride, a.stride, q.lb, e);
 }
 
 // AU and AR on a large system: the tile loop of the standalone product as
 // pf = sol_subs(G) blocks of kSpBlock threads per block of the map (r~ loaded with the
 // tile, the product held in the LDS ring), one partial slot per sub-block.
 __global__ __launch_bounds__(kSpBlock) void k_l_AUt(const LArgs a) {
-    const SubBlock q = sub_block_of(a.bmap, a.G, a.pf);
+    const SysBlock q = lblock(a, a.pf);
     if (q.sys < 0 || a.sc[q.sys].done) return;
     const double2* __restrict__ uj = a.u[a.j];
     double2* __restrict__ un = a.u[a.j + 1];
@@ -221,11 +204,11 @@ __global__ __launch_bounds__(kSpBlock) void k_l_AUt(const LArgs a) {
             e[1] = c.y;
         },
         [un](int64_t row, double2 acc) { un[row] = acc; });
-    store_sub_partials<2>(a.part + kPartA * a.stride, a.stride, q.ls, e);
+    store_sys_partials<2, kTileLanes, 0, kSpBlock>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 __global__ __launch_bounds__(kSpBlock) void k_l_ARt(const LArgs a) {
-    const SubBlock q = sub_block_of(a.bmap, a.G, a.pf);
+    const SysBlock q = lblock(a, a.pf);
     if (q.sys < 0 || a.sc[q.sys].done) return;
     const double2* __restrict__ rj = a.r[a.j];
     double2* __restrict__ rn = a.r[a.j + 1];
@@ -239,7 +222,7 @@ __global__ __launch_bounds__(kSpBlock) void k_l_ARt(const LArgs a) {
             e[1] = c.y;
         },
         [rn](int64_t row, double2 acc) { rn[row] = acc; });
-    store_sub_partials<3>(a.part + kPartC * a.stride, a.stride, q.ls, e);
+    store_sys_partials<3, kTileLanes, 0, kSpBlock>(a.part + kPartC * a.stride, a.stride, q.lb, e);
 }
 
 // Gram partials of <r_p, r_q>, 0 <= p <= q <= ELL, pair index in row-major

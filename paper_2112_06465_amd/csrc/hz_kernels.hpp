@@ -29,11 +29,11 @@ constexpr int kMaxGrid = 512;  // bound on blocks (= partials) of a reducing lau
 #define HZ_STREAM_BOUNDS __launch_bounds__(1024, 8)  // 8 waves per SIMD (two blocks per CU): <= 64 VGPRs
 
 // partial-sum regions (component index; component c lives at part[c * kMaxGrid + block])
-constexpr int kPartA = 0;  // <rhat, v>                      (2)
-constexpr int kPartB = 2;  // ||s||^2, <t, s>, ||t||^2         (4)
-constexpr int kPartC = 6;  // <rhat, r>, ||r||^2               (3)
-constexpr int kPartI = 9;  // ||b||^2 / residual norms          (1)
-constexpr int kParts = 10;
+constexpr int kPartA = 0;   // <rhat, v>                                             (2)
+constexpr int kPartB = 2;   // ||s||^2, <t, s>, ||t||^2, <rhat, t>, <rhat, s>          (8)
+constexpr int kPartC = 10;  // <rhat, r>, ||r||^2                                    (3)
+constexpr int kPartI = 13;  // ||b||^2 / residual norms                              (1)
+constexpr int kParts = 14;
 
 // ------------------------------------------------------------------ complex
 
@@ -200,6 +200,46 @@ template <int K, int NT = kBlock> __device__ __forceinline__ void block_sum(doub
     }
 }
 
+// Sum over a wave of values that only the lanes l = 0 mod STRIDE hold (the
+// others hold 0), in the lanes l = 0 mod STRIDE: the steps below STRIDE are
+// left out.  Rotations within a row of 16 pair every lane with the one s away.
+template <int S> __device__ __forceinline__ double row_ror(double v) { return dpp<0x120 + S>(v); }
+template <int STRIDE> __device__ __forceinline__ double wave_sum(double v) {
+    if constexpr (STRIDE <= 1) v += row_ror<1>(v);
+    if constexpr (STRIDE <= 2) v += row_ror<2>(v);
+    if constexpr (STRIDE <= 4) v += row_ror<4>(v);
+    if constexpr (STRIDE <= 8) v += row_ror<8>(v);
+    if constexpr (STRIDE <= 16) v += swz<kSwzXor16>(v);
+    if constexpr (STRIDE <= 32) v += __shfl_xor(v, 32);
+    return v;
+}
+
+// The block's totals of K doubles to out[k * stride], k < K: wave sums to LDS,
+// one barrier, then the first wave adds the NW wave sums of 64 / NW components
+// at a time.  STRIDE: the lanes that hold values (wave_sum).  TAG separates
+// the LDS of several calls in one kernel.
+template <int K, int STRIDE = 1, int TAG = 0, int NT = kBlock>
+__device__ __forceinline__ void block_store(double* __restrict__ out, int stride, double (&v)[K]) {
+    constexpr int NW = NT / kWave, PER = kWave / NW;
+    __shared__ double lds[K][NW];
+    const int wid = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum<STRIDE>(v[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) lds[k][wid] = v[k];
+    }
+    __syncthreads();
+    if (wid == 0) {
+#pragma unroll
+        for (int k0 = 0; k0 < K; k0 += PER) {
+            const int k = k0 + lane / NW;
+            const double t = group_sum<NW>(lds[k < K ? k : K - 1][lane % NW]);
+            if (k < K && lane % NW == 0) out[k * stride] = t;
+        }
+    }
+}
+
 // Sum of K partial components (component k at part[k*kMaxGrid + g], g < G)
 // in a fixed order, delivered to every thread of the block.
 // (G <= kMaxGrid <= kBlock: one partial per thread, the K loads issued
@@ -302,8 +342,8 @@ __device__ __forceinline__ RowRange rows_of_block(int n, Geom geo) {
 // deterministic.
 template <typename T, int L, int U, typename Op>
 __device__ __forceinline__ cx<T> row_partial(int beg, int end, int lane, const int* __restrict__ ci,
-                                             const cx<T>* __restrict__ vals, Op op) {
-    cx<T> acc = mk<T>(T(0), T(0));
+                                             const cx<T>* __restrict__ vals, Op op,
+                                             cx<T> acc = mk<T>(T(0), T(0))) {
     for (int base = beg + lane; base < end; base += L * U) {
         int c[U];
         cx<T> a[U], o[U];
@@ -410,16 +450,55 @@ __device__ __forceinline__ void for_tiles(const Rows& rw, const int* __restrict_
     }
 }
 
+// A thread's share of the block's first tile of rows, loaded ahead of a
+// kernel's head (whose loads, reduction and scalar arithmetic then run while
+// these are in flight): the bounds of its row and, with UP = U, its first U
+// entries.  (The chain row_ptr -> entries -> gathers is three round trips to
+// memory, most of the time of a small system's product.)
+template <typename T, int UP> struct FirstRow {
+    int beg = 0, end = 0;
+    int c[UP > 0 ? UP : 1];
+    cx<T> a[UP > 0 ? UP : 1];
+};
+template <typename T, int L, int UP>
+__device__ __forceinline__ void first_row(FirstRow<T, UP>& f, const Rows& rw, const int* __restrict__ rp,
+                                          const int* __restrict__ ci, const cx<T>* __restrict__ vals) {
+    if constexpr (L > 1) {
+        constexpr int RPS = kBlock / L;
+        const int64_t row = rw.x0 + (int64_t)rw.k * RPS + threadIdx.x / L;
+        if (row < rw.x1) {
+            f.beg = rp[row];
+            f.end = rp[row + 1];
+        }
+        if constexpr (UP > 0) {
+            const int lane = threadIdx.x % L;
+#pragma unroll
+            for (int u = 0; u < UP; ++u) {
+                f.c[u] = 0;
+                f.a[u] = mk<T>(T(0), T(0));
+            }
+            if (f.beg + lane < f.end) {
+#pragma unroll
+                for (int u = 0; u < UP; ++u) {
+                    const int p = f.beg + lane + u * L < f.end ? f.beg + lane + u * L : f.end - 1;
+                    f.c[u] = ci[p];
+                    f.a[u] = vals[p];
+                }
+            }
+        }
+    }
+}
+
 // Row loop of a block over its tiles of RPS = kBlock/L rows (g = thread / L
-// picks the row of the tile).  With
-// PF the next step's row_ptr pair is loaded before the current row's product,
-// so that load's latency overlaps the current step (two more live registers;
-// kernels whose column functor gathers several vectors leave it off to stay
-// within 64 VGPRs).  epi(row, total) runs in lane 0 of each row's group after
+// picks the row of the tile).  The next step's row_ptr pair is loaded before
+// the current row's product, so that load's latency overlaps the current
+// step.  `f` holds the first tile's bounds, and its entries if UP = U (first_row).
+// epi(row, total) runs in lane 0 of each row's group after
 // the group sum.  The trip count is uniform across the block.
-template <typename T, int L, int U, bool PF = true, typename Op, typename Epi, typename Pre = NoPre>
-__device__ __forceinline__ void for_rows(const Rows& rw, const int* __restrict__ rp, const int* __restrict__ ci,
-                                         const cx<T>* __restrict__ vals, Op op, Epi epi, Pre pre = Pre{}) {
+template <typename T, int L, int U, int UP, typename Op, typename Epi, typename Pre = NoPre>
+__device__ __forceinline__ void for_rows(const FirstRow<T, UP>& f, const Rows& rw, const int* __restrict__ rp,
+                                         const int* __restrict__ ci, const cx<T>* __restrict__ vals, Op op, Epi epi,
+                                         Pre pre = Pre{}) {
     constexpr bool kPre = !std::is_same_v<Pre, NoPre>;
     if constexpr (L == 1) {
         for_tiles<T>(rw, rp, ci, vals, op, epi, pre);
@@ -429,28 +508,36 @@ __device__ __forceinline__ void for_rows(const Rows& rw, const int* __restrict__
     const int g = threadIdx.x / L, lane = threadIdx.x % L;
     const int64_t first = rw.x0 + (int64_t)rw.k * RPS, step = (int64_t)rw.K * RPS, r1 = rw.x1;
     int64_t row = first + g;
-    int beg = 0, end = 0;
-    if (row < r1) {
-        beg = rp[row];
-        end = rp[row + 1];
-    }
+    int beg = f.beg, end = f.end;
     for (int64_t base = first; base < r1; base += step) {
         const int64_t nrow = row + step;
         int nbeg = 0, nend = 0;
-        if (PF && nrow < r1) {
+        if (nrow < r1) {
             nbeg = rp[nrow];
             nend = rp[nrow + 1];
         }
         const bool ok = row < r1;
-        if (!PF && ok && base != first) {
-            beg = rp[row];
-            end = rp[row + 1];
-        }
         cx<T> acc = mk<T>(T(0), T(0));
         decltype(pre(row)) w{};
         if (ok) {
             if constexpr (kPre) w = pre(row);
-            acc = row_partial<T, L, U>(beg, end, lane, ci, vals, op);
+            if (UP > 0 && base == first) {  // uniform: the prefetched entries, in the order of row_partial
+                if (beg + lane < end) {
+                    cx<T> o[UP > 0 ? UP : 1];
+#pragma unroll
+                    for (int u = 0; u < UP; ++u) o[u] = op(f.c[u]);
+#pragma unroll
+                    for (int u = 0; u < UP; ++u) {
+                        const bool in = beg + lane + u * L < end;
+                        const cx<T> nx = cfma<T>(f.a[u], o[u], acc);
+                        acc.x = in ? nx.x : acc.x;
+                        acc.y = in ? nx.y : acc.y;
+                    }
+                }
+                acc = row_partial<T, L, U>(beg + L * U, end, lane, ci, vals, op, acc);
+            } else {
+                acc = row_partial<T, L, U>(beg, end, lane, ci, vals, op);
+            }
         }
         acc.x = group_sum<L>(acc.x);
         acc.y = group_sum<L>(acc.y);
@@ -462,11 +549,18 @@ __device__ __forceinline__ void for_rows(const Rows& rw, const int* __restrict__
             }
         }
         row = nrow;
-        if (PF) {
-            beg = nbeg;
-            end = nend;
-        }
+        beg = nbeg;
+        end = nend;
     }
+}
+
+// The same without a head to hide the first loads behind.
+template <typename T, int L, int U, typename Op, typename Epi, typename Pre = NoPre>
+__device__ __forceinline__ void for_rows(const Rows& rw, const int* __restrict__ rp, const int* __restrict__ ci,
+                                         const cx<T>* __restrict__ vals, Op op, Epi epi, Pre pre = Pre{}) {
+    FirstRow<T, 0> f;
+    first_row<T, L, 0>(f, rw, rp, ci, vals);
+    for_rows<T, L, U, 0>(f, rw, rp, ci, vals, op, epi, pre);
 }
 
 // ------------------------------------------------------------------ solver scalars (device resident)
@@ -524,10 +618,23 @@ struct SysMap {
     int gbeg, gcnt, row0, row1;
 };
 
+// The map of a one-system launch by value: groups of K blocks, one per XCD
+// (or one group of fewer than 8 blocks), each owning gr rows.  A block finds
+// its rows from its index and these arguments; from the BlockMap and SysMap
+// arrays of a batch it takes two dependent loads, each a round trip past the
+// L2 that the kernel boundary has emptied, before any other load can start.
+struct OneMap {
+    int n = 0;       // rows; 0: a batch, take the arrays
+    int groups = 1;  // 8 or 1
+    int K = 1, gr = 0;
+};
+
 template <typename T> struct BicgArgs {
     int G;       // blocks of every solver launch (a multiple of 8, or < 8)
     int stride;  // partial component stride (>= pf G)
     int pf = 1;  // partial slots per block in regions A and B (sol_subs(G) when the products run as sub-blocks)
+    OneMap one;
+    int spare = 0;  // (no padding bytes: the graph cache compares these structs bytewise)
     const BlockMap* bmap;
     const SysMap* smap;
     int* ndone;  // systems finished so far
@@ -537,8 +644,8 @@ template <typename T> struct BicgArgs {
     const cx<T>* b;
     cx<T>* r;
     const cx<T>* rh;
-    cx<T>* p[2];
-    cx<T>* v[2];
+    cx<T>* p;
+    cx<T>* v;
     cx<T>* s;
     cx<T>* t;
     cx<T>* x;
@@ -551,24 +658,47 @@ struct SysBlock {
     Rows rw;
     int gbeg, gcnt;
 };
-template <typename T> __device__ __forceinline__ SysBlock sys_block(const BicgArgs<T>& a) {
+// Block `b` of a launch of F G blocks over the map: F sub-blocks share the
+// rows of each logical block, lb counts them, and partials [gbeg, gbeg +
+// gcnt) are those of the launch's own blocks.
+__device__ __forceinline__ SysBlock map_block(const OneMap& one, const BlockMap* bmap, const SysMap* smap, int G,
+                                              int F, int b) {
     SysBlock q;
-    q.lb = logical_block(blockIdx.x, a.G);
-    const BlockMap m = a.bmap[q.lb];
+    if (one.n > 0) {
+        const int x = one.groups == kXcd ? b % kXcd : 0, k = one.groups == kXcd ? b / kXcd : b;
+        q.rw.k = k;
+        q.rw.K = F * one.K;
+        q.rw.x0 = (int64_t)x * one.gr;
+        q.rw.x1 = q.rw.x0 + one.gr < one.n ? q.rw.x0 + one.gr : one.n;
+        q.lb = q.local = x * F * one.K + k;
+        q.sys = 0;
+        q.gbeg = 0;
+        q.gcnt = F * G;
+        return q;
+    }
+    q.lb = logical_block(b, F * G);
+    const BlockMap m = bmap[q.lb / F];
     q.sys = m.sys;
-    q.local = m.local;
+    q.local = F * m.local + q.lb % F;
     q.rw.x0 = m.x0;
     q.rw.x1 = m.x1;
-    q.rw.k = m.k;
-    q.rw.K = m.K;
+    q.rw.k = F * m.k + q.lb % F;
+    q.rw.K = F * m.K;
     if (m.sys >= 0) {
-        const SysMap sm = a.smap[m.sys];
-        q.gbeg = sm.gbeg;
-        q.gcnt = sm.gcnt;
+        const SysMap sm = smap[m.sys];
+        q.gbeg = F * sm.gbeg;
+        q.gcnt = F * sm.gcnt;
     } else {
         q.gbeg = q.gcnt = 0;
     }
     return q;
+}
+template <typename T> __device__ __forceinline__ SysBlock sys_block(const BicgArgs<T>& a) {
+    return map_block(a.one, a.bmap, a.smap, a.G, 1, blockIdx.x);
+}
+// Partial range of system j (for the one-block-per-system kernels).
+template <typename T> __device__ __forceinline__ SysMap sys_range(const BicgArgs<T>& a, int j) {
+    return a.one.n > 0 ? SysMap{0, a.G, 0, a.one.n} : a.smap[j];
 }
 
 __device__ __forceinline__ bool sys_leader(const SysBlock& q) { return q.local == 0 && threadIdx.x == 0; }
@@ -582,66 +712,95 @@ __device__ __forceinline__ void finish(SolverScal* sc, int* ndone, int status, i
     atomicAdd(ndone, 1);
 }
 
-// Sum of K components over one system's partials [gbeg, gbeg + gcnt), in a
-// fixed order, delivered to every thread of the block.
-// Thread t takes partial t of every component; the K loads are issued
-// together (so their latencies overlap).  Waves wholly past the partials
-// load nothing (a wave-uniform branch); in the wave that straddles the end,
-// the lanes past it read the last partial, a duplicate address that the
-// load instruction merges (clamping every idle thread of every block to one
-// address would make that address a hot spot).  A system's blocks never
-// exceed kMaxGrid <= kBlock (gcnt >= 1); the loop for gcnt > kBlock only
-// keeps the function general.
-__device__ __forceinline__ int wave_base() {
-    return __builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~(kWave - 1);
-}
-template <int K>
-__device__ __forceinline__ void sys_sum(const double* __restrict__ part, int stride, int gbeg, int gcnt,
-                                        double (&out)[K]) {
-    static_assert(kMaxGrid <= kBlock, "one partial per thread");
-    __shared__ double bc[K];
-    const int t = threadIdx.x;
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) / kWave; }
+
+// The sum of K components of partials by the 16 waves of a block: component
+// k by the W = 16 / K (rounded down to a power of two) waves k W .. k W + W - 1,
+// wave i of them taking its partials i, i + W, ... in rounds of 64.  load()
+// issues the loads of the first kHeadNV rounds of each wave, all at once;
+// store() waits for them, adds the rest if any, and puts the wave's sum into
+// tot; after a barrier at() adds the W sums.  The order is fixed.  With one
+// partial of every component per thread, and all waves adding all components,
+// the eight sums of a head took the SIMDs about 1 us (7.3 us for the C-kernel of
+// 8,000 rows, 4.3 us with a wave per component).
+constexpr int kHeadNV = 4;
+constexpr int head_waves(int K) { return K > 8 ? 1 : (K > 4 ? 2 : (K > 2 ? 4 : 8)); }
+template <int K> struct PartSum {
+    static constexpr int W = head_waves(K);
+    static_assert(K * W <= kBlock / kWave, "K W waves");
+    double v[kHeadNV];
+    const double* part;
+    int cnt, g0;
+    // the component of this wave (a uniform value; K or more: none)
+    static __device__ __forceinline__ int comp() { return wave_id() / W; }
+    // p: the first partial of this wave's component, c >= 1 of them
+    __device__ __forceinline__ void load(const double* __restrict__ p, int c) {
+        part = p;
+        cnt = c;
+        g0 = (wave_id() % W) * kWave;
+        const int lane = threadIdx.x % kWave;
 #pragma unroll
-    for (int k = 0; k < K; ++k) out[k] = 0.0;
-    if (wave_base() < gcnt) {
-        const bool mine = t < gcnt;
-        const int g0 = gbeg + (mine ? t : gcnt - 1);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const double v = part[k * stride + g0];
-            out[k] = mine ? v : 0.0;
+        for (int j = 0; j < kHeadNV; ++j) {
+            v[j] = 0.0;
+            const int r = g0 + j * W * kWave;
+            if (r < cnt) v[j] = p[r + lane < cnt ? r + lane : cnt - 1];  // uniform; masked in store()
         }
     }
-    if (gcnt > kBlock) {
+    __device__ __forceinline__ void store(double* tot) {
+        const int lane = threadIdx.x % kWave;
+        double t = masked(0, lane);
+        for (int g = kHeadNV * W * kWave; g < cnt; g += kHeadNV * W * kWave) {  // uniform
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            for (int g = t + kBlock; g < gcnt; g += kBlock) out[k] += part[k * stride + gbeg + g];
+            for (int j = 0; j < kHeadNV; ++j) {
+                const int r = g + g0 + j * W * kWave;
+                if (r < cnt) v[j] = part[r + lane < cnt ? r + lane : cnt - 1];
+            }
+            t += masked(g, lane);
+        }
+        t = wave_sum<1>(t);
+        if (lane == 0) tot[wave_id()] = t;
     }
-    block_sum<K>(out);
-    if (threadIdx.x == 0) {
+    // the sum of v, whose rounds start at partial g
+    __device__ __forceinline__ double masked(int g, int lane) const {
+        double m[kHeadNV];
 #pragma unroll
-        for (int k = 0; k < K; ++k) bc[k] = out[k];
+        for (int j = 0; j < kHeadNV; ++j) m[j] = g + g0 + j * W * kWave + lane < cnt ? v[j] : 0.0;
+        return (m[0] + m[1]) + (m[2] + m[3]);
+    }
+    static __device__ __forceinline__ double at(const double* tot, int k) {
+        double t = tot[k * W];
+#pragma unroll
+        for (int i = 1; i < W; ++i) t += tot[k * W + i];
+        return t;
+    }
+};
+
+// Sum of K components over one system's partials [gbeg, gbeg + gcnt), in a
+// fixed order, delivered to every thread of the block (component k at
+// part[k * stride + g]).  One barrier.
+template <int K, int TAG = 0>
+__device__ __forceinline__ void sys_sum(const double* __restrict__ part, int stride, int gbeg, int gcnt,
+                                        double (&out)[K]) {
+    __shared__ double tot[kBlock / kWave];
+    const int c = PartSum<K>::comp();
+    if (c < K) {
+        PartSum<K> ps;
+        ps.load(part + c * stride + gbeg, gcnt);
+        ps.store(tot);
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) out[k] = bc[k];
+    for (int k = 0; k < K; ++k) out[k] = PartSum<K>::at(tot, k);
 }
 
-// Thread 0 writes the block's totals to slot pf lb of each component and
-// zeros to the pf - 1 slots after it (a region whose other components come
-// from a launch of pf times as many blocks).
-template <int K>
-__device__ __forceinline__ void store_sys_partials(double* __restrict__ part, int stride, int lb, double (&e)[K],
-                                                   int pf = 1) {
-    block_sum<K>(e);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            part[k * stride + pf * lb] = e[k];
-            for (int f = 1; f < pf; ++f) part[k * stride + pf * lb + f] = 0.0;
-        }
-    }
+// The block's totals to slot lb of each component.
+template <int K, int STRIDE = 1, int TAG = 0, int NT = kBlock>
+__device__ __forceinline__ void store_sys_partials(double* __restrict__ part, int stride, int lb, double (&e)[K]) {
+    block_store<K, STRIDE, TAG, NT>(part + lb, stride, e);
 }
+
+// The lanes of a row loop's epilogue with lane code L (L = 1: the tiles' kSolTileLanes).
+constexpr int epi_stride(int L) { return L == 1 ? kSolTileLanes : L; }
 
 // ------------------------------------------------------------------ standalone SpMV with residual epilogue
 
@@ -698,331 +857,414 @@ __global__ HZ_STREAM_BOUNDS void k_sys_resid(const BicgArgs<T> a, const cx<T>* _
         e[0] = __builtin_fma((double)acc.y, (double)acc.y, e[0]);
         y[row] = acc;
     });
-    store_sys_partials<1>(a.part + kPartI * a.stride, a.stride, q.lb, e);
+    store_sys_partials<1, epi_stride(L)>(a.part + kPartI * a.stride, a.stride, q.lb, e);
 }
 
-// ------------------------------------------------------------------ BiCGStab: three kernels per iteration
+// ------------------------------------------------------------------ BiCGStab: three or four kernels per iteration
 //
 // Iteration i (Section 7's P-BiCGSTAB, right-preconditioned; A here is the
 // column-scaled matrix under Jacobi), for every system of the launch:
-//   A-kernel: decide the end of iteration i-1 from <rhat,r>, ||r||; beta;
-//             v = A p with p = r + beta (p_old - omega v_old) formed for every
-//             gathered column; store p, v; partial <rhat, v>.
-//   B-kernel: alpha = rho / <rhat, v>; t = A s with s = r - alpha v formed for
-//             every gathered column; store s, t; partials ||s||^2, <t,s>, ||t||^2.
-//   C-kernel: half-step test on ||s||; omega = <t,s>/<t,t>;
-//             x += alpha p + omega s; r = s - omega t; partials <rhat,r>, ||r||^2.
-// p and v are double-buffered by the parity of i, so the A-kernel reads the
-// old vectors while writing the new ones.  Systems of a batch share nothing
-// but the launches: each has its own scalars, partial range and exit.
+//   A-kernel: v = A p; partial <rhat, v>.  No scalars: it starts on its rows at once.
+//   S-kernel: the end of iteration i-1 decided from ||r||; alpha = rho / <rhat, v>;
+//             s = r - alpha v.
+//   B-kernel: t = A s; partials ||s||^2, <t, s>, ||t||^2, <rhat, t>, <rhat, s>.
+//   C-kernel: half-step test on ||s||; omega = <t, s>/<t, t>;
+//             rho_{i+1} = <rhat, s> - omega <rhat, t>; beta;
+//             x += alpha p + omega s; r = s - omega t; p = r + beta (p - omega v);
+//             partial ||r||^2.
+// rho of the next iteration comes from sums that the B-kernel takes beside
+// the others (<rhat, r> by linearity; <rhat, s> vanishes but for rounding, so
+// no cancellation is added), which lets one pass update x, r and p: a kernel
+// that read r, p, v again and wrote p is gone, with its launch (48 n bytes an
+// iteration), and rhat is read by the two products only.
+//
+// On a small system the S-kernel is folded into the B-kernel, which forms s
+// for every gathered column (k_bicg_SB), so an iteration is three
+// launches; see choose_fused.
+//
+// Systems of a batch share nothing but the launches: each has its own
+// scalars, partial range and exit.  The heads issue every load (scalars,
+// partials, first rows or elements) before the reduction's one barrier, so
+// their latencies overlap; decisions are taken after it.
 
-// Start of iteration i = sc->iter for the block's system: conclude iteration
-// i-1 (convergence on ||r||, breakdown, iteration limit) from the partials
-// <rhat, r>, ||r||^2, then rho_i and beta.  Returns false when the system's
-// solve has ended (every block of the system returns); its leader records
-// the decision.
-struct IterStart {
-    int it;
-    double2 rho, beta, omega;
-};
-// EARLY: the scalars written by earlier kernels are read before the
-// reduction's barriers (a barrier is a fence, so loads after it cannot be
-// hoisted above it), overlapping their latency with the partial loads; the
-// fused A-kernel reads them after, as it has no registers to spare.
-template <typename T, bool EARLY = true>
-__device__ __forceinline__ bool iteration_start(const BicgArgs<T>& a, const SysBlock& q, IterStart& st) {
-    if (q.sys < 0) return false;
-    SolverScal* sc = a.sc + q.sys;
-    if (sc->done) return false;
-    if (sc->pending) {  // every block of the previous kernel has applied x += alpha p
-        if (sys_leader(q)) finish(sc, a.ndone, ST_OK, sc->pending);
-        return false;
-    }
-    const int it = sc->iter;
+// The end of iteration it - 1 (it >= 2) from ||r||^2: convergence, breakdown,
+// iteration limit, in the order of the textbook loop.  Returns the status
+// that ends the solve, or -1.
+struct EndIn {
     double bnorm, rtol;
+    double2 omega, rho, beta;  // omega of iteration it - 1; rho and beta of iteration it
     int maxiter;
-    double2 om_prev, rho_prev, al_prev;
-    auto read = [&] {
-        bnorm = sc->bnorm;
-        rtol = sc->rtol;
-        maxiter = sc->maxiter;
-        om_prev = sc->omega;
-        rho_prev = sc->rho2[(it - 1) & 1];
-        al_prev = sc->alpha;
-    };
-    if constexpr (EARLY) read();
-    double h[3];
-    sys_sum<3>(a.part + kPartC * a.stride, a.stride, q.gbeg, q.gcnt, h);
-    if constexpr (!EARLY) read();
-    const double2 rho = mk<double>(h[0], h[1]);
-    double2 beta = mk<double>(0.0, 0.0), om = mk<double>(0.0, 0.0);
-    if (it > 1) {
-        const double rel = __builtin_sqrt(h[2]) / bnorm;
-        om = om_prev;
-        int stt = -1, sit = 0, why = BD_NONE;
-        if (!__builtin_isfinite(rel)) stt = ST_NONFINITE, sit = it - 1;
-        else if (rel <= rtol) stt = ST_OK, sit = it - 1;
-        else if (zzero(om)) stt = ST_BREAKDOWN, sit = it - 1, why = BD_OMEGA;
-        else if (it - 1 >= maxiter) stt = ST_NOT_CONVERGED, sit = maxiter;
-        else if (!zfinite(rho)) stt = ST_NONFINITE, sit = it;
-        else if (zzero(rho)) stt = ST_BREAKDOWN, sit = it, why = BD_RHO;
-        else {
-            beta = zmul(zdiv(rho, rho_prev), zdiv(al_prev, om));
-            if (!zfinite(beta)) stt = ST_NONFINITE, sit = it;
+};
+__device__ __forceinline__ int iteration_end(int it, double rr, const EndIn& z, double& rel, int& sit, int& why) {
+    rel = __builtin_sqrt(rr) / z.bnorm;
+    why = BD_NONE;
+    sit = it - 1;
+    if (!__builtin_isfinite(rel)) return ST_NONFINITE;
+    if (rel <= z.rtol) return ST_OK;
+    if (zzero(z.omega)) {
+        why = BD_OMEGA;
+        return ST_BREAKDOWN;
+    }
+    if (it - 1 >= z.maxiter) {
+        sit = z.maxiter;
+        return ST_NOT_CONVERGED;
+    }
+    sit = it;
+    if (!zfinite(z.rho)) return ST_NONFINITE;
+    if (zzero(z.rho)) {
+        why = BD_RHO;
+        return ST_BREAKDOWN;
+    }
+    if (!zfinite(z.beta)) return ST_NONFINITE;
+    return -1;
+}
+
+// Head of the S-kernel and of the B-kernel that contains it: conclude a
+// half-step exit or iteration it - 1, then alpha = rho / <rhat, v>.  load()
+// issues the loads; run() returns false when the system's solve has ended
+// (every block of the system returns); its leader records the decision.  The
+// scalar arithmetic (FP64 divisions and a square root) runs in the first wave
+// only and is broadcast: in all 16 waves it kept the SIMDs busy for longer
+// than the extra barrier costs.
+struct AlphaHead {
+    PartSum<3> ps;
+    int done, pending, it;
+    EndIn z;
+
+    template <typename T> __device__ __forceinline__ void load(const BicgArgs<T>& a, const SysBlock& q) {
+        const SolverScal* sc = a.sc + q.sys;
+        done = sc->done;
+        pending = sc->pending;
+        it = sc->iter;
+        z.bnorm = sc->bnorm;
+        z.rtol = sc->rtol;
+        z.maxiter = sc->maxiter;
+        z.omega = sc->omega;
+        z.beta = sc->beta;
+        const double2 r0 = sc->rho2[0], r1 = sc->rho2[1];
+        z.rho = (it & 1) ? r1 : r0;
+        const int c = ps.comp();  // <rhat, v>, then ||r||^2
+        if (c < 3)
+            ps.load(a.part + (c < 2 ? kPartA + c : kPartC + 2) * a.stride + (c < 2 ? a.pf : 1) * q.gbeg,
+                    (c < 2 ? a.pf : 1) * q.gcnt);
+    }
+    template <typename T> __device__ __forceinline__ bool run(const BicgArgs<T>& a, const SysBlock& q, double2& alpha) {
+        __shared__ double tot[kBlock / kWave];
+        __shared__ double2 al;
+        __shared__ int go;
+        if (ps.comp() < 3) ps.store(tot);
+        __syncthreads();
+        if (wave_id() == 0) {
+            const double s0 = ps.at(tot, 0), s1 = ps.at(tot, 1), rr = ps.at(tot, 2);
+            const int g = decide(a, q, s0, s1, rr, alpha);
+            if (threadIdx.x == 0) {
+                al = alpha;
+                go = g;
+            }
         }
-        if (sys_leader(q)) sc->relres = rel;
-        if (stt >= 0) {
-            if (sys_leader(q)) finish(sc, a.ndone, stt, sit, why);
+        __syncthreads();
+        alpha = al;
+        return go != 0;
+    }
+    template <typename T>
+    __device__ __forceinline__ bool decide(const BicgArgs<T>& a, const SysBlock& q, double s0, double s1, double rr,
+                                           double2& alpha) {
+        SolverScal* sc = a.sc + q.sys;
+        alpha = mk<double>(0.0, 0.0);
+        if (done) return false;
+        if (pending) {  // every block of the previous kernel has applied x += alpha p
+            if (sys_leader(q)) finish(sc, a.ndone, ST_OK, pending);
             return false;
         }
+        if (it > 1) {
+            double rel;
+            int sit, why;
+            const int st = iteration_end(it, rr, z, rel, sit, why);
+            if (sys_leader(q)) sc->relres = rel;
+            if (st >= 0) {
+                if (sys_leader(q)) finish(sc, a.ndone, st, sit, why);
+                return false;
+            }
+        }
+        const double2 sigma = mk<double>(s0, s1);
+        if (!zfinite(sigma) || zzero(sigma)) {
+            if (sys_leader(q))
+                finish(sc, a.ndone, zzero(sigma) ? ST_BREAKDOWN : ST_NONFINITE, it, zzero(sigma) ? BD_RHAT_V : BD_NONE);
+            return false;
+        }
+        alpha = zdiv(z.rho, sigma);
+        if (sys_leader(q)) {
+            sc->alpha = alpha;
+            sc->cur = it;
+        }
+        return true;
     }
-    if (sys_leader(q)) {
-        sc->rho2[it & 1] = rho;
-        sc->beta = beta;
-        sc->cur = it;
-    }
-    st.it = it;
-    st.rho = rho;
-    st.beta = beta;
-    st.omega = om;
-    return true;
+};
+
+// After the last iteration of a limited solve: conclude it (one block per system).
+template <typename T> __global__ HZ_STREAM_BOUNDS void k_bicg_end(const BicgArgs<T> a) {
+    const int j = blockIdx.x;
+    const SysMap sm = sys_range(a, j);
+    SolverScal* sc = a.sc + j;
+    double h[1];
+    sys_sum<1>(a.part + (kPartC + 2) * a.stride, a.stride, sm.gbeg, sm.gcnt, h);
+    if (threadIdx.x != 0 || sc->done) return;
+    if (sc->pending) return finish(sc, a.ndone, ST_OK, sc->pending);
+    const int it = sc->iter;
+    if (it <= 1) return;
+    const EndIn z{sc->bnorm, sc->rtol, sc->omega, sc->rho2[it & 1], sc->beta, sc->maxiter};
+    double rel;
+    int sit, why;
+    const int st = iteration_end(it, h[0], z, rel, sit, why);
+    sc->relres = rel;
+    if (st >= 0) finish(sc, a.ndone, st, sit, why);
 }
 
-// p_i = r_i (first iteration) or r_i + beta (p_old_i - omega v_old_i)
-template <typename T>
-__device__ __forceinline__ cx<T> p_update(bool first, cx<T> bt, cx<T> omt, cx<T> rc, cx<T> pc, cx<T> vc) {
-    if (first) return rc;
-    const cx<T> d = mk<T>(pc.x - fmaT(omt.x, vc.x, -omt.y * vc.y), pc.y - fmaT(omt.x, vc.y, omt.y * vc.x));
-    return cfma<T>(bt, d, rc);
-}
-
+// v = A p; partial <rhat, v>
 template <typename T, int L, int U>
 __global__ HZ_STREAM_BOUNDS void k_bicg_A(const BicgArgs<T> a) {
     const SysBlock q = sys_block(a);
-    IterStart st;
-    if (!iteration_start<T, false>(a, q, st)) return;
-    const int it = st.it;
-    const bool first = it == 1;
-    const cx<T> bt = narrow<T>(st.beta), omt = narrow<T>(st.omega);
-    const cx<T>* __restrict__ r = a.r;
-    const cx<T>* __restrict__ pold = a.p[(it - 1) & 1];
-    const cx<T>* __restrict__ vold = a.v[(it - 1) & 1];
-    cx<T>* __restrict__ pnew = a.p[it & 1];
-    cx<T>* __restrict__ vnew = a.v[it & 1];
-    auto pcol = [=](int c) {
-        if (first) return r[c];
-        return p_update<T>(false, bt, omt, r[c], pold[c], vold[c]);
-    };
-    double e[2] = {0.0, 0.0};
-    for_rows<T, L, U, false>(q.rw, a.row_ptr, a.col_idx, a.vals, pcol, [&](int64_t row, cx<T> acc) {
-        pnew[row] = pcol((int)row);
-        vnew[row] = acc;
-        const cx<T> w = a.rh[row];
-        double2 c = cdotacc(w.x, w.y, acc.x, acc.y, mk<double>(e[0], e[1]));
-        e[0] = c.x;
-        e[1] = c.y;
-    });
-    store_sys_partials<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
-}
-
-// alpha = rho / <rhat, v> for the block's system; false when the system ends here.
-template <typename T>
-__device__ __forceinline__ bool alpha_step(const BicgArgs<T>& a, const SysBlock& q, int& it, double2& alpha) {
-    if (q.sys < 0) return false;
-    SolverScal* sc = a.sc + q.sys;
-    if (sc->done) return false;
-    it = sc->cur;
-    const double2 rho = sc->rho2[it & 1];  // written by the iteration's first kernel; read before the barriers
-    double h[2];
-    sys_sum<2>(a.part + kPartA * a.stride, a.stride, a.pf * q.gbeg, a.pf * q.gcnt, h);
-    const double2 sigma = mk<double>(h[0], h[1]);
-    if (!zfinite(sigma) || zzero(sigma)) {
-        if (sys_leader(q)) finish(sc, a.ndone, zzero(sigma) ? ST_BREAKDOWN : ST_NONFINITE, it, zzero(sigma) ? BD_RHAT_V : BD_NONE);
-        return false;
-    }
-    alpha = zdiv(rho, sigma);
-    if (sys_leader(q)) sc->alpha = alpha;
-    return true;
-}
-
-template <typename T, int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
-    const SysBlock q = sys_block(a);
-    int it;
-    double2 alpha;
-    if (!alpha_step(a, q, it, alpha)) return;
-    const cx<T> al = narrow<T>(alpha);
-    const cx<T>* __restrict__ r = a.r;
-    const cx<T>* __restrict__ v = a.v[it & 1];
-    auto scol = [=](int c) { return cfma<T>(mk<T>(-al.x, -al.y), v[c], r[c]); };
-    double e[4] = {0.0, 0.0, 0.0, 0.0};
-    for_rows<T, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, scol, [&](int64_t row, cx<T> acc) {
-        const cx<T> s = scol((int)row);
-        a.s[row] = s;
-        a.t[row] = acc;
-        e[0] = __builtin_fma((double)s.x, (double)s.x, e[0]);
-        e[0] = __builtin_fma((double)s.y, (double)s.y, e[0]);
-        double2 c = cdotacc(acc.x, acc.y, s.x, s.y, mk<double>(e[1], e[2]));
-        e[1] = c.x;
-        e[2] = c.y;
-        e[3] = __builtin_fma((double)acc.x, (double)acc.x, e[3]);
-        e[3] = __builtin_fma((double)acc.y, (double)acc.y, e[3]);
-    });
-    store_sys_partials<4>(a.part + kPartB * a.stride, a.stride, q.lb, e);
-}
-
-template <typename T>
-__global__ HZ_STREAM_BOUNDS void k_bicg_C(const BicgArgs<T> a) {
-    const SysBlock q = sys_block(a);
     if (q.sys < 0) return;
-    SolverScal* sc = a.sc + q.sys;
-    if (sc->done) return;
-    const int it = sc->cur;
-    const double bnorm = sc->bnorm, rtol = sc->rtol;  // read before the reduction's barriers
-    const double2 alpha = sc->alpha;
-    double h[4];
-    sys_sum<4>(a.part + kPartB * a.stride, a.stride, a.pf * q.gbeg, a.pf * q.gcnt, h);
-    const double rel = __builtin_sqrt(h[0]) / bnorm;
-    const cx<T> al = narrow<T>(alpha);
-    const cx<T>* __restrict__ p = a.p[it & 1];
-    if (!__builtin_isfinite(rel)) {
-        if (sys_leader(q)) finish(sc, a.ndone, ST_NONFINITE, it);
-        return;
-    }
-    if (rel <= rtol) {  // half-step exit: x += alpha p (concluded by the next first kernel)
-        HZ_FOR_ELEMS(i, q.rw) a.x[i] = cfma<T>(al, p[i], a.x[i]);
-        if (sys_leader(q)) {
-            sc->relres = rel;
-            sc->pending = it;
-        }
-        return;
-    }
-    const double2 ts = mk<double>(h[1], h[2]);
-    const double tt = h[3];
-    int st = -1, why = BD_NONE;
-    double2 om = mk<double>(0.0, 0.0);
-    if (!zfinite(ts) || !__builtin_isfinite(tt)) st = ST_NONFINITE;
-    else if (tt == 0.0) st = ST_BREAKDOWN, why = BD_TT;
-    else {
-        om = zdiv(ts, mk<double>(tt, 0.0));
-        if (!zfinite(om)) st = ST_NONFINITE;
-    }
-    if (st >= 0) {
-        if (sys_leader(q)) finish(sc, a.ndone, st, it, why);
-        return;
-    }
-    if (sys_leader(q)) {
-        sc->omega = om;
-        sc->iter = it + 1;
-    }
-    const cx<T> omt = narrow<T>(om), nom = mk<T>(-omt.x, -omt.y);
-    double e[3] = {0.0, 0.0, 0.0};
-    HZ_FOR_ELEMS(i, q.rw) {
-        const cx<T> sv = a.s[i], tv = a.t[i], rh = a.rh[i];
-        cx<T> x = a.x[i];
-        x = cfma<T>(al, p[i], x);
-        x = cfma<T>(omt, sv, x);
-        a.x[i] = x;
-        const cx<T> r = cfma<T>(nom, tv, sv);
-        a.r[i] = r;
-        double2 c = cdotacc(rh.x, rh.y, r.x, r.y, mk<double>(e[0], e[1]));
-        e[0] = c.x;
-        e[1] = c.y;
-        e[2] = __builtin_fma((double)r.x, (double)r.x, e[2]);
-        e[2] = __builtin_fma((double)r.y, (double)r.y, e[2]);
-    }
-    store_sys_partials<3>(a.part + kPartC * a.stride, a.stride, q.lb, e);
-}
-
-// ------------------------------------------------------------------ gather-light variant (five kernels)
-//
-// For matrices whose column indices are far from the row (a random node
-// numbering), forming p and s for every gathered column multiplies the
-// number of scattered reads.  This variant materialises them first, so
-// each product gathers one vector:
-//   P-kernel: iteration_start, p = r + beta (p_old - omega v_old)   (element-wise)
-//   A1-kernel: v = A p; partial <rhat, v>
-//   S-kernel: alpha = rho / <rhat, v>; s = r - alpha v; partial ||s||^2
-//   B1-kernel: t = A s; partials <t, s>, ||t||^2
-//   C-kernel: as in the fused variant.
-
-template <typename T>
-__global__ HZ_STREAM_BOUNDS void k_bicg_P(const BicgArgs<T> a) {
-    const SysBlock q = sys_block(a);
-    IterStart st;
-    if (!iteration_start(a, q, st)) return;
-    const int it = st.it;
-    const bool first = it == 1;
-    const cx<T> bt = narrow<T>(st.beta), omt = narrow<T>(st.omega);
-    const cx<T>* __restrict__ pold = a.p[(it - 1) & 1];
-    const cx<T>* __restrict__ vold = a.v[(it - 1) & 1];
-    cx<T>* __restrict__ pnew = a.p[it & 1];
-    HZ_FOR_ELEMS(i, q.rw)
-        pnew[i] = first ? a.r[i] : p_update<T>(false, bt, omt, a.r[i], pold[i], vold[i]);
-}
-
-template <typename T, int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_bicg_A1(const BicgArgs<T> a) {
-    const SysBlock q = sys_block(a);
-    if (q.sys < 0) return;
+    FirstRow<T, 0> f;
+    first_row<T, L, 0>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
     const SolverScal* sc = a.sc + q.sys;
     if (sc->done || sc->pending) return;
-    const int it = sc->cur;
-    const cx<T>* __restrict__ p = a.p[it & 1];
-    cx<T>* __restrict__ v = a.v[it & 1];
-    auto pcol = [p](int c) { return p[c]; };
+    const cx<T>* __restrict__ p = a.p;
+    cx<T>* __restrict__ v = a.v;
     const cx<T>* __restrict__ rh = a.rh;
     double e[2] = {0.0, 0.0};
-    for_rows<T, L, U>(
-        q.rw, a.row_ptr, a.col_idx, a.vals, pcol,
+    for_rows<T, L, U, 0>(
+        f, q.rw, a.row_ptr, a.col_idx, a.vals, [p](int c) { return p[c]; },
         [&](int64_t row, cx<T> acc, cx<T> w) {
             v[row] = acc;
-            double2 c = cdotacc(w.x, w.y, acc.x, acc.y, mk<double>(e[0], e[1]));
+            const double2 c = cdotacc(w.x, w.y, acc.x, acc.y, mk<double>(e[0], e[1]));
             e[0] = c.x;
             e[1] = c.y;
         },
         [rh](int64_t row) { return rh[row]; });
-    store_sys_partials<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
+// s = r - alpha v
 template <typename T>
 __global__ HZ_STREAM_BOUNDS void k_bicg_S(const BicgArgs<T> a) {
     const SysBlock q = sys_block(a);
-    int it;
-    double2 alpha;
-    if (!alpha_step(a, q, it, alpha)) return;
-    const cx<T> nal = mk<T>((T)-alpha.x, (T)-alpha.y);
-    const cx<T>* __restrict__ v = a.v[it & 1];
-    double e[1] = {0.0};
-    HZ_FOR_ELEMS(i, q.rw) {
-        const cx<T> s = cfma<T>(nal, v[i], a.r[i]);
-        a.s[i] = s;
-        e[0] = __builtin_fma((double)s.x, (double)s.x, e[0]);
-        e[0] = __builtin_fma((double)s.y, (double)s.y, e[0]);
+    if (q.sys < 0) return;
+    AlphaHead hd;
+    hd.load(a, q);
+    const cx<T>* __restrict__ v = a.v;
+    const cx<T>* __restrict__ r = a.r;
+    int64_t i = q.rw.x0 + (int64_t)q.rw.k * kBlock + threadIdx.x;
+    const int64_t step = (int64_t)q.rw.K * kBlock;
+    cx<T> v0 = mk<T>(T(0), T(0)), r0 = v0;
+    if (i < q.rw.x1) {
+        v0 = v[i];
+        r0 = r[i];
     }
-    store_sys_partials<1>(a.part + kPartB * a.stride, a.stride, q.lb, e, a.pf);
+    double2 alpha;
+    if (!hd.run(a, q, alpha)) return;
+    const cx<T> nal = mk<T>((T)-alpha.x, (T)-alpha.y);
+    while (i < q.rw.x1) {
+        const int64_t at = i;
+        const cx<T> s = cfma<T>(nal, v0, r0);
+        i += step;
+        if (i < q.rw.x1) {
+            v0 = v[i];
+            r0 = r[i];
+        }
+        a.s[at] = s;
+    }
 }
 
+// The dot products of a row of t = A s: ||s||^2, <t, s>, ||t||^2, <rhat, t>, <rhat, s>.
+template <typename T> __device__ __forceinline__ void b_terms(double (&e)[8], cx<T> s, cx<T> t, cx<T> w) {
+    e[0] = __builtin_fma((double)s.x, (double)s.x, e[0]);
+    e[0] = __builtin_fma((double)s.y, (double)s.y, e[0]);
+    double2 c = cdotacc(t.x, t.y, s.x, s.y, mk<double>(e[1], e[2]));
+    e[1] = c.x;
+    e[2] = c.y;
+    e[3] = __builtin_fma((double)t.x, (double)t.x, e[3]);
+    e[3] = __builtin_fma((double)t.y, (double)t.y, e[3]);
+    c = cdotacc(w.x, w.y, t.x, t.y, mk<double>(e[4], e[5]));
+    e[4] = c.x;
+    e[5] = c.y;
+    c = cdotacc(w.x, w.y, s.x, s.y, mk<double>(e[6], e[7]));
+    e[6] = c.x;
+    e[7] = c.y;
+}
+
+// The epilogue operands of a row of t = A s: s and rhat.
+template <typename T> struct BRow {
+    cx<T> s, w;
+};
+
+// t = A s and its dot products
 template <typename T, int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_bicg_B1(const BicgArgs<T> a) {
+__global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
     const SysBlock q = sys_block(a);
     if (q.sys < 0) return;
+    FirstRow<T, 0> f;
+    first_row<T, L, 0>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
     if (a.sc[q.sys].done) return;
     const cx<T>* __restrict__ sv = a.s;
-    auto scol = [sv](int c) { return sv[c]; };
-    double e[3] = {0.0, 0.0, 0.0};
-    for_rows<T, L, U>(
-        q.rw, a.row_ptr, a.col_idx, a.vals, scol,
-        [&](int64_t row, cx<T> acc, cx<T> s) {
-            a.t[row] = acc;
-            double2 c = cdotacc(acc.x, acc.y, s.x, s.y, mk<double>(e[0], e[1]));
-            e[0] = c.x;
-            e[1] = c.y;
-            e[2] = __builtin_fma((double)acc.x, (double)acc.x, e[2]);
-            e[2] = __builtin_fma((double)acc.y, (double)acc.y, e[2]);
+    const cx<T>* __restrict__ rh = a.rh;
+    cx<T>* __restrict__ tv = a.t;
+    double e[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for_rows<T, L, U, 0>(
+        f, q.rw, a.row_ptr, a.col_idx, a.vals, [sv](int c) { return sv[c]; },
+        [&](int64_t row, cx<T> acc, BRow<T> m) {
+            tv[row] = acc;
+            b_terms<T>(e, m.s, acc, m.w);
         },
-        [sv](int64_t row) { return sv[row]; });
-    store_sys_partials<3>(a.part + (kPartB + 1) * a.stride, a.stride, q.lb, e);
+        [sv, rh](int64_t row) { return BRow<T>{sv[row], rh[row]}; });
+    store_sys_partials<8, epi_stride(L)>(a.part + kPartB * a.stride, a.stride, q.lb, e);
+}
+
+// The same with the S-kernel's head: s = r - alpha v is formed for every
+// gathered column and stored.  One block per CU: the head, the prefetched
+// entries and eight sums need more than the 64 registers of two.
+template <typename T, int L, int U>
+__global__ __launch_bounds__(kBlock) void k_bicg_SB(const BicgArgs<T> a) {
+    const SysBlock q = sys_block(a);
+    if (q.sys < 0) return;
+    AlphaHead hd;
+    hd.load(a, q);
+    FirstRow<T, U> f;
+    first_row<T, L, U>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
+    double2 alpha;
+    if (!hd.run(a, q, alpha)) return;
+    const cx<T> nal = mk<T>((T)-alpha.x, (T)-alpha.y);
+    const cx<T>* __restrict__ r = a.r;
+    const cx<T>* __restrict__ v = a.v;
+    const cx<T>* __restrict__ rh = a.rh;
+    cx<T>* __restrict__ sv = a.s;
+    cx<T>* __restrict__ tv = a.t;
+    auto scol = [=](int c) { return cfma<T>(nal, v[c], r[c]); };
+    double e[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for_rows<T, L, U, U>(
+        f, q.rw, a.row_ptr, a.col_idx, a.vals, scol,
+        [&](int64_t row, cx<T> acc, BRow<T> m) {
+            sv[row] = m.s;
+            tv[row] = acc;
+            b_terms<T>(e, m.s, acc, m.w);
+        },
+        [=](int64_t row) { return BRow<T>{scol((int)row), rh[row]}; });
+    store_sys_partials<8, epi_stride(L)>(a.part + kPartB * a.stride, a.stride, q.lb, e);
+}
+
+// p_{i+1} = r_{i+1} + beta (p_i - omega v_i)
+template <typename T>
+__device__ __forceinline__ cx<T> p_update(cx<T> bt, cx<T> omt, cx<T> rc, cx<T> pc, cx<T> vc) {
+    const cx<T> d = mk<T>(pc.x - fmaT(omt.x, vc.x, -omt.y * vc.y), pc.y - fmaT(omt.x, vc.y, omt.y * vc.x));
+    return cfma<T>(bt, d, rc);
+}
+
+template <typename T>
+__global__ HZ_STREAM_BOUNDS void k_bicg_C(const BicgArgs<T> a) {
+    enum : int { STOP = 0, HALF = 1, FULL = 2 };
+    __shared__ double tot[kBlock / kWave];
+    __shared__ double2 coef[3];  // alpha, omega, beta
+    __shared__ int mode;
+    const SysBlock q = sys_block(a);
+    if (q.sys < 0) return;
+    SolverScal* sc = a.sc + q.sys;
+    const int done = sc->done, it = sc->cur;
+    const double bnorm = sc->bnorm, rtol = sc->rtol;
+    const double2 alpha = sc->alpha, rho_0 = sc->rho2[0], rho_1 = sc->rho2[1];
+    const double2 rho = (it & 1) ? rho_1 : rho_0;
+    PartSum<8> ps;
+    ps.load(a.part + (kPartB + ps.comp()) * a.stride + a.pf * q.gbeg, a.pf * q.gcnt);
+    cx<T> s0 = mk<T>(T(0), T(0)), t0 = s0;
+    auto load = [&](int64_t j) {
+        s0 = a.s[j];
+        t0 = a.t[j];
+    };
+    int64_t i = q.rw.x0 + (int64_t)q.rw.k * kBlock + threadIdx.x;
+    const int64_t step = (int64_t)q.rw.K * kBlock;
+    if (i < q.rw.x1) load(i);
+    ps.store(tot);
+    __syncthreads();
+    if (wave_id() == 0) {  // the decision and the scalars, once per block
+        double h[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) h[k] = ps.at(tot, k);
+        auto decide = [&]() -> int {
+            if (done) return STOP;
+            const bool lead = sys_leader(q);
+            const double rel = __builtin_sqrt(h[0]) / bnorm;
+            if (!__builtin_isfinite(rel)) {
+                if (lead) finish(sc, a.ndone, ST_NONFINITE, it);
+                return STOP;
+            }
+            if (rel <= rtol) {  // concluded by the next head
+                if (lead) {
+                    sc->relres = rel;
+                    sc->pending = it;
+                }
+                return HALF;
+            }
+            const double2 ts = mk<double>(h[1], h[2]);
+            const double tt = h[3];
+            int st = -1, why = BD_NONE;
+            double2 om = mk<double>(0.0, 0.0);
+            if (!zfinite(ts) || !__builtin_isfinite(tt)) st = ST_NONFINITE;
+            else if (tt == 0.0) st = ST_BREAKDOWN, why = BD_TT;
+            else {
+                om = zdiv(ts, mk<double>(tt, 0.0));
+                if (!zfinite(om)) st = ST_NONFINITE;
+            }
+            if (st >= 0) {
+                if (lead) finish(sc, a.ndone, st, it, why);
+                return STOP;
+            }
+            // rho and beta of the next iteration; omega = 0, rho = 0 or a non-finite
+            // beta end the solve in the next head, after its test on ||r||
+            const double2 ort = zmul(om, mk<double>(h[4], h[5]));
+            const double2 rho_n = mk<double>(h[6] - ort.x, h[7] - ort.y);
+            const double2 beta = zmul(zdiv(rho_n, rho), zdiv(alpha, om));
+            if (lead) {
+                sc->omega = om;
+                sc->rho2[(it + 1) & 1] = rho_n;
+                sc->beta = beta;
+                sc->iter = it + 1;
+            }
+            if (threadIdx.x == 0) {
+                coef[1] = om;
+                coef[2] = beta;
+            }
+            return FULL;
+        };
+        const int md = decide();
+        if (threadIdx.x == 0) {
+            coef[0] = alpha;
+            mode = md;
+        }
+    }
+    __syncthreads();
+    if (mode == STOP) return;
+    const cx<T> al = narrow<T>(coef[0]);
+    if (mode == HALF) {  // half-step exit: x += alpha p
+        HZ_FOR_ELEMS(j, q.rw) a.x[j] = cfma<T>(al, a.p[j], a.x[j]);
+        return;
+    }
+    const cx<T> omt = narrow<T>(coef[1]), nom = mk<T>(-omt.x, -omt.y), bt = narrow<T>(coef[2]);
+    double e[1] = {0.0};
+    while (i < q.rw.x1) {
+        const int64_t j = i;
+        const cx<T> p0 = a.p[j], v = a.v[j];
+        cx<T> x = cfma<T>(al, p0, a.x[j]);
+        x = cfma<T>(omt, s0, x);
+        const cx<T> r = cfma<T>(nom, t0, s0);
+        const cx<T> p = p_update<T>(bt, omt, r, p0, v);
+        i += step;
+        if (i < q.rw.x1) load(i);
+        a.x[j] = x;
+        a.r[j] = r;
+        a.p[j] = p;
+        e[0] = __builtin_fma((double)r.x, (double)r.x, e[0]);
+        e[0] = __builtin_fma((double)r.y, (double)r.y, e[0]);
+    }
+    store_sys_partials<1>(a.part + (kPartC + 2) * a.stride, a.stride, q.lb, e);
 }
 
 // Locality of a CSR matrix: count of entries with |col - row| > W (integer atomics).
@@ -1050,6 +1292,7 @@ __global__ __launch_bounds__(kBlock) void k_init(const BicgArgs<T> a, const cx<T
         const cx<T> bv = a.b[i], rv = src[i];
         if (a.r != src) a.r[i] = rv;
         const_cast<cx<T>*>(a.rh)[i] = rv;
+        if (a.p != nullptr) a.p[i] = rv;  // p_1 = r_0 (BiCGStab)
         eb[0] = __builtin_fma((double)bv.x, (double)bv.x, eb[0]);
         eb[0] = __builtin_fma((double)bv.y, (double)bv.y, eb[0]);
         double2 c = cdotacc(rv.x, rv.y, rv.x, rv.y, mk<double>(e[0], e[1]));
@@ -1059,14 +1302,14 @@ __global__ __launch_bounds__(kBlock) void k_init(const BicgArgs<T> a, const cx<T
         e[2] = __builtin_fma((double)rv.y, (double)rv.y, e[2]);
     }
     store_sys_partials<3>(a.part + kPartC * a.stride, a.stride, q.lb, e);
-    store_sys_partials<1>(a.part + kPartI * a.stride, a.stride, q.lb, eb);
+    store_sys_partials<1, 1, 1>(a.part + kPartI * a.stride, a.stride, q.lb, eb);
 }
 
 // ||b||, initial convergence test, per system (one block per system); iteration 1 comes next.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_fin_init(const BicgArgs<T> a) {
     const int j = blockIdx.x;
-    const SysMap sm = a.smap[j];
+    const SysMap sm = sys_range(a, j);
     SolverScal* sc = a.sc + j;
     double hb[1], hr[3];
     sys_sum<1>(a.part + kPartI * a.stride, a.stride, sm.gbeg, sm.gcnt, hb);
@@ -1083,6 +1326,7 @@ __global__ __launch_bounds__(kBlock) void k_fin_init(const BicgArgs<T> a) {
     sc->why = BD_NONE;
     sc->status = ST_NOT_CONVERGED;
     sc->alpha = sc->omega = sc->beta = mk<double>(1.0, 0.0);
+    sc->rho2[1] = mk<double>(hr[0], hr[1]);  // rho of iteration 1
     if (!__builtin_isfinite(bn) || !__builtin_isfinite(hr[2])) return finish(sc, a.ndone, ST_NONFINITE, 0);
     if (bn == 0.0) {
         sc->zero_x = 1;
@@ -1099,7 +1343,7 @@ __global__ __launch_bounds__(kBlock) void k_fin_init(const BicgArgs<T> a) {
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_fin_true(const BicgArgs<T> a) {
     const int j = blockIdx.x;
-    const SysMap sm = a.smap[j];
+    const SysMap sm = sys_range(a, j);
     double h[1];
     sys_sum<1>(a.part + kPartI * a.stride, a.stride, sm.gbeg, sm.gcnt, h);
     SolverScal* sc = a.sc + j;

@@ -9,8 +9,9 @@
 // Vorst, reliable updated residuals in hybrid Bi-CG methods): the FP64
 // iterate takes x += ||b|| D^{-1} y and y restarts from zero, the true
 // residual r64 = b - A x is formed in FP64, and the complex64 recursive
-// residual is replaced by r64 / ||b|| (with its <rhat, r>, ||r||^2 partials)
-// while p, v, rhat and the scalars carry on.  Convergence is decided on the
+// residual is replaced by r64 / ||b|| (with <rhat, r>, ||r||^2 and the
+// direction p that were formed from the old one) while v, rhat and the other
+// scalars carry on.  Convergence is decided on the
 // FP64 true residual only.
 #pragma once
 
@@ -43,8 +44,10 @@ __global__ __launch_bounds__(kBlock) void k_ru_promote(int n, float2* __restrict
     y[i] = mk<float>(0.0f, 0.0f);
 }
 
-// Replace the complex64 recursive residual by r64 / ||b|| and recompute the
-// partials the next iteration starts from: <rhat, r>, ||r||^2 (region C).
+// Replace the complex64 recursive residual by r64 / ||b||, in three launches
+// between iterations (the next iteration's p, rho and beta were formed from
+// the old residual).  First the new residual into s (free here) with its
+// partials <rhat, r>, ||r||^2 (region C) ...
 __global__ HZ_STREAM_BOUNDS void k_ru_replace(const BicgArgs<float> a, const double2* __restrict__ r64,
                                               const SolverScal* outer) {
     const SysBlock q = sys_block(a);
@@ -54,7 +57,7 @@ __global__ HZ_STREAM_BOUNDS void k_ru_replace(const BicgArgs<float> a, const dou
     HZ_FOR_ELEMS(i, q.rw) {
         const double2 v = r64[i];
         const float2 r = mk<float>((float)(v.x * inv), (float)(v.y * inv));
-        a.r[i] = r;
+        a.s[i] = r;
         const float2 w = a.rh[i];
         const double2 c = cdotacc(w.x, w.y, r.x, r.y, mk<double>(e[0], e[1]));
         e[0] = c.x;
@@ -63,6 +66,40 @@ __global__ HZ_STREAM_BOUNDS void k_ru_replace(const BicgArgs<float> a, const dou
         e[2] = __builtin_fma((double)r.y, (double)r.y, e[2]);
     }
     store_sys_partials<3>(a.part + kPartC * a.stride, a.stride, q.lb, e);
+}
+
+// ... then p = r_new + (rho_new / rho_old) (p - r_old), which is r_new + beta
+// (p_prev - omega v) with the beta of the new rho = <rhat, r_new>; the old
+// direction is dropped where rho_old is zero ...
+__device__ __forceinline__ double2 ru_factor(const double2 rho_new, const double2 rho_old) {
+    if (zzero(rho_old) || !zfinite(rho_old)) return mk<double>(0.0, 0.0);
+    return zdiv(rho_new, rho_old);
+}
+__global__ HZ_STREAM_BOUNDS void k_ru_direction(const BicgArgs<float> a) {
+    const SysBlock q = sys_block(a);
+    if (q.sys < 0) return;
+    const SolverScal* sc = a.sc + q.sys;
+    const double2 rho_old = sc->rho2[sc->iter & 1];
+    double h[2];
+    sys_sum<2>(a.part + kPartC * a.stride, a.stride, q.gbeg, q.gcnt, h);
+    const float2 f = narrow<float>(ru_factor(mk<double>(h[0], h[1]), rho_old));
+    HZ_FOR_ELEMS(i, q.rw) {
+        const float2 rn = a.s[i], ro = a.r[i], p = a.p[i];
+        a.p[i] = cfma<float>(f, mk<float>(p.x - ro.x, p.y - ro.y), rn);
+        a.r[i] = rn;
+    }
+}
+
+// ... and last rho and beta of the next iteration (one block).
+__global__ HZ_STREAM_BOUNDS void k_ru_rho(const BicgArgs<float> a) {
+    double h[2];
+    const SysMap sm = sys_range(a, 0);
+    sys_sum<2>(a.part + kPartC * a.stride, a.stride, sm.gbeg, sm.gcnt, h);
+    if (threadIdx.x != 0) return;
+    SolverScal* sc = a.sc;
+    const double2 rho = mk<double>(h[0], h[1]);
+    sc->beta = zmul(ru_factor(rho, sc->rho2[sc->iter & 1]), sc->beta);
+    sc->rho2[sc->iter & 1] = rho;
 }
 
 }  // namespace hz

@@ -41,8 +41,7 @@ struct TScal {
 
 struct QArgs {
     int G, stride;
-    const BlockMap* bmap;
-    const SysMap* smap;
+    OneMap one;
     int* ndone;
     const int* __restrict__ row_ptr;
     const int* __restrict__ col_idx;
@@ -62,23 +61,7 @@ struct QArgs {
 };
 
 __device__ __forceinline__ SysBlock qblock(const QArgs& a) {
-    SysBlock q;
-    q.lb = logical_block(blockIdx.x, a.G);
-    const BlockMap m = a.bmap[q.lb];
-    q.sys = m.sys;
-    q.local = m.local;
-    q.rw.x0 = m.x0;
-    q.rw.x1 = m.x1;
-    q.rw.k = m.k;
-    q.rw.K = m.K;
-    if (m.sys >= 0) {
-        const SysMap sm = a.smap[m.sys];
-        q.gbeg = sm.gbeg;
-        q.gcnt = sm.gcnt;
-    } else {
-        q.gbeg = q.gcnt = 0;
-    }
-    return q;
+    return map_block(a.one, nullptr, nullptr, a.G, 1, blockIdx.x);
 }
 
 // theta, c, tau, eta of a half step from ||w||^2, the previous tau and alpha
@@ -104,8 +87,7 @@ __device__ __forceinline__ double2 q_dcoef(double theta, double2 eta, double2 al
 // TFQMR set-up: rho_0 = <r~, r_0>, tau_0 = ||r_0|| from the set-up partials
 __global__ __launch_bounds__(kBlock) void k_q_fin_init(const QArgs a) {
     double h[3];
-    const SysMap sm = a.smap[0];
-    sys_sum<3>(a.part + kPartC * a.stride, a.stride, sm.gbeg, sm.gcnt, h);
+    sys_sum<3>(a.part + kPartC * a.stride, a.stride, 0, a.G, h);
     if (threadIdx.x != 0) return;
     a.sc->rho2[0] = mk<double>(h[0], h[1]);
     a.tq->tau[0] = __builtin_sqrt(h[2]);
@@ -154,7 +136,7 @@ __global__ HZ_STREAM_BOUNDS void k_q_init(const QArgs a, const double2* __restri
                                e[0] = c.x;
                                e[1] = c.y;
                            });
-    store_sys_partials<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 // K1: the even half step's vector work
@@ -253,7 +235,7 @@ __global__ HZ_STREAM_BOUNDS void k_q_odd(const QArgs a) {
                                e[1] = c.x;
                                e[2] = c.y;
                            });
-    store_sys_partials<3>(a.part + kPartC * a.stride, a.stride, q.lb, e);
+    store_sys_partials<3, epi_stride(L)>(a.part + kPartC * a.stride, a.stride, q.lb, e);
 }
 
 // K3: the end of the odd half step and the next even step's directions
@@ -306,7 +288,7 @@ __global__ HZ_STREAM_BOUNDS void k_q_next(const QArgs a) {
     const double2* __restrict__ u1 = a.u1;
     auto ucol = [w, u1, beta](int c) { return cfma<double>(beta, u1[c], w[c]); };
     double e[2] = {0.0, 0.0};
-    for_rows<double, L, U, false>(q.rw, a.row_ptr, a.col_idx, a.vals, ucol, [&](int64_t row, double2 acc) {
+    for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, ucol, [&](int64_t row, double2 acc) {
         a.x[row] = cfma<double>(s2.eta, a.d[row], a.x[row]);
         a.u[row] = ucol((int)row);
         a.au[row] = acc;
@@ -318,7 +300,7 @@ __global__ HZ_STREAM_BOUNDS void k_q_next(const QArgs a) {
         e[0] = c.x;
         e[1] = c.y;
     });
-    store_sys_partials<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 // Gather-light form of K3 for large systems (two launches instead of one,
@@ -396,7 +378,7 @@ __global__ HZ_STREAM_BOUNDS void k_q_next_light(const QArgs a) {
                                e[0] = c.x;
                                e[1] = c.y;
                            });
-    store_sys_partials<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 }  // namespace hz
