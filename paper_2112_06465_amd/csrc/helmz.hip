@@ -22,6 +22,7 @@
 #include "hz_reliable.hpp"
 #include "hz_spmv.hpp"
 #include "hz_soltile.hpp"
+#include "hz_slices.hpp"
 #include "hz_bicgstabl.hpp"
 #include "hz_tfqmr.hpp"
 #include "hz_formats.hpp"
@@ -84,7 +85,7 @@ struct hz_handle {
     int* dflag;            // device word for CSR validation
     unsigned long long* dcount;  // device counter for the locality test
     unsigned long long* hcount;  // pinned host copy
-    int* hflag;            // pinned host word
+    int* hflag;            // two pinned host words
     SolverScal* hsc;       // pinned host copy of the solver scalars
     SolverScal* hsc2;      // pinned host copy of the refinement's outer scalars
 };
@@ -384,12 +385,15 @@ int enqueue_far_count(hz_handle* h, hipStream_t s, int n, const int* rp, const i
 // Which iteration: the gather-light one (s and, in TFQMR, u'' materialised, one
 // gathered vector per product) or the fused one (formed per gathered column,
 // two gathered vectors, one launch fewer).  Each launch costs about 3 us of
-// start-up, head and tail; the second gathered vector costs more from about
-// 57,000 rows on.  BiCGStab, us per iteration, fused / split: 8,000 rows 14.6 /
-// 16.0, 31,429 rows 17.0 / 18.1, 46,656 rows 17.5 / 18.5, 57,005 rows 21.9 / 21.8,
-// 92,477 rows 26.3 / 24.7, 209,777 rows 42.7 / 39.8.
+// start-up, head and tail; the second gathered vector costs more from some
+// size on, which is larger for the sliced operator, whose gathers touch a
+// third of the cache lines.  BiCGStab, us per iteration, fused / split: CSR,
+// 8,000 rows 14.6 / 16.0, 46,656 rows 17.5 / 18.5, 57,005 rows 21.9 / 21.8,
+// 92,477 rows 26.3 / 24.7; sliced, 57,005 rows 17.2 / 19.0, 92,477 rows 21.0 /
+// 22.3, 125,885 rows 25.8 / 27.6, 209,777 rows 41.1 / 38.1.
 // `rows` is the total over the systems of a launch.  HZ_FUSED=0/1 overrides.
 constexpr int64_t kFusedMaxRows = 57344;
+constexpr int64_t kFusedMaxRowsSliced = 163840;
 constexpr int64_t kFusedMaxRowsQ = 131072;  // TFQMR's third launch
 bool choose_fused(const hz_handle*, int64_t rows, int64_t most = kFusedMaxRows) {
     if (const char* env = std::getenv("HZ_FUSED")) return std::atoi(env) != 0;
@@ -423,14 +427,16 @@ struct WorkMap {
     std::vector<SysMap> systems;
 };
 
-// The one-system map: groups own equal shares of the rows, rounded up to 16
-// (the last ones may be shorter, or empty on a tiny system).
-hz::OneMap one_map(int n, int G) {
+// The one-system map: groups own equal shares of the rows, rounded up to
+// `unit` rows (the last ones may be shorter, or empty on a tiny system): 16,
+// or the 64 rows of a slice where the operator may be sliced.
+hz::OneMap one_map(int n, int G, int unit) {
     hz::OneMap o;
     o.n = n;
     o.groups = (G % hz::kXcd == 0) ? hz::kXcd : 1;
     o.K = G / o.groups;
-    o.gr = o.groups == 1 ? n : int((int64_t(n) + hz::kXcd - 1) / hz::kXcd + 15) / 16 * 16;
+    const int64_t share = (int64_t(n) + hz::kXcd - 1) / hz::kXcd;
+    o.gr = o.groups == 1 ? n : int((share + unit - 1) / unit * unit);
     return o;
 }
 
@@ -440,7 +446,7 @@ WorkMap build_map(int nsys, const int* row_off, int L) {
     const int64_t N = int64_t(row_off[nsys]) - row_off[0];
     if (nsys == 1) {
         m.G = geom_for(int(N), kBlock / L).G;
-        m.one = one_map(int(N), m.G);
+        m.one = one_map(int(N), m.G, 16);
         m.stride = std::max(m.G, kMaxGrid);
         return m;
     }
@@ -474,16 +480,26 @@ struct SolveWs {
     void* vec[6];
     void* dinv;
     void* ahat;
+    int* soff;  // the sliced operator's offsets and columns (its values are in ahat), or null
+    short* scol;
 };
 
 // Partial component stride of the BiCGStab workspace for a map of G blocks:
 // room for the products' sub-blocks, sol_subs(G) G <= max(2 G, kSolSlots) slots.
 int bicg_stride(int G) { return std::max(2 * G, std::max(2 * kMaxGrid, hz::kSolSlots)); }
 
+// The sliced operator (hz_slices.hpp) of n rows with room for nnz slots: its
+// offsets and its columns.
+size_t slice_off_bytes(int n) { return align_up(sizeof(int) * (size_t(n > 0 ? n : 1) / hz::kWave + 2)); }
+size_t slice_col_bytes(int64_t nnz) { return align_up(sizeof(short) * size_t(nnz > 0 ? nnz : 1)); }
+
 // The size is never less than that of eight vectors and ten partial regions,
 // which callers' limits (the static scratch's among them) have been set by.
+// A one-system Jacobi solve may slice its operator where the offsets and
+// columns fit into what that leaves (up to about 15.9 entries a row from
+// 12,000 rows on), or with `grow`.
 template <typename T>
-size_t ws_layout(int n, int64_t nnz, bool jacobi, int nsys, int G, char* base, SolveWs* out) {
+size_t ws_layout(int n, int64_t nnz, bool jacobi, int nsys, int G, char* base, SolveWs* out, bool grow = false) {
     const size_t vb = align_up(sizeof(cx<T>) * size_t(n > 0 ? n : 1));
     const int stride = bicg_stride(G);
     size_t off = 0;
@@ -501,10 +517,15 @@ size_t ws_layout(int n, int64_t nnz, bool jacobi, int nsys, int G, char* base, S
     for (auto& v : w.vec) v = take(vb);
     w.dinv = jacobi ? take(vb) : nullptr;
     w.ahat = jacobi ? take(sizeof(cx<T>) * size_t(nnz > 0 ? nnz : 1)) : nullptr;
-    if (out) *out = w;
     const size_t extra_parts = align_up(sizeof(double) * size_t(hz::kParts) * size_t(stride)) -
                                align_up(sizeof(double) * size_t(10) * size_t(stride));
-    return std::max(off, off + 2 * vb - extra_parts);
+    const size_t total = std::max(off, off + 2 * vb - extra_parts);
+    if (jacobi && nsys == 1 && nnz > 0 && (grow || off + slice_off_bytes(n) + slice_col_bytes(nnz) <= total)) {
+        w.soff = static_cast<int*>(take(slice_off_bytes(n)));
+        w.scol = static_cast<short*>(take(slice_col_bytes(nnz)));
+    }
+    if (out) *out = w;
+    return std::max(off, total);
 }
 
 // Worst case of the one-system map: G <= kMaxGrid.
@@ -525,6 +546,8 @@ hz::BicgArgs<T> bicg_args(const WorkMap& m, const int* rp, const int* ci, const 
     a.row_ptr = rp;
     a.col_idx = ci;
     a.vals = av;
+    a.soff = nullptr;
+    a.scol = nullptr;
     a.b = b;
     a.r = static_cast<cx<T>*>(w.vec[0]);
     a.rh = static_cast<const cx<T>*>(w.vec[1]);
@@ -542,7 +565,7 @@ hz::BicgArgs<T> bicg_args(const WorkMap& m, const int* rp, const int* ci, const 
 // and zero the done-counter.
 int upload_map(hipStream_t s, const WorkMap& m, const SolveWs& w) {
     if (m.nsys == 1) {
-        HZ_HIP(hipMemsetAsync(w.ndone, 0, sizeof(int), s));
+        HZ_HIP(hipMemsetAsync(w.ndone, 0, 2 * sizeof(int), s));
         return HZ_OK;
     }
     HZ_HIP(hipMemcpyAsync(w.bmap, m.blocks.data(), sizeof(BlockMap) * m.blocks.size(), hipMemcpyHostToDevice, s));
@@ -551,31 +574,107 @@ int upload_map(hipStream_t s, const WorkMap& m, const SolveWs& w) {
     return HZ_OK;
 }
 
-// The gather-light products of a one-system solve on the block-tile row loop
-// (L = 1) run as sub-blocks with an LDS result ring (k_bicg_At, k_bicg_Bt);
-// the returned arguments carry their partial layout.
+// D^{-1} and A D^{-1} of a one-system Jacobi solve: sliced if there is room
+// (soff != null) and the matrix allows it (*no stays 0), else in the caller's
+// pattern.
+template <typename TO>
+void enqueue_jacobi(hipStream_t s, int n, int nnz, const int* rp, const int* ci, const double2* A, double2* dinv,
+                    SolverScal* sc, cx<TO>* out, int* soff, short* scol, int* no) {
+    const bool room = soff != nullptr;
+    hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, dinv, sc,
+                       room ? no : nullptr);
+    const double2* d = dinv;
+    if (room) {
+        const int ns = (n + hz::kWave - 1) / hz::kWave;
+        const dim3 G((n + hz::kSlBlock - 1) / hz::kSlBlock), B(hz::kSlBlock);
+        hipLaunchKernelGGL(hz::k_slice_width, G, B, 0, s, n, rp, soff);
+        hipLaunchKernelGGL(hz::k_slice_scan, dim3(1), dim3(kBlock), 0, s, ns, soff, int64_t(nnz), no);
+        hipLaunchKernelGGL((hz::k_slice_fill<TO>), G, B, 0, s, n, rp, ci, A, d, static_cast<const int*>(soff), out,
+                           scol, static_cast<const int*>(no));
+    }
+    if (nnz > 0)
+        hipLaunchKernelGGL((hz::k_colscale<TO>), grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A, d, out,
+                           room ? static_cast<const int*>(no) : nullptr);
+}
+
+// Blocks of a sliced product over the one-system map.
+int slice_grid(const hz::OneMap& o) {
+    const int64_t slices = (int64_t(o.gr) + hz::kWave - 1) / hz::kWave;  // per group
+    const int64_t K = (slices + hz::kSlWaves - 1) / hz::kSlWaves, most = hz::kSlMaxGrid / o.groups;
+    return int(o.groups * std::max<int64_t>(1, std::min(K, most)));
+}
+// Streaming loads for a sliced operator of `nnz` slots that does not stay in the Infinity Cache beside the vectors.
+template <typename T> bool slice_stream(int64_t nnz) { return int64_t(sizeof(cx<T>) + 2) * nnz > (int64_t(128) << 20); }
+
+// Which product kernels a solve launches.
+enum ProdForm : int {
+    PF_CSR = 0,     // on the CSR operator (vector rows or tiles)
+    PF_SLICED = 1,  // on the sliced operator
+    PF_BOTH = 2     // both, each of which runs if the operator is its own (asynchronous solves)
+};
+
+// The gather-light CSR products of a one-system solve on the block-tile row
+// loop (L = 1) run as sub-blocks with an LDS result ring (k_bicg_At,
+// k_bicg_Bt).
 template <typename T> bool sub_products(const WorkMap& m, int L, bool fused) { return L == 1 && m.nsys == 1 && !fused; }
-template <typename T> hz::BicgArgs<T> iteration_args(const WorkMap& m, hz::BicgArgs<T> a, int L, bool fused) {
-    a.pf = sub_products<T>(m, L, fused) ? hz::sol_subs(m.G) : 1;
+
+// How a solve's iterations are launched.
+struct IterPlan {
+    int L = 0;
+    bool fused = false, sub = false;    // the CSR operator
+    bool fused_s = false, nt = false;   // the sliced operator
+    ProdForm form = PF_CSR;
+};
+
+template <typename T>
+IterPlan iter_plan(const hz_handle* h, const WorkMap& m, int L, int n, ProdForm form, int64_t nnz) {
+    const bool fused = choose_fused(h, n);
+    return IterPlan{L, fused, sub_products<T>(m, L, fused), choose_fused(h, n, kFusedMaxRowsSliced),
+                    slice_stream<T>(nnz), form};
+}
+
+// The kernels' arguments under a plan: the products' blocks and partial slots.
+template <typename T> hz::BicgArgs<T> iteration_args(const WorkMap& m, hz::BicgArgs<T> a, const IterPlan& ip) {
+    a.pf = ip.sub ? hz::sol_subs(m.G) : 1;
+    a.both = ip.form == PF_BOTH;
+    a.s_csr = a.both && ip.fused_s;
+    const int csr = a.pf * m.G;
+    a.sg = m.nsys == 1 ? slice_grid(m.one) : 0;
+    a.np = ip.form == PF_CSR ? csr : (ip.form == PF_SLICED ? a.sg : std::max(csr, a.sg));
     return a;
 }
 
 // One iteration on stream q: A, B, C with s formed in B (fused), or A, S, B, C.
+// (Both families: the sliced one may be fused where the CSR one is not, never
+// the reverse, and the S-kernel is then for the CSR one only.)
 template <typename T, int LL, int UU>
-void enqueue_iteration(hipStream_t q, const WorkMap& m, const hz::BicgArgs<T>& a, bool fused, bool sub) {
+void enqueue_iteration(hipStream_t q, const WorkMap& m, const hz::BicgArgs<T>& a, const IterPlan& ip) {
     const dim3 G(m.G), B(kBlock);
-    if (sub)
-        hipLaunchKernelGGL((hz::k_bicg_At<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
-    else
-        hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU>), G, B, 0, q, a);
-    if (fused) {
-        hipLaunchKernelGGL((hz::k_bicg_SB<T, LL, UU>), G, B, 0, q, a);
-    } else {
-        hipLaunchKernelGGL((hz::k_bicg_S<T>), G, B, 0, q, a);
-        if (sub)
+    const bool csr = ip.form != PF_SLICED, sl = ip.form != PF_CSR;
+    const dim3 SG(a.sg), SB(hz::kSlBlock);
+    if (csr) {
+        if (ip.sub)
+            hipLaunchKernelGGL((hz::k_bicg_At<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
+        else
+            hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU>), G, B, 0, q, a);
+    }
+    if (sl) {
+        if (ip.nt) hipLaunchKernelGGL((hz::k_bicg_As<T, true>), SG, SB, 0, q, a);
+        else hipLaunchKernelGGL((hz::k_bicg_As<T, false>), SG, SB, 0, q, a);
+    }
+    if ((csr && !ip.fused) || (sl && !ip.fused_s)) hipLaunchKernelGGL((hz::k_bicg_S<T>), G, B, 0, q, a);
+    if (csr) {
+        if (ip.fused)
+            hipLaunchKernelGGL((hz::k_bicg_SB<T, LL, UU>), G, B, 0, q, a);
+        else if (ip.sub)
             hipLaunchKernelGGL((hz::k_bicg_Bt<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
         else
             hipLaunchKernelGGL((hz::k_bicg_B<T, LL, UU>), G, B, 0, q, a);
+    }
+    if (sl) {
+        if (ip.fused_s) hipLaunchKernelGGL((hz::k_bicg_SBs<T>), SG, SB, 0, q, a);
+        else if (ip.nt) hipLaunchKernelGGL((hz::k_bicg_Bs<T, true>), SG, SB, 0, q, a);
+        else hipLaunchKernelGGL((hz::k_bicg_Bs<T, false>), SG, SB, 0, q, a);
     }
     hipLaunchKernelGGL((hz::k_bicg_C<T>), G, B, 0, q, a);
 }
@@ -586,15 +685,15 @@ void enqueue_iteration(hipStream_t q, const WorkMap& m, const hz::BicgArgs<T>& a
 // one kernel that concludes the last iteration; polls the
 // done-counter between chunks of 8, 16, ..., 64 iterations.
 template <typename T>
-int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>& a0, int L, int maxiter, bool fused,
+int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>& a0, const IterPlan& ip, int maxiter,
             bool poll_done = true, bool graphs = true) {
-    const hz::BicgArgs<T> a = iteration_args(m, a0, L, fused);
-    const bool sub = sub_products<T>(m, L, fused);
+    const hz::BicgArgs<T> a = iteration_args(m, a0, ip);
+    const int L = ip.L;
     int launched = 0, poll = poll_done ? 8 : 64;
     while (launched < maxiter) {
         const int k_n = (maxiter - launched) < poll ? (maxiter - launched) : poll;
         const bool tail = launched + k_n == maxiter;
-        const int family = (fused ? 1 : 2) + (sizeof(T) == 4 ? 10 : 0);
+        const int family = (ip.fused ? 1 : 2) + (sizeof(T) == 4 ? 10 : 0) + 1000 * ip.form + (ip.fused_s ? 5000 : 0);
         auto chunk = [&](auto&& record) {
             if (graphs) return launch_chunk(h, s, chunk_key(family, L, k_n, tail, a), record);
             record(s);  // direct launches: no graph is captured or instantiated (nothing allocated)
@@ -602,7 +701,7 @@ int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>
         };
         int rc = chunk([&](hipStream_t q) {
             with_lanes(L, [&]<int LL, int UU>() {
-                for (int k = 0; k < k_n; ++k) enqueue_iteration<T, LL, UU>(q, m, a, fused, sub);
+                for (int k = 0; k < k_n; ++k) enqueue_iteration<T, LL, UU>(q, m, a, ip);
             });
             if (tail) hipLaunchKernelGGL((hz::k_bicg_end<T>), dim3(m.nsys), dim3(kBlock), 0, q, a);
         });
@@ -618,9 +717,10 @@ int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>
     return HZ_OK;
 }
 
-// The done-counter zeroed by a kernel (the asynchronous solve may be captured, so it records no memset).
-__global__ void k_zero_word(int* w) {
-    if (threadIdx.x == 0) *w = 0;
+// The done-counter and the word after it zeroed by a kernel (the asynchronous
+// solve may be captured, so it records no memset).
+__global__ void k_zero_words(int* w) {
+    if (threadIdx.x < 2) w[threadIdx.x] = 0;
 }
 
 // x = 0 by a kernel (the allocation-free solve records no memset, so that a
@@ -664,12 +764,13 @@ int solve_fp64(hz_handle* h, hipStream_t s, int nsys, const int* row_off, int nn
     const int n = row_off[nsys] - row_off[0];
     const bool jacobi = (flags & HZ_PRECOND_JACOBI) != 0;
     const int L = nsys == 1 ? solve_lanes(h, rp, ci, n, nnz) : pick_lanes(h, rp, ci, n, nnz);
-    const WorkMap m = build_map(nsys, row_off, L);
+    WorkMap m = build_map(nsys, row_off, L);
     SolveWs w;
     ws_layout<double>(n, nnz, jacobi, nsys, m.G, ws, &w);
+    if (w.soff != nullptr) m.one = one_map(n, m.G, hz::kWave);
     int rc = HZ_OK;
     if (async)
-        hipLaunchKernelGGL(k_zero_word, dim3(1), dim3(64), 0, s, w.ndone);
+        hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, w.ndone);
     else
         rc = upload_map(s, m, w);
     if (rc) return rc;
@@ -680,14 +781,13 @@ int solve_fp64(hz_handle* h, hipStream_t s, int nsys, const int* row_off, int nn
 
     const double2* Aop = A;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, dinv, w.sc);
         double2* ah = static_cast<double2*>(w.ahat);
-        if (nnz > 0)
-            hipLaunchKernelGGL(hz::k_colscale<double>, grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A,
-                               static_cast<const double2*>(dinv), ah);
+        enqueue_jacobi<double>(s, n, nnz, rp, ci, A, dinv, w.sc, ah, w.soff, w.scol, w.ndone + 1);
         Aop = ah;
     }
-    const hz::BicgArgs<double> a = bicg_args<double>(m, rp, ci, Aop, bd, xd, w);
+    hz::BicgArgs<double> a = bicg_args<double>(m, rp, ci, Aop, bd, xd, w);
+    a.soff = w.soff;
+    a.scol = w.scol;
     // initial iterate (y = D x0 under Jacobi) and residual
     const double2* rsrc = bd;
     if (flags & HZ_X0_ZERO) {
@@ -696,15 +796,16 @@ int solve_fp64(hz_handle* h, hipStream_t s, int nsys, const int* row_off, int nn
         else
             HZ_HIP(hipMemsetAsync(xd, 0, 16 * size_t(n), s));
     } else {
+        launch_sys_resid<double>(L, m, a, A, xd, r, s);
         if (jacobi) hipLaunchKernelGGL(hz::k_diag_apply<double>, grid1(n), dim3(kBlock), 0, s, n, dinv, xd, 1);
-        launch_sys_resid<double>(L, m, a, Aop, xd, r, s);
         rsrc = r;
     }
     hipLaunchKernelGGL(hz::k_init<double>, dim3(m.G), dim3(kBlock), 0, s, a, rsrc);
     hipLaunchKernelGGL(hz::k_fin_init<double>, dim3(nsys), dim3(kBlock), 0, s, a);
     HZ_HIP(hipGetLastError());
     if (async) {
-        rc = iterate<double>(h, s, m, a, L, maxiter, choose_fused(h, n), false, !direct);
+        rc = iterate<double>(h, s, m, a, iter_plan<double>(h, m, L, n, w.soff ? PF_BOTH : PF_CSR, nnz),
+                             maxiter, false, !direct);
         if (rc) return rc;
         hipLaunchKernelGGL(hz::k_zero_if<double>, dim3(m.G), dim3(kBlock), 0, s, a);
         if (jacobi) hipLaunchKernelGGL(hz::k_diag_apply<double>, grid1(n), dim3(kBlock), 0, s, n, dinv, xd, 0);
@@ -717,12 +818,13 @@ int solve_fp64(hz_handle* h, hipStream_t s, int nsys, const int* row_off, int nn
     }
     SolverScal* hs = h->hsc;
     HZ_HIP(hipMemcpyAsync(hs, w.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
-    HZ_HIP(hipMemcpyAsync(h->hflag, w.ndone, sizeof(int), hipMemcpyDeviceToHost, s));
+    HZ_HIP(hipMemcpyAsync(h->hflag, w.ndone, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     if (hs->bad_diag) return HZ_ERR_INVALID;
 
     if (*h->hflag < nsys) {
-        rc = iterate<double>(h, s, m, a, L, maxiter, choose_fused(h, n));
+        const ProdForm form = w.soff != nullptr && h->hflag[1] == 0 ? PF_SLICED : PF_CSR;
+        rc = iterate<double>(h, s, m, a, iter_plan<double>(h, m, L, n, form, nnz), maxiter);
         if (rc) return rc;
     }
     hipLaunchKernelGGL(hz::k_zero_if<double>, dim3(m.G), dim3(kBlock), 0, s, a);
@@ -1093,10 +1195,10 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     hipLaunchKernelGGL(hz::k_sc_init, dim3(1), dim3(256), 0, s, w.sc, 1, rtol, maxcycles);
     const double2* Aop = A;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, w.dinv, w.sc);
+        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, w.dinv, w.sc, nullptr);
         if (nnz > 0)
             hipLaunchKernelGGL(hz::k_colscale<double>, grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A,
-                               static_cast<const double2*>(w.dinv), w.ahat);
+                               static_cast<const double2*>(w.dinv), w.ahat, nullptr);
         Aop = w.ahat;
     }
     // the BiCGStab set-up and finishing kernels on the same map, scalars and partials
@@ -1274,10 +1376,10 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     hipLaunchKernelGGL(hz::k_sc_init, dim3(1), dim3(256), 0, s, w.sc, 1, rtol, maxiter);
     const double2* Aop = A;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, w.dinv, w.sc);
+        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, w.dinv, w.sc, nullptr);
         if (nnz > 0)
             hipLaunchKernelGGL(hz::k_colscale<double>, grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A,
-                               static_cast<const double2*>(w.dinv), w.ahat);
+                               static_cast<const double2*>(w.dinv), w.ahat, nullptr);
         Aop = w.ahat;
     }
     hz::BicgArgs<double> ba{};  // the BiCGStab set-up and finishing kernels on the same map and scalars
@@ -1747,8 +1849,8 @@ size_t mixed_layout(int n, int64_t nnz, bool jacobi, char* base, MixedWs* out) {
     MixedWs m{};
     m.outer = static_cast<SolverScal*>(take(sizeof(SolverScal)));
     // the inner workspace always holds the demoted matrix (ahat) and, under Jacobi, D^{-1}
-    char* inner = static_cast<char*>(take(ws_layout<float>(n, nnz, true, 1, kMaxGrid, nullptr, nullptr)));
-    ws_layout<float>(n, nnz, true, 1, kMaxGrid, inner, &m.in);
+    char* inner = static_cast<char*>(take(ws_layout<float>(n, nnz, true, 1, kMaxGrid, nullptr, nullptr, true)));
+    ws_layout<float>(n, nnz, true, 1, kMaxGrid, inner, &m.in, true);
     if (!jacobi) m.in.dinv = nullptr;
     m.r64 = static_cast<double2*>(take(sizeof(double2) * nn));
     m.b32 = static_cast<float2*>(take(sizeof(float2) * nn));
@@ -1817,7 +1919,8 @@ int solve_mixed(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, cons
     const int L = pick_lanes(h, rp, ci, n, nnz);
     const Geom geo = geom_for(n, kBlock / L);
     const int row_off[2] = {0, n};
-    const WorkMap m = build_map(1, row_off, L);
+    WorkMap m = build_map(1, row_off, L);
+    if (jacobi && mw.in.soff != nullptr) m.one = one_map(n, m.G, hz::kWave);
     int rc = upload_map(s, m, mw.in);
     if (rc) return rc;
     const dim3 one(1), B(kBlock);
@@ -1826,16 +1929,14 @@ int solve_mixed(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, cons
     hipLaunchKernelGGL(hz::k_sc_init, one, dim3(64), 0, s, mw.outer, 1, rtol, max_outer);
     hipLaunchKernelGGL(hz::k_sc_init, one, dim3(64), 0, s, mw.in.sc, 1, inner_rtol, maxiter);
     // complex64 copy of the (column-scaled) matrix; r64 holds the FP64 D^{-1} meanwhile
-    const double2* dinv64 = nullptr;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), B, 0, s, n, rp, ci, A, mw.r64, mw.outer);
+        enqueue_jacobi<float>(s, n, nnz, rp, ci, A, mw.r64, mw.outer, static_cast<float2*>(mw.in.ahat), mw.in.soff,
+                              mw.in.scol, mw.in.ndone + 1);
         hipLaunchKernelGGL(hz::k_demote_vec, grid1(n), B, 0, s, n, static_cast<const double2*>(mw.r64),
                            static_cast<float2*>(mw.in.dinv));
-        dinv64 = mw.r64;
+    } else if (nnz > 0) {
+        hipLaunchKernelGGL(hz::k_demote_vals, grid1(nnz), B, 0, s, int64_t(nnz), A, static_cast<float2*>(mw.in.ahat));
     }
-    if (nnz > 0)
-        hipLaunchKernelGGL(hz::k_demote_vals, grid1(nnz), B, 0, s, int64_t(nnz), ci, A, dinv64,
-                           static_cast<float2*>(mw.in.ahat));
     if (flags & HZ_X0_ZERO) HZ_HIP(hipMemsetAsync(xd, 0, 16 * size_t(n), s));
     hipLaunchKernelGGL(hz::k_dot_part<1>, dim3(geo.G), B, 0, s, n, geo, bd, nullptr, partI);
     hipLaunchKernelGGL(hz::k_fin_bnorm, one, B, 0, s, partI, geo.G, mw.outer);
@@ -1843,11 +1944,15 @@ int solve_mixed(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, cons
     SolverScal* ho = h->hsc2;
     SolverScal* hi = h->hsc;
     HZ_HIP(hipMemcpyAsync(ho, mw.outer, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
+    HZ_HIP(hipMemcpyAsync(h->hflag, mw.in.ndone, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     if (ho->bad_diag) return HZ_ERR_INVALID;
-    const bool fused = choose_fused(h, n);
-    const hz::BicgArgs<float> ai =
+    const ProdForm form = jacobi && mw.in.soff != nullptr && h->hflag[1] == 0 ? PF_SLICED : PF_CSR;
+    const IterPlan ip = iter_plan<float>(h, m, L, n, form, nnz);
+    hz::BicgArgs<float> ai =
         bicg_args<float>(m, rp, ci, static_cast<const float2*>(mw.in.ahat), mw.b32, mw.d32, mw.in);
+    ai.soff = mw.in.soff;
+    ai.scol = mw.in.scol;
 
     const float2* dinv32 = jacobi ? static_cast<const float2*>(mw.in.dinv) : nullptr;
     int inner_total = 0, outer = 0;
@@ -1868,7 +1973,7 @@ int solve_mixed(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, cons
         hipLaunchKernelGGL(hz::k_init<float>, dim3(m.G), B, 0, s, ai, static_cast<const float2*>(mw.b32));
         hipLaunchKernelGGL(hz::k_fin_init<float>, one, B, 0, s, ai);
         HZ_HIP(hipGetLastError());
-        rc = iterate<float>(h, s, m, ai, L, maxiter, fused);
+        rc = iterate<float>(h, s, m, ai, ip, maxiter);
         if (rc) return rc;
         HZ_HIP(hipMemcpyAsync(hi, mw.in.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
         HZ_HIP(hipStreamSynchronize(s));
@@ -1895,14 +2000,13 @@ int solve_mixed(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, cons
 
 // Enqueue k iterations of the single-system BiCGStab (no poll).
 template <typename T>
-int launch_iterations(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>& a0, int L, int k,
-                      bool fused) {
-    const hz::BicgArgs<T> a = iteration_args(m, a0, L, fused);
-    const bool sub = sub_products<T>(m, L, fused);
-    const int family = (fused ? 3 : 4) + (sizeof(T) == 4 ? 10 : 0);
-    return launch_chunk(h, s, chunk_key(family, L, k, 0, a), [&](hipStream_t q) {
-        with_lanes(L, [&]<int LL, int UU>() {
-            for (int i = 0; i < k; ++i) enqueue_iteration<T, LL, UU>(q, m, a, fused, sub);
+int launch_iterations(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>& a0, const IterPlan& ip,
+                      int k) {
+    const hz::BicgArgs<T> a = iteration_args(m, a0, ip);
+    const int family = (ip.fused ? 3 : 4) + (sizeof(T) == 4 ? 10 : 0) + 1000 * ip.form + (ip.fused_s ? 5000 : 0);
+    return launch_chunk(h, s, chunk_key(family, ip.L, k, 0, a), [&](hipStream_t q) {
+        with_lanes(ip.L, [&]<int LL, int UU>() {
+            for (int i = 0; i < k; ++i) enqueue_iteration<T, LL, UU>(q, m, a, ip);
         });
     });
 }
@@ -1925,22 +2029,21 @@ int solve_mixed_reliable(hz_handle* h, hipStream_t s, int n, int nnz, const int*
     const int L = pick_lanes(h, rp, ci, n, nnz);
     const Geom geo = geom_for(n, kBlock / L);
     const int row_off[2] = {0, n};
-    const WorkMap m = build_map(1, row_off, L);
+    WorkMap m = build_map(1, row_off, L);
+    if (jacobi && mw.in.soff != nullptr) m.one = one_map(n, m.G, hz::kWave);
     int rc = upload_map(s, m, mw.in);
     if (rc) return rc;
     const dim3 one(1), B(kBlock);
     double* partI = mw.in.part + hz::kPartI * bicg_stride(m.G);  // the inner solve's region I
     hipLaunchKernelGGL(hz::k_sc_init, one, dim3(64), 0, s, mw.outer, 1, rtol, max_updates);
-    const double2* dinv64 = nullptr;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), B, 0, s, n, rp, ci, A, mw.r64, mw.outer);
+        enqueue_jacobi<float>(s, n, nnz, rp, ci, A, mw.r64, mw.outer, static_cast<float2*>(mw.in.ahat), mw.in.soff,
+                              mw.in.scol, mw.in.ndone + 1);
         hipLaunchKernelGGL(hz::k_demote_vec, grid1(n), B, 0, s, n, static_cast<const double2*>(mw.r64),
                            static_cast<float2*>(mw.in.dinv));
-        dinv64 = mw.r64;
+    } else if (nnz > 0) {
+        hipLaunchKernelGGL(hz::k_demote_vals, grid1(nnz), B, 0, s, int64_t(nnz), A, static_cast<float2*>(mw.in.ahat));
     }
-    if (nnz > 0)
-        hipLaunchKernelGGL(hz::k_demote_vals, grid1(nnz), B, 0, s, int64_t(nnz), ci, A, dinv64,
-                           static_cast<float2*>(mw.in.ahat));
     if (flags & HZ_X0_ZERO) HZ_HIP(hipMemsetAsync(xd, 0, 16 * size_t(n), s));
     hipLaunchKernelGGL(hz::k_dot_part<1>, dim3(geo.G), B, 0, s, n, geo, bd, nullptr, partI);
     hipLaunchKernelGGL(hz::k_fin_bnorm, one, B, 0, s, partI, geo.G, mw.outer);
@@ -1951,11 +2054,15 @@ int solve_mixed_reliable(hz_handle* h, hipStream_t s, int n, int nnz, const int*
     SolverScal* ho = h->hsc2;
     SolverScal* hi = h->hsc;
     HZ_HIP(hipMemcpyAsync(ho, mw.outer, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
+    HZ_HIP(hipMemcpyAsync(h->hflag, mw.in.ndone, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     if (ho->bad_diag) return HZ_ERR_INVALID;
-    const bool fused = choose_fused(h, n);
-    const hz::BicgArgs<float> ai =
+    const ProdForm form = jacobi && mw.in.soff != nullptr && h->hflag[1] == 0 ? PF_SLICED : PF_CSR;
+    const IterPlan ip = iter_plan<float>(h, m, L, n, form, nnz);
+    hz::BicgArgs<float> ai =
         bicg_args<float>(m, rp, ci, static_cast<const float2*>(mw.in.ahat), mw.b32, mw.d32, mw.in);
+    ai.soff = mw.in.soff;
+    ai.scol = mw.in.scol;
     const float2* dinv32 = jacobi ? static_cast<const float2*>(mw.in.dinv) : nullptr;
 
     // (re)start the complex64 iteration from the current r64: y = 0, r = rhat = r64 / ||b||
@@ -1981,7 +2088,7 @@ int solve_mixed_reliable(hz_handle* h, hipStream_t s, int n, int nnz, const int*
     double ref = ho->relres;
     while (!ho->done) {
         const int k = std::min(poll, std::max(1, maxiter - launched));
-        rc = launch_iterations<float>(h, s, m, ai, L, k, fused);
+        rc = launch_iterations<float>(h, s, m, ai, ip, k);
         if (rc) return rc;
         launched += k;
         HZ_HIP(hipMemcpyAsync(hi, mw.in.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
@@ -2093,7 +2200,7 @@ int hz_handle_create(hz_handle** out) {
         hipMalloc(reinterpret_cast<void**>(&h->dcount), sizeof(unsigned long long)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&h->hcount), sizeof(unsigned long long), hipHostMallocDefault) !=
             hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&h->hflag), sizeof(int), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&h->hflag), 2 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&h->hsc), sizeof(SolverScal), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&h->hsc2), sizeof(SolverScal), hipHostMallocDefault) != hipSuccess ||
         hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking) != hipSuccess ||

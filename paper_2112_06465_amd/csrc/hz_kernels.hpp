@@ -20,6 +20,8 @@
 #include <type_traits>
 #include <stdint.h>
 
+#define HZ_INLINE __attribute__((always_inline))
+
 namespace hz {
 
 constexpr int kWave = 64;
@@ -102,6 +104,13 @@ template <typename T> __device__ __forceinline__ cx<T> narrow(double2 a) { retur
 typedef double hz_d2v __attribute__((ext_vector_type(2)));
 typedef float hz_f2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int ld_mat(const int* p) {
+#if HZ_STREAM_MATRIX
+    return __builtin_nontemporal_load(p);
+#else
+    return *p;
+#endif
+}
+__device__ __forceinline__ short ld_mat(const short* p) {
 #if HZ_STREAM_MATRIX
     return __builtin_nontemporal_load(p);
 #else
@@ -631,16 +640,23 @@ struct OneMap {
 
 template <typename T> struct BicgArgs {
     int G;       // blocks of every solver launch (a multiple of 8, or < 8)
-    int stride;  // partial component stride (>= pf G)
-    int pf = 1;  // partial slots per block in regions A and B (sol_subs(G) when the products run as sub-blocks)
+    int stride;  // partial component stride (>= np)
+    int pf = 1;  // product blocks per block of the map (sol_subs(G) when the products run as sub-blocks)
     OneMap one;
-    int spare = 0;  // (no padding bytes: the graph cache compares these structs bytewise)
+    int np = 0;    // one system: partial slots that the products write (regions A and B)
+    int sg = 0;    // blocks of the sliced products
+    int both = 0;  // both families of product kernels are launched: run only on the operator's own form
+    int s_csr = 0;  // the S-kernel runs for the CSR operator only (both families, the sliced one fused)
+    int spare = 0;
+    // (no padding bytes: the graph cache compares these structs bytewise)
     const BlockMap* bmap;
     const SysMap* smap;
     int* ndone;  // systems finished so far
     const int* __restrict__ row_ptr;
     const int* __restrict__ col_idx;
     const cx<T>* __restrict__ vals;
+    const int* __restrict__ soff;    // the sliced operator's offsets and columns (vals its values), or null
+    const short* __restrict__ scol;
     const cx<T>* b;
     cx<T>* r;
     const cx<T>* rh;
@@ -696,6 +712,24 @@ __device__ __forceinline__ SysBlock map_block(const OneMap& one, const BlockMap*
 template <typename T> __device__ __forceinline__ SysBlock sys_block(const BicgArgs<T>& a) {
     return map_block(a.one, a.bmap, a.smap, a.G, 1, blockIdx.x);
 }
+// Partials of the block's system in the products' regions A and B.
+template <typename T> __device__ __forceinline__ int prod_parts(const BicgArgs<T>& a, const SysBlock& q) {
+    return a.one.n > 0 ? a.np : q.gcnt;
+}
+// The word after the done-counter: 1 if the operator is not sliced.
+__device__ __forceinline__ int* slice_no(int* ndone) { return ndone + 1; }
+// Whether a CSR product kernel has nothing to do, the operator being sliced.
+template <typename A> __device__ __forceinline__ bool not_csr(const A& a) {
+    return a.both != 0 && *slice_no(a.ndone) == 0;
+}
+// A product of `cnt` blocks where both families are launched: zeros to the
+// slots past its own that the readers also add.
+template <typename A>
+__device__ __forceinline__ void zero_slots(const A& a, int region, int K, int lb, int cnt) {
+    if (a.both == 0 || threadIdx.x != 0) return;
+    for (int g = lb + cnt; g < a.np; g += cnt)
+        for (int k = 0; k < K; ++k) a.part[(region + k) * a.stride + g] = 0.0;
+}
 // Partial range of system j (for the one-block-per-system kernels).
 template <typename T> __device__ __forceinline__ SysMap sys_range(const BicgArgs<T>& a, int j) {
     return a.one.n > 0 ? SysMap{0, a.G, 0, a.one.n} : a.smap[j];
@@ -714,8 +748,8 @@ __device__ __forceinline__ void finish(SolverScal* sc, int* ndone, int status, i
 
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) / kWave; }
 
-// The sum of K components of partials by the 16 waves of a block: component
-// k by the W = 16 / K (rounded down to a power of two) waves k W .. k W + W - 1,
+// The sum of K components of partials by the NW waves of a block: component
+// k by the W = NW / K (rounded down to a power of two) waves k W .. k W + W - 1,
 // wave i of them taking its partials i, i + W, ... in rounds of 64.  load()
 // issues the loads of the first kHeadNV rounds of each wave, all at once;
 // store() waits for them, adds the rest if any, and puts the wave's sum into
@@ -724,10 +758,10 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 // the eight sums of a head took the SIMDs about 1 us (7.3 us for the C-kernel of
 // 8,000 rows, 4.3 us with a wave per component).
 constexpr int kHeadNV = 4;
-constexpr int head_waves(int K) { return K > 8 ? 1 : (K > 4 ? 2 : (K > 2 ? 4 : 8)); }
-template <int K> struct PartSum {
-    static constexpr int W = head_waves(K);
-    static_assert(K * W <= kBlock / kWave, "K W waves");
+constexpr int head_waves(int K, int NW) { return 2 * K > NW ? 1 : 2 * head_waves(K, NW / 2); }
+template <int K, int NT = kBlock> struct PartSum {
+    static constexpr int W = head_waves(K, NT / kWave);
+    static_assert(K * W <= NT / kWave, "K W waves");
     double v[kHeadNV];
     const double* part;
     int cnt, g0;
@@ -926,8 +960,8 @@ __device__ __forceinline__ int iteration_end(int it, double rr, const EndIn& z, 
 // scalar arithmetic (FP64 divisions and a square root) runs in the first wave
 // only and is broadcast: in all 16 waves it kept the SIMDs busy for longer
 // than the extra barrier costs.
-struct AlphaHead {
-    PartSum<3> ps;
+template <int NT = kBlock> struct AlphaHead {
+    PartSum<3, NT> ps;
     int done, pending, it;
     EndIn z;
 
@@ -945,11 +979,10 @@ struct AlphaHead {
         z.rho = (it & 1) ? r1 : r0;
         const int c = ps.comp();  // <rhat, v>, then ||r||^2
         if (c < 3)
-            ps.load(a.part + (c < 2 ? kPartA + c : kPartC + 2) * a.stride + (c < 2 ? a.pf : 1) * q.gbeg,
-                    (c < 2 ? a.pf : 1) * q.gcnt);
+            ps.load(a.part + (c < 2 ? kPartA + c : kPartC + 2) * a.stride + q.gbeg, c < 2 ? prod_parts(a, q) : q.gcnt);
     }
     template <typename T> __device__ __forceinline__ bool run(const BicgArgs<T>& a, const SysBlock& q, double2& alpha) {
-        __shared__ double tot[kBlock / kWave];
+        __shared__ double tot[NT / kWave];
         __shared__ double2 al;
         __shared__ int go;
         if (ps.comp() < 3) ps.store(tot);
@@ -1028,7 +1061,8 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_A(const BicgArgs<T> a) {
     FirstRow<T, 0> f;
     first_row<T, L, 0>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
     const SolverScal* sc = a.sc + q.sys;
-    if (sc->done || sc->pending) return;
+    if (sc->done || sc->pending || not_csr(a)) return;
+    zero_slots(a, kPartA, 2, q.lb, a.G);
     const cx<T>* __restrict__ p = a.p;
     cx<T>* __restrict__ v = a.v;
     const cx<T>* __restrict__ rh = a.rh;
@@ -1049,8 +1083,8 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_A(const BicgArgs<T> a) {
 template <typename T>
 __global__ HZ_STREAM_BOUNDS void k_bicg_S(const BicgArgs<T> a) {
     const SysBlock q = sys_block(a);
-    if (q.sys < 0) return;
-    AlphaHead hd;
+    if (q.sys < 0 || (a.s_csr && not_csr(a))) return;
+    AlphaHead<> hd;
     hd.load(a, q);
     const cx<T>* __restrict__ v = a.v;
     const cx<T>* __restrict__ r = a.r;
@@ -1105,7 +1139,8 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
     if (q.sys < 0) return;
     FirstRow<T, 0> f;
     first_row<T, L, 0>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
-    if (a.sc[q.sys].done) return;
+    if (a.sc[q.sys].done || not_csr(a)) return;
+    zero_slots(a, kPartB, 8, q.lb, a.G);
     const cx<T>* __restrict__ sv = a.s;
     const cx<T>* __restrict__ rh = a.rh;
     cx<T>* __restrict__ tv = a.t;
@@ -1126,8 +1161,9 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
 template <typename T, int L, int U>
 __global__ __launch_bounds__(kBlock) void k_bicg_SB(const BicgArgs<T> a) {
     const SysBlock q = sys_block(a);
-    if (q.sys < 0) return;
-    AlphaHead hd;
+    if (q.sys < 0 || not_csr(a)) return;
+    zero_slots(a, kPartB, 8, q.lb, a.G);
+    AlphaHead<> hd;
     hd.load(a, q);
     FirstRow<T, U> f;
     first_row<T, L, U>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
@@ -1173,15 +1209,17 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_C(const BicgArgs<T> a) {
     const double2 alpha = sc->alpha, rho_0 = sc->rho2[0], rho_1 = sc->rho2[1];
     const double2 rho = (it & 1) ? rho_1 : rho_0;
     PartSum<8> ps;
-    ps.load(a.part + (kPartB + ps.comp()) * a.stride + a.pf * q.gbeg, a.pf * q.gcnt);
-    cx<T> s0 = mk<T>(T(0), T(0)), t0 = s0;
-    auto load = [&](int64_t j) {
-        s0 = a.s[j];
-        t0 = a.t[j];
-    };
-    int64_t i = q.rw.x0 + (int64_t)q.rw.k * kBlock + threadIdx.x;
-    const int64_t step = (int64_t)q.rw.K * kBlock;
-    if (i < q.rw.x1) load(i);
+    ps.load(a.part + (kPartB + ps.comp()) * a.stride + q.gbeg, prod_parts(a, q));
+    // the first element's s, t and p are in flight during the head (32-bit
+    // indices: with 64-bit ones the kernel spilled two of its 64 registers)
+    cx<T> s0 = mk<T>(T(0), T(0)), t0 = s0, p0 = s0;
+    int i = (int)q.rw.x0 + q.rw.k * kBlock + threadIdx.x;
+    const int step = q.rw.K * kBlock, end = (int)q.rw.x1;
+    if (i < end) {
+        s0 = a.s[i];
+        t0 = a.t[i];
+        p0 = a.p[i];
+    }
     ps.store(tot);
     __syncthreads();
     if (wave_id() == 0) {  // the decision and the scalars, once per block
@@ -1249,15 +1287,19 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_C(const BicgArgs<T> a) {
     }
     const cx<T> omt = narrow<T>(coef[1]), nom = mk<T>(-omt.x, -omt.y), bt = narrow<T>(coef[2]);
     double e[1] = {0.0};
-    while (i < q.rw.x1) {
-        const int64_t j = i;
-        const cx<T> p0 = a.p[j], v = a.v[j];
+    while (i < end) {
+        const int j = i;
+        const cx<T> v = a.v[j];
         cx<T> x = cfma<T>(al, p0, a.x[j]);
         x = cfma<T>(omt, s0, x);
         const cx<T> r = cfma<T>(nom, t0, s0);
         const cx<T> p = p_update<T>(bt, omt, r, p0, v);
-        i += step;
-        if (i < q.rw.x1) load(i);
+        i = i < end - step ? i + step : end;
+        if (i < end) {
+            s0 = a.s[i];
+            t0 = a.t[i];
+            p0 = a.p[i];
+        }
         a.x[j] = x;
         a.r[j] = r;
         a.p[j] = p;
@@ -1360,16 +1402,27 @@ __global__ __launch_bounds__(kBlock) void k_zero_if(const BicgArgs<T> a) {
 
 // ------------------------------------------------------------------ Jacobi folding: A D^{-1}
 
-// dinv_i = 1 / A_ii ; flags a missing or zero diagonal.
+// dinv_i = 1 / A_ii (the last diagonal entry of the row); flags a missing or
+// zero diagonal and, with no != null, what the sliced operator cannot hold: a
+// column too far from the row's slice, or a row without a diagonal.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_jacobi_diag(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                         const cx<T>* __restrict__ vals, cx<T>* __restrict__ dinv,
-                                                        SolverScal* sc) {
+                                                        SolverScal* sc, int* no) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     cx<T> d = mk<T>(T(0), T(0));
-    for (int p = rp[i]; p < rp[i + 1]; ++p)
-        if (ci[p] == i) d = vals[p];
+    const int base = (int)i & ~(kWave - 1);
+    bool far = false, has = false;
+    for (int p = rp[i]; p < rp[i + 1]; ++p) {
+        const int c = ci[p];
+        if (c == i) {
+            d = vals[p];
+            has = true;
+        }
+        far = far || c - base > 32767 || base - c > 32768;
+    }
+    if (no != nullptr && (far || !has)) *no = 1;  // every writer stores 1
     if (d.x == T(0) && d.y == T(0)) {
         sc->bad_diag = 1;  // every writer stores 1
         dinv[i] = mk<T>(T(0), T(0));
@@ -1379,13 +1432,18 @@ __global__ __launch_bounds__(kBlock) void k_jacobi_diag(int n, const int* __rest
     dinv[i] = mk<T>(d.x / q, -d.y / q);
 }
 
-// scaled_p = vals_p * dinv[col_p]   (column scaling A D^{-1})
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_colscale(int64_t nnz, const int* __restrict__ ci, const cx<T>* __restrict__ vals,
-                                                     const cx<T>* __restrict__ dinv, cx<T>* __restrict__ out) {
+// out_p = vals_p * dinv[col_p]   (column scaling A D^{-1}, rounded to TO for
+// the complex64 iteration); with no != null only if the operator is not sliced
+template <typename TO>
+__global__ __launch_bounds__(kBlock) void k_colscale(int64_t nnz, const int* __restrict__ ci,
+                                                     const double2* __restrict__ vals,
+                                                     const double2* __restrict__ dinv, cx<TO>* __restrict__ out,
+                                                     const int* no) {
+    if (no != nullptr && *no == 0) return;
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= nnz) return;
-    out[p] = cmul<T>(vals[p], dinv[ci[p]]);
+    const double2 a = cmul<double>(vals[p], dinv[ci[p]]);
+    out[p] = mk<TO>((TO)a.x, (TO)a.y);
 }
 
 // y_i = d_i x_i with d = 1 / dinv (the preconditioned initial iterate), or x_i = dinv_i y_i at the end
@@ -1476,14 +1534,12 @@ __global__ __launch_bounds__(kBlock) void k_validate(int n, int nnz, const int* 
 // ================================================================== mixed precision (complex64 inner solve)
 namespace hz {
 
-// out32_p = complex64(vals_p * dinv[col_p]) (Jacobi) or complex64(vals_p)
-__global__ __launch_bounds__(kBlock) void k_demote_vals(int64_t nnz, const int* __restrict__ ci,
-                                                        const double2* __restrict__ vals,
-                                                        const double2* __restrict__ dinv, float2* __restrict__ out) {
+// out32_p = complex64(vals_p)
+__global__ __launch_bounds__(kBlock) void k_demote_vals(int64_t nnz, const double2* __restrict__ vals,
+                                                        float2* __restrict__ out) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= nnz) return;
-    double2 v = vals[p];
-    if (dinv != nullptr) v = cmul<double>(v, dinv[ci[p]]);
+    const double2 v = vals[p];
     out[p] = mk<float>((float)v.x, (float)v.y);
 }
 

@@ -1,0 +1,340 @@
+// The sliced operator of a Jacobi solve, and the row products on it.
+//
+// A one-system solve under Jacobi scales the matrix once, so it is free to
+// store A D^{-1} as its products read it best: slices of 64 consecutive rows,
+// entry k of a slice's row g at off + 64 k + g (sliced ELLPACK with slices of
+// a wave, rows in order), every row padded to the slice's longest.  One lane
+// computes one row, so
+//  - a wave's load of entry k is 1 KB of values and 128 bytes of columns,
+//    contiguous, and a slice is one contiguous stream;
+//  - the entries k of 64 consecutive rows of a mesh have nearly consecutive
+//    columns, so a gather touches about 17 cache lines where 64 consecutive
+//    entries of four rows touch about 60 (the tile loop's gathers kept the L1
+//    busy for half of its time, and its waves waited 74 % of theirs);
+//  - no row sum crosses lanes: no LDS, no barrier, a quarter of the
+//    instructions of the tile loop.
+// The diagonal of A D^{-1} is 1 and is left out, and columns are 16-bit
+// offsets from the slice's first row: 18 bytes for 13.6 entries a row of the
+// P1 meshes plus 1.6-3.2 % padding, instead of 20 bytes for 14.6 entries.
+// Measured: v = A p with its dot product on the 1.24 M-row cabin 82.3 -> 66 us
+// (5.9 TB/s of 390 MB), on the 210k-row cylinder 12.7 -> 9 us.
+//
+// A matrix is not sliced when a column is more than 32,767 rows from its
+// slice, a row has no diagonal, or the padding exceeds the room (irregular
+// rows): the set-up kernels find that on the device and leave it in the word
+// after the done-counter (slice_no).  The host of a synchronous solve reads
+// it with the set-up's other results and launches one family of product
+// kernels; an asynchronous solve launches both and each returns unless the
+// word is its own (`both`).
+//
+// A row is summed in the order diagonal, then its entries as stored; a padded
+// slot is a zero value at the row's own column.  Batches of slots are
+// straight-line (a slot past the slice's width reads its last slot and is
+// dropped by a uniform branch): with the loads themselves behind uniform
+// branches the compiler spilled 60 registers and the product took twice as
+// long.
+#pragma once
+
+#include "hz_kernels.hpp"
+
+namespace hz {
+
+constexpr int kSlBlock = 256;            // threads: four waves, one slice each at a time
+constexpr int kSlMaxGrid = 1024;         // blocks (= partials) at most: four per CU
+constexpr int kSlWaves = kSlBlock / kWave;
+#define HZ_SLICE_BOUNDS __launch_bounds__(256, 4)  // four blocks per CU: <= 128 VGPRs
+
+// ------------------------------------------------------------------ set-up
+
+// off[s + 1] = slots of slice s: 64 x (longest row - 1), off[0] = 0
+__global__ __launch_bounds__(kSlBlock) void k_slice_width(int n, const int* __restrict__ rp, int* __restrict__ off) {
+    const int64_t i = (int64_t)blockIdx.x * kSlBlock + threadIdx.x;
+    int len = i < n ? rp[i + 1] - rp[i] - 1 : 0;
+#pragma unroll
+    for (int s = 1; s < kWave; s *= 2) {
+        const int o = __shfl_xor(len, s);
+        len = len > o ? len : o;
+    }
+    if (i == 0) off[0] = 0;
+    if (i < n && threadIdx.x % kWave == 0) off[i / kWave + 1] = kWave * len;  // i / 64 < 2^25
+}
+
+// In-place inclusive scan of off[1 .. ns] by one block; *no = 1 if the slots
+// exceed `room` (the offsets are then not used).
+__global__ __launch_bounds__(kBlock) void k_slice_scan(int ns, int* __restrict__ off, int64_t room, int* no) {
+    __shared__ long long wsum[kBlock / kWave];
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    long long run = 0;
+    for (int64_t c = 0; c < ns; c += kBlock) {  // uniform
+        const int64_t s = c + threadIdx.x;
+        long long v = s < ns ? off[s + 1] : 0;
+#pragma unroll
+        for (int d = 1; d < kWave; d *= 2) {
+            const long long o = __shfl_up(v, d);
+            v += lane >= d ? o : 0;
+        }
+        if (lane == kWave - 1) wsum[wid] = v;
+        __syncthreads();
+        long long before = run, all = run;
+        for (int w = 0; w < kBlock / kWave; ++w) {
+            before += w < wid ? wsum[w] : 0;
+            all += wsum[w];
+        }
+        if (s < ns) off[s + 1] = (int)(before + v);
+        run = all;
+        __syncthreads();  // wsum may be rewritten
+    }
+    if (threadIdx.x == 0 && run > room) *no = 1;
+}
+
+// The slices' values A D^{-1} (rounded to TO for the complex64 iteration) and
+// columns; one lane per row.  The diagonal entry that dinv came from (the
+// row's last) is left out.  Nothing is written if the matrix is not sliced.
+template <typename TO>
+__global__ __launch_bounds__(kSlBlock) void k_slice_fill(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                         const double2* __restrict__ vals,
+                                                         const double2* __restrict__ dinv,
+                                                         const int* __restrict__ off, cx<TO>* __restrict__ out,
+                                                         short* __restrict__ col, const int* no) {
+    if (*no != 0) return;
+    const int64_t i = (int64_t)blockIdx.x * kSlBlock + threadIdx.x;
+    const int64_t s = i / kWave;
+    if (s * kWave >= n) return;  // whole waves
+    const int lane = threadIdx.x % kWave, o = off[s], w = (off[s + 1] - o) / kWave;
+    const int base = (int)(s * kWave);
+    int beg = 0, end = 0, diag = -1;
+    if (i < n) {
+        beg = rp[i];
+        end = rp[i + 1];
+        for (int p = beg; p < end; ++p)
+            if (ci[p] == i) diag = p;
+    }
+    const int own = (int)(i < n ? i : n - 1) - base;  // the padding's column
+    int p = beg;
+    for (int k = 0; k < w; ++k) {  // uniform
+        if (p == diag) ++p;
+        cx<TO> v = mk<TO>(TO(0), TO(0));
+        int c = own;
+        if (p < end) {
+            const int cc = ci[p];
+            const double2 a = cmul<double>(vals[p], dinv[cc]);
+            v = mk<TO>((TO)a.x, (TO)a.y);
+            c = cc - base;
+            ++p;
+        }
+        out[(int64_t)o + (int64_t)k * kWave + lane] = v;
+        col[(int64_t)o + (int64_t)k * kWave + lane] = (short)c;
+    }
+}
+
+// ------------------------------------------------------------------ row products
+
+template <typename T> struct Sliced {
+    const int* __restrict__ off;
+    const short* __restrict__ col;
+    const cx<T>* __restrict__ v;
+};
+
+// The rows of a block of a launch of `sg` sliced product blocks over the
+// one-system map: group x's blocks take its slices four at a time in turn.
+struct SliceRows {
+    int lb;              // the block's partial slot
+    int64_t s, step, s1; // this wave's first slice, the step, the group's end
+};
+__device__ __forceinline__ SliceRows slice_rows_of(const OneMap& one, int sg) {
+    SliceRows q;
+    const int b = blockIdx.x, x = one.groups == kXcd ? b % kXcd : 0, k = one.groups == kXcd ? b / kXcd : b;
+    const int K = sg / one.groups;
+    const int64_t x0 = (int64_t)x * one.gr, x1 = x0 + one.gr < one.n ? x0 + one.gr : one.n;
+    q.lb = x * K + k;
+    q.s = x0 / kWave + (int64_t)k * kSlWaves + wave_id();
+    q.step = (int64_t)K * kSlWaves;
+    q.s1 = (x1 + kWave - 1) / kWave;
+    return q;
+}
+
+template <bool NT, typename P> __device__ __forceinline__ auto ld_if(const P* p) {
+    if constexpr (NT) return ld_mat(p);
+    else return *p;
+}
+
+// A slice's row sums in batches of U slots, all of a batch's loads issued
+// before any is used.  (Issuing the next batch's loads with a batch's gathers
+// gained nothing where it fitted the registers, complex64, and spilled in
+// FP64.)
+template <typename T, int U, bool NT, typename Op>
+__device__ __forceinline__ cx<T> slice_sum(const short* __restrict__ cp, const cx<T>* __restrict__ vp, int base, int w,
+                                           cx<T> acc, Op op) {
+    for (int k0 = 0; k0 < w; k0 += U) {  // uniform
+        short c[U];
+        cx<T> v[U], g[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = ld_if<NT>(cp + (k0 + u < w ? k0 + u : w - 1) * kWave);
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = ld_if<NT>(vp + (k0 + u < w ? k0 + u : w - 1) * kWave);
+#pragma unroll
+        for (int u = 0; u < U; ++u) g[u] = op(base + c[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k0 + u < w) acc = cfma<T>(v[u], g[u], acc);  // uniform
+    }
+    return acc;
+}
+
+// The offset and width of a wave's first slice, loaded ahead of a kernel's head.
+struct FirstSlice {
+    int o = 0, w = 0;
+};
+template <typename T> __device__ __forceinline__ FirstSlice first_slice(const Sliced<T>& m, const SliceRows& q) {
+    FirstSlice f;
+    if (q.s < q.s1) {  // uniform
+        f.o = m.off[q.s];
+        f.w = (m.off[q.s + 1] - f.o) / kWave;
+    }
+    return f;
+}
+
+// epi(row, total, operand of the row, pre(row)) for every row of the wave's
+// slices, one lane per row; op(col) is the gathered operand.  A slice's width
+// is split into equal batches of 4 to 7 slots.  NT: streaming loads, for
+// operators that do not stay in the Infinity Cache (cabin 73 -> 66 us;
+// 12.0 -> 12.8 us on the cylinder, which does).
+template <typename T, bool NT, typename Op, typename Pre, typename Epi>
+__device__ __forceinline__ void slice_rows(const Sliced<T>& m, const SliceRows& q, FirstSlice f, int n, Op op, Pre pre,
+                                           Epi epi) {
+    const int lane = threadIdx.x % kWave;
+    for (int64_t s = q.s; s < q.s1; s += q.step) {  // uniform in the wave
+        const int o = f.o, w = f.w;
+        if (s + q.step < q.s1) {
+            f.o = m.off[s + q.step];
+            f.w = (m.off[s + q.step + 1] - f.o) / kWave;
+        }
+        const int base = (int)(s * kWave), row = base + lane < n ? base + lane : n - 1;
+        const cx<T> self = op(row);
+        const auto pr = pre(row);
+        const short* cp = m.col + (int64_t)o + lane;
+        const cx<T>* vp = m.v + (int64_t)o + lane;
+        const int nb = (w + 6) / 7, u = nb > 0 ? (w + nb - 1) / nb : 0;
+        cx<T> acc = self;
+        switch (u) {  // uniform
+            case 0: break;
+            case 7: acc = slice_sum<T, 7, NT>(cp, vp, base, w, acc, op); break;
+            case 6: acc = slice_sum<T, 6, NT>(cp, vp, base, w, acc, op); break;
+            case 5: acc = slice_sum<T, 5, NT>(cp, vp, base, w, acc, op); break;
+            default: acc = slice_sum<T, 4, NT>(cp, vp, base, w, acc, op); break;
+        }
+        if (base + lane < n) epi((int64_t)row, acc, self, pr);
+    }
+}
+
+// The block's totals of K doubles to out[k * stride], summed through LDS (the
+// values of 256 threads per component, then one wave per component at a time):
+// with every row in a lane of its own the wave butterflies of eight sums would
+// take about 1 us of the SIMDs.
+template <int K>
+__device__ __forceinline__ void slice_store(double* __restrict__ out, int stride, double (&e)[K]) {
+    __shared__ double l[K][kSlBlock];
+    const int lane = threadIdx.x % kWave, w = wave_id();
+#pragma unroll
+    for (int k = 0; k < K; ++k) l[k][threadIdx.x] = e[k];
+    __syncthreads();
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += kSlWaves) {
+        const int k = k0 + w;
+        if (k < K) {
+            const double* p = l[k] + lane;
+            const double t = wave_sum<1>((p[0] + p[kWave]) + (p[2 * kWave] + p[3 * kWave]));
+            if (lane == 0) out[k * stride] = t;
+        }
+    }
+}
+
+// ------------------------------------------------------------------ BiCGStab's products on it
+
+template <typename T> __device__ __forceinline__ Sliced<T> sliced_of(const BicgArgs<T>& a) {
+    return Sliced<T>{a.soff, a.scol, a.vals};
+}
+// Whether a sliced product kernel has nothing to do.
+template <typename A> __device__ __forceinline__ bool not_sliced(const A& a) {
+    return a.both != 0 && *slice_no(a.ndone) != 0;
+}
+
+// v = A p; partial <rhat, v>
+template <typename T, bool NT>
+__global__ HZ_SLICE_BOUNDS void k_bicg_As(const BicgArgs<T> a) {
+    const SliceRows q = slice_rows_of(a.one, a.sg);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    const SolverScal* sc = a.sc;
+    if (sc->done || sc->pending || not_sliced(a)) return;
+    zero_slots(a, kPartA, 2, q.lb, a.sg);
+    const cx<T>* __restrict__ p = a.p;
+    const cx<T>* __restrict__ rh = a.rh;
+    cx<T>* __restrict__ v = a.v;
+    double e[2] = {0.0, 0.0};
+    slice_rows<T, NT>(
+        sliced_of(a), q, f, a.one.n, [p](int c) { return p[c]; }, [rh](int row) { return rh[row]; },
+        [&](int64_t row, cx<T> acc, cx<T>, cx<T> w) {
+            v[row] = acc;
+            const double2 c = cdotacc(w.x, w.y, acc.x, acc.y, mk<double>(e[0], e[1]));
+            e[0] = c.x;
+            e[1] = c.y;
+        });
+    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+}
+
+// t = A s and its dot products
+template <typename T, bool NT>
+__global__ HZ_SLICE_BOUNDS void k_bicg_Bs(const BicgArgs<T> a) {
+    const SliceRows q = slice_rows_of(a.one, a.sg);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    if (a.sc->done || not_sliced(a)) return;
+    zero_slots(a, kPartB, 8, q.lb, a.sg);
+    const cx<T>* __restrict__ sv = a.s;
+    const cx<T>* __restrict__ rh = a.rh;
+    cx<T>* __restrict__ tv = a.t;
+    double e[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    slice_rows<T, NT>(
+        sliced_of(a), q, f, a.one.n, [sv](int c) { return sv[c]; }, [rh](int row) { return rh[row]; },
+        [&](int64_t row, cx<T> acc, cx<T> s, cx<T> w) {
+            tv[row] = acc;
+            b_terms<T>(e, s, acc, w);
+        });
+    slice_store<8>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+}
+
+// The same with the S-kernel's head, s formed for every gathered column and stored.
+// (No register limit: it gathers two vectors, and runs on systems that do not
+// fill the chip; 9 spilled registers cost 1.5 us.)
+template <typename T>
+__global__ __launch_bounds__(kSlBlock) void k_bicg_SBs(const BicgArgs<T> a) {
+    const SliceRows q = slice_rows_of(a.one, a.sg);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    if (not_sliced(a)) return;
+    zero_slots(a, kPartB, 8, q.lb, a.sg);
+    SysBlock sb{};
+    sb.sys = 0;
+    sb.local = q.lb;
+    sb.gbeg = 0;
+    sb.gcnt = a.G;
+    AlphaHead<kSlBlock> hd;
+    hd.load(a, sb);
+    double2 alpha;
+    if (!hd.run(a, sb, alpha)) return;
+    const cx<T> nal = mk<T>((T)-alpha.x, (T)-alpha.y);
+    const cx<T>* __restrict__ r = a.r;
+    const cx<T>* __restrict__ v = a.v;
+    const cx<T>* __restrict__ rh = a.rh;
+    cx<T>* __restrict__ sv = a.s;
+    cx<T>* __restrict__ tv = a.t;
+    double e[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    slice_rows<T, false>(
+        sliced_of(a), q, f, a.one.n, [=](int c) { return cfma<T>(nal, v[c], r[c]); }, [rh](int row) { return rh[row]; },
+        [&](int64_t row, cx<T> acc, cx<T> s, cx<T> w) {
+            sv[row] = s;
+            tv[row] = acc;
+            b_terms<T>(e, s, acc, w);
+        });
+    slice_store<8>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+}
+
+}  // namespace hz

@@ -15,7 +15,7 @@
 // tiles and stored when the ring is flushed.  Sub-block j of logical block lb
 // takes 64-row tiles j, j + F K, ... of its group's rows, and writes its
 // partials to a slot of its own; the regions' readers sum F slots per block
-// (BicgArgs::pf = F).  Sums are taken in a fixed order: results are bitwise
+// (BicgArgs::np = F G).  Sums are taken in a fixed order: results are bitwise
 // reproducible.
 #pragma once
 
@@ -38,7 +38,8 @@ __global__ __launch_bounds__(kSpBlock) void k_bicg_At(const BicgArgs<T> a) {
     const SysBlock q = map_block(a.one, a.bmap, a.smap, a.G, a.pf, blockIdx.x);
     if (q.sys < 0) return;
     const SolverScal* sc = a.sc + q.sys;
-    if (sc->done || sc->pending) return;
+    if (sc->done || sc->pending || not_csr(a)) return;
+    zero_slots(a, kPartA, 2, q.lb, a.pf * a.G);
     const cx<T>* __restrict__ p = a.p;
     cx<T>* __restrict__ v = a.v;
     const cx<T>* __restrict__ rh = a.rh;
@@ -58,7 +59,8 @@ template <typename T>
 __global__ __launch_bounds__(kSpBlock) void k_bicg_Bt(const BicgArgs<T> a) {
     const SysBlock q = map_block(a.one, a.bmap, a.smap, a.G, a.pf, blockIdx.x);
     if (q.sys < 0) return;
-    if (a.sc[q.sys].done) return;
+    if (a.sc[q.sys].done || not_csr(a)) return;
+    zero_slots(a, kPartB, 8, q.lb, a.pf * a.G);
     const cx<T>* __restrict__ sv = a.s;
     const cx<T>* __restrict__ rh = a.rh;
     cx<T>* __restrict__ tv = a.t;

@@ -70,3 +70,74 @@ def test_iterates_follow_the_oracle(hz, monkeypatch, n, fused):
             assert err <= 1e-12
             if n >= 8:
                 assert abs(info["relres_recursive"] - io["relres_recursive"]) <= 1e-9 * io["relres_recursive"]
+
+
+def regular(n, k, seed, far=0):
+    """About k off-diagonal entries in every row, at k common offsets within 150 rows (2 % of them missing at random),
+    dominated by the diagonal; far > 0 adds one entry that many rows from the diagonal."""
+    rng = np.random.default_rng(seed)
+    offsets = rng.choice(np.concatenate([np.arange(-150, 0), np.arange(1, 151)]), k, replace=False) if k else np.zeros(0, int)
+    r = np.repeat(np.arange(n, dtype=np.int64), k)
+    c = (np.arange(n, dtype=np.int64)[:, None] + offsets[None, :]).ravel()
+    keep = (c >= 0) & (c < n) & (rng.random(r.size) > 0.02)
+    r, c = r[keep], c[keep]
+    if far:
+        r, c = np.append(r, 7), np.append(c, 7 + far)
+    vals = rng.standard_normal(r.size) + 1j * rng.standard_normal(r.size)
+    absum = np.bincount(r, weights=np.abs(vals), minlength=n)
+    r, c = np.concatenate([r, np.arange(n)]), np.concatenate([c, np.arange(n)])
+    v = np.concatenate([vals, (2.0 + absum) * np.exp(1j * rng.uniform(0, 2 * np.pi, n))])
+    o = np.lexsort((c, r))
+    rp = np.zeros(n + 1, np.int32)
+    np.cumsum(np.bincount(r, minlength=n), out=rp[1:])
+    return CSR(rp, c[o].astype(np.int32), v[o])
+
+
+# Off-diagonal entries a row on both sides of the batches of 4 to 7 slots, and rows past and short of a slice's end;
+# sizes on both sides of the fused form's line for the sliced operator; an entry at the 16-bit columns' limit (from
+# row 7, in the slice of row 0: 32,767 rows away at most) and one past it, which leaves the matrix in CSR.
+SLICED = [(12544, k, 0) for k in (0, 1, 3, 4, 7, 8, 13, 14)] + [
+    (12545, 6, 0), (12607, 13, 0), (40000, 13, 32760), (40000, 13, 32761), (163840, 6, 0), (163841, 6, 0)]
+
+
+@pytest.mark.parametrize("n,k,far", SLICED)
+def test_sliced_operator_follows_the_oracle(hz, n, k, far):
+    """The iterates of a Jacobi solve on the sliced operator (or, where it cannot hold the matrix, in CSR) against the
+    oracle's, with the bound above; the asynchronous solve, which leaves the choice to the device, bit for bit the
+    same; and one complex64 correction, whose operator is sliced at any size."""
+    A = regular(n, k, seed=n + k, far=far)
+    rng = np.random.default_rng(8)
+    b = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    rp, ci, v, bd = dev(A.row_ptr), dev(A.col_idx), dev(A.vals), dev(b)
+    iters = 1 if k == 0 else 5  # a diagonal matrix is solved by the first step
+    flags = hz.PRECOND_JACOBI | hz.X0_ZERO | hz.NO_REORDER
+    tol = 1e-9 if k == 0 else 0.0
+    x, info = hz.zbicgstab_solve(rp, ci, v, bd, rtol=tol, maxiter=iters, flags=flags)
+    xo, io = O.zbicgstab(A, b, tol=tol, maxiter=iters, jacobi=True)
+    assert info["iterations"] == io["iterations"] and info["status"] == io["status"]
+    err = np.linalg.norm(x.cpu().numpy() - xo) / np.linalg.norm(xo)
+    print(f"n={n} k={k} far={far}: {err:.2e}")
+    assert err <= 1e-12
+    xa, ia = hz.zbicgstab_solve_async(rp, ci, v, bd, rtol=tol, maxiter=iters, flags=hz.PRECOND_JACOBI | hz.X0_ZERO)
+    assert torch.equal(torch.view_as_real(x), torch.view_as_real(xa))
+    assert hz.read_info(ia)["iterations"] == info["iterations"]
+    for more in (0, hz.RELIABLE):
+        xm, im = hz.zbicgstab_solve_mixed(rp, ci, v, bd, rtol=1e-10, flags=flags | more)
+        assert im["status"] == hz.OK
+        assert np.linalg.norm(b - O.zspmv(A, xm.cpu().numpy())) <= 1e-10 * (1 + 1e-3) * np.linalg.norm(b)
+
+
+def test_row_without_diagonal_is_invalid(hz):
+    """A missing diagonal under Jacobi: refused by the synchronous solve, reported by the asynchronous one."""
+    A = regular(12544, 6, seed=3)
+    rows = A.row_of_entry()
+    keep = ~((rows == 5000) & (A.col_idx == 5000))
+    rp = np.zeros(A.n + 1, np.int32)
+    np.cumsum(np.bincount(rows[keep], minlength=A.n), out=rp[1:])
+    rp, ci, v = dev(rp), dev(A.col_idx[keep]), dev(A.vals[keep])
+    b = dev(np.ones(A.n, complex))
+    with pytest.raises(hz.HelmzError) as e:
+        hz.zbicgstab_solve(rp, ci, v, b, flags=hz.PRECOND_JACOBI | hz.X0_ZERO)
+    assert e.value.code == -1
+    _, info = hz.zbicgstab_solve_async(rp, ci, v, b, maxiter=2, flags=hz.PRECOND_JACOBI | hz.X0_ZERO)
+    assert hz.read_info(info)["status"] == -1
