@@ -1121,19 +1121,24 @@ int solve_single(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, con
 
 // ------------------------------------------------------------------ BiCGstab(l)
 
-// Workspace: scalars, partials, the done counter, r~,
-// r_0 .. r_l, u_0 .. u_l, a residual vector, Jacobi D^{-1} and A D^{-1},
-// the Gram partials and the minimal-residual coefficients.
+// Workspace: scalars, partials, the done counter, r~, r_0 .. r_{l-1} and
+// u_0 .. u_{l-1}, two vectors each that the products write by turns, Jacobi
+// D^{-1} and A D^{-1} with room for its slices, the Gram partials and the
+// minimal-residual coefficients.  (The set-up's and the true residual use r_0.)
 struct LWs {
     SolverScal* sc;
     double* part;
     int* ndone;
+    hz::LScal* ls;
     double2* rt;
-    double2* r[hz::kLMax + 1];
-    double2* u[hz::kLMax + 1];
-    double2* t;
+    double2* r[hz::kLMax];
+    double2* u[hz::kLMax];
+    double2* rp[2];
+    double2* up[2];
     double2* dinv;
     double2* ahat;
+    int* soff;
+    short* scol;
     double* gpart;
     double2* gam;
 };
@@ -1150,12 +1155,16 @@ size_t lws_layout(int n, int64_t nnz, int ell, bool jacobi, char* base, LWs* out
     w.sc = static_cast<SolverScal*>(take(sizeof(SolverScal)));
     w.part = static_cast<double*>(take(sizeof(double) * size_t(hz::kParts) * size_t(bicg_stride(kMaxGrid))));
     w.ndone = static_cast<int*>(take(sizeof(int)));
+    w.ls = static_cast<hz::LScal*>(take(sizeof(hz::LScal)));
     w.rt = static_cast<double2*>(take(vb));
-    for (int p = 0; p <= ell; ++p) w.r[p] = static_cast<double2*>(take(vb));
-    for (int p = 0; p <= ell; ++p) w.u[p] = static_cast<double2*>(take(vb));
-    w.t = static_cast<double2*>(take(vb));
+    for (int p = 0; p < ell; ++p) w.r[p] = static_cast<double2*>(take(vb));
+    for (int p = 0; p < ell; ++p) w.u[p] = static_cast<double2*>(take(vb));
+    for (int p = 0; p < 2; ++p) w.rp[p] = static_cast<double2*>(take(vb));
+    for (int p = 0; p < 2; ++p) w.up[p] = static_cast<double2*>(take(vb));
     w.dinv = jacobi ? static_cast<double2*>(take(vb)) : nullptr;
     w.ahat = jacobi ? static_cast<double2*>(take(sizeof(double2) * size_t(nnz > 0 ? nnz : 1))) : nullptr;
+    w.soff = jacobi ? static_cast<int*>(take(slice_off_bytes(n))) : nullptr;
+    w.scol = jacobi ? static_cast<short*>(take(slice_col_bytes(nnz))) : nullptr;
     w.gpart = static_cast<double*>(take(sizeof(double) * 2 * size_t(hz::kGramPairs) * size_t(hz::kGramMaxGrid)));
     w.gam = static_cast<double2*>(take(sizeof(double2) * (hz::kLMax + 1)));
     if (out) *out = w;
@@ -1189,16 +1198,18 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     const bool jacobi = (flags & HZ_PRECOND_JACOBI) != 0;
     const int L = solve_lanes(h, rp, ci, n, nnz);
     const int row_off[2] = {0, n};
-    const WorkMap m = build_map(1, row_off, L);
+    WorkMap m = build_map(1, row_off, L);
     LWs w;
     lws_layout(n, nnz, ell, jacobi, ws, &w);
+    const bool room = jacobi && nnz > 0;
+    if (room) m.one = one_map(n, m.G, hz::kWave);
     hipLaunchKernelGGL(hz::k_sc_init, dim3(1), dim3(256), 0, s, w.sc, 1, rtol, maxcycles);
+    HZ_HIP(hipMemsetAsync(w.ndone, 0, 2 * sizeof(int), s));
+    HZ_HIP(hipMemsetAsync(w.ls, 0, sizeof(hz::LScal), s));
     const double2* Aop = A;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, w.dinv, w.sc, nullptr);
-        if (nnz > 0)
-            hipLaunchKernelGGL(hz::k_colscale<double>, grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A,
-                               static_cast<const double2*>(w.dinv), w.ahat, nullptr);
+        enqueue_jacobi<double>(s, n, nnz, rp, ci, A, w.dinv, w.sc, w.ahat, room ? w.soff : nullptr, w.scol,
+                               w.ndone + 1);
         Aop = w.ahat;
     }
     // the BiCGStab set-up and finishing kernels on the same map, scalars and partials
@@ -1211,76 +1222,101 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     ba.col_idx = ci;
     ba.vals = Aop;
     ba.b = bd;
-    ba.r = w.r[0];
+    ba.r = w.rp[0];
     ba.rh = w.rt;
     ba.x = xd;
     ba.part = w.part;
     ba.sc = w.sc;
-    HZ_HIP(hipMemsetAsync(w.ndone, 0, sizeof(int), s));
-    HZ_HIP(hipMemsetAsync(w.u[0], 0, 16 * size_t(n), s));
+    HZ_HIP(hipMemsetAsync(w.up[0], 0, 16 * size_t(n), s));
     const double2* rsrc = bd;
     if (flags & HZ_X0_ZERO) {
         HZ_HIP(hipMemsetAsync(xd, 0, 16 * size_t(n), s));
     } else {
         if (jacobi) hipLaunchKernelGGL(hz::k_diag_apply<double>, grid1(n), dim3(kBlock), 0, s, n, w.dinv, xd, 1);
-        launch_sys_resid<double>(L, m, ba, Aop, xd, w.t, s);
-        rsrc = w.t;
+        launch_sys_resid<double>(L, m, ba, Aop, xd, w.r[0], s);
+        rsrc = w.r[0];
     }
     hipLaunchKernelGGL(hz::k_init<double>, dim3(m.G), dim3(kBlock), 0, s, ba, rsrc);
     hipLaunchKernelGGL(hz::k_fin_init<double>, dim3(1), dim3(kBlock), 0, s, ba);
     HZ_HIP(hipGetLastError());
     SolverScal* hs = h->hsc;
     HZ_HIP(hipMemcpyAsync(hs, w.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
-    HZ_HIP(hipMemcpyAsync(h->hflag, w.ndone, sizeof(int), hipMemcpyDeviceToHost, s));
+    HZ_HIP(hipMemcpyAsync(h->hflag, w.ndone, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     if (hs->bad_diag) return HZ_ERR_INVALID;
 
+    const bool sliced = room && h->hflag[1] == 0;
+    const bool nt = slice_stream<double>(nnz);
     hz::LArgs la{};
     la.G = m.G;
     la.stride = ba.stride;
-    const bool sub = L == 1;  // the tile row loop: AU and AR as sub-blocks with the LDS result ring
+    const bool sub = L == 1;  // the tile row loop: products as sub-blocks with the LDS result ring
     la.pf = sub ? hz::sol_subs(m.G) : 1;
+    la.np = sliced ? slice_grid(m.one) : la.pf * m.G;
     la.one = m.one;
     la.ndone = w.ndone;
     la.row_ptr = rp;
     la.col_idx = ci;
     la.vals = Aop;
+    la.soff = w.soff;
+    la.scol = w.scol;
     la.rt = w.rt;
-    for (int p = 0; p <= ell; ++p) {
+    for (int p = 0; p < 2; ++p) {
+        la.rp[p] = w.rp[p];
+        la.up[p] = w.up[p];
+    }
+    for (int p = 0; p < ell; ++p) {
         la.r[p] = w.r[p];
         la.u[p] = w.u[p];
     }
+    la.r[ell] = w.rp[ell & 1];
+    la.u[ell] = w.up[ell & 1];
     la.x = xd;
     la.part = w.part;
     la.gpart = w.gpart;
     la.gam = w.gam;
+    la.ls = w.ls;
     la.sc = w.sc;
     la.n = n;
     la.ell = ell;
     la.gG = int(std::min<int64_t>(hz::kGramMaxGrid, (int64_t(n) + hz::kGramBlock - 1) / hz::kGramBlock));
+    la.uG = int(std::min<int64_t>(hz::kLUpMaxGrid, (int64_t(n) + hz::kLUpBlock - 1) / hz::kLUpBlock));
     const dim3 G(m.G), B(kBlock);
+    // a launch's arguments: step j, dst = add - c src or dst = A src
+    auto with = [&la](int j, const double2* src, const double2* add, double2* dst, int reg) {
+        hz::LArgs a = la;
+        a.j = j;
+        a.src = src;
+        a.add = add;
+        a.dst = dst;
+        a.reg = reg;
+        return a;
+    };
+    auto first = [&](int j) { return with(j, la.up[j & 1], la.rp[j & 1], la.u[j], 0); };
+    auto product = [&](hipStream_t q, const hz::LArgs& a) {
+        if (sliced && nt)
+            hipLaunchKernelGGL((hz::k_l_As<true>), dim3(a.np), dim3(hz::kSlBlock), 0, q, a);
+        else if (sliced)
+            hipLaunchKernelGGL((hz::k_l_As<false>), dim3(a.np), dim3(hz::kSlBlock), 0, q, a);
+        else if (sub)
+            hipLaunchKernelGGL(hz::k_l_At, dim3(a.np), dim3(hz::kSpBlock), 0, q, a);
+        else
+            with_lanes(L, [&]<int LL, int UU>() { hipLaunchKernelGGL((hz::k_l_A<LL, UU>), G, B, 0, q, a); });
+    };
     auto cycle = [&](hipStream_t q) {
-        with_lanes(L, [&]<int LL, int UU>() {
-            for (int j = 0; j < ell; ++j) {
-                hz::LArgs aj = la;
-                aj.j = j;
-                hipLaunchKernelGGL(hz::k_l_U, G, B, 0, q, aj);
-                if (sub)
-                    hipLaunchKernelGGL(hz::k_l_AUt, dim3(aj.pf * m.G), dim3(hz::kSpBlock), 0, q, aj);
-                else
-                    hipLaunchKernelGGL((hz::k_l_AU<LL, UU>), G, B, 0, q, aj);
-                hipLaunchKernelGGL(hz::k_l_R, G, B, 0, q, aj);
-                if (sub)
-                    hipLaunchKernelGGL(hz::k_l_ARt, dim3(aj.pf * m.G), dim3(hz::kSpBlock), 0, q, aj);
-                else
-                    hipLaunchKernelGGL((hz::k_l_AR<LL, UU>), G, B, 0, q, aj);
-            }
-        });
+        for (int j = 0; j < ell; ++j) {
+            double2* const un = la.up[(j + 1) & 1];
+            double2* const rn = la.rp[(j + 1) & 1];
+            hipLaunchKernelGGL(hz::k_l_U, G, B, 0, q, first(j));
+            product(q, with(j, la.u[j], nullptr, un, hz::kPartA));
+            hipLaunchKernelGGL(hz::k_l_R, G, B, 0, q, with(j, un, la.rp[j & 1], la.r[j], 0));
+            product(q, with(j, la.r[j], nullptr, rn, hz::kPartC));
+        }
         with_ell(ell, [&]<int EL>() {
             hipLaunchKernelGGL((hz::k_l_gram<EL>), dim3(la.gG), dim3(hz::kGramBlock), 0, q, la);
             hipLaunchKernelGGL((hz::k_l_mr<EL>), dim3(1), B, 0, q, la);
+            hipLaunchKernelGGL((hz::k_l_update<EL>), dim3(la.uG), dim3(hz::kLUpBlock), 0, q, la);
         });
-        hipLaunchKernelGGL(hz::k_l_update, G, B, 0, q, la);
     };
     int launched = 0, poll = 1;
     int rc = HZ_OK;
@@ -1288,11 +1324,9 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
         while (launched < maxcycles) {
             const int k_n = (maxcycles - launched) < poll ? (maxcycles - launched) : poll;
             const bool tail = launched + k_n == maxcycles;
-            hz::LArgs a0 = la;
-            a0.j = 0;
-            rc = launch_chunk(h, s, chunk_key(40 + ell, L, k_n, tail, la), [&](hipStream_t q) {
+            rc = launch_chunk(h, s, chunk_key(40 + ell + (sliced ? 100 : 0), L, k_n, tail, la), [&](hipStream_t q) {
                 for (int k = 0; k < k_n; ++k) cycle(q);
-                if (tail) hipLaunchKernelGGL(hz::k_l_U, G, B, 0, q, a0);
+                if (tail) hipLaunchKernelGGL(hz::k_l_U, G, B, 0, q, first(0));
             });
             if (rc) return rc;
             launched += k_n;
@@ -1302,11 +1336,12 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
             if (poll < 8) poll *= 2;
         }
     }
+    hipLaunchKernelGGL(hz::k_l_late, dim3(la.uG), dim3(hz::kLUpBlock), 0, s, la);
     hipLaunchKernelGGL(hz::k_zero_if<double>, G, B, 0, s, ba);
     if (jacobi) hipLaunchKernelGGL(hz::k_diag_apply<double>, grid1(n), dim3(kBlock), 0, s, n, w.dinv, xd, 0);
     hz::BicgArgs<double> b0 = ba;  // true residual with the caller's matrix
     b0.vals = A;
-    launch_sys_resid<double>(L, m, b0, A, xd, w.t, s);
+    launch_sys_resid<double>(L, m, b0, A, xd, w.r[0], s);
     hipLaunchKernelGGL(hz::k_fin_true<double>, dim3(1), B, 0, s, b0);
     HZ_HIP(hipGetLastError());
     SolverScal out;
