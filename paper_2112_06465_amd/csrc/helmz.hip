@@ -382,19 +382,20 @@ int enqueue_far_count(hz_handle* h, hipStream_t s, int n, const int* rp, const i
     return HZ_OK;
 }
 
-// Which iteration: the gather-light one (s and, in TFQMR, u'' materialised, one
-// gathered vector per product) or the fused one (formed per gathered column,
-// two gathered vectors, one launch fewer).  Each launch costs about 3 us of
+// Which iteration: the gather-light one (s and, in TFQMR, u' and u materialised,
+// one gathered vector per product) or the fused one (formed per gathered column,
+// two gathered vectors, one launch fewer, or two in TFQMR).  Each launch costs about 3 us of
 // start-up, head and tail; the second gathered vector costs more from some
 // size on, which is larger for the sliced operator, whose gathers touch a
 // third of the cache lines.  BiCGStab, us per iteration, fused / split: CSR,
 // 8,000 rows 14.6 / 16.0, 46,656 rows 17.5 / 18.5, 57,005 rows 21.9 / 21.8,
 // 92,477 rows 26.3 / 24.7; sliced, 57,005 rows 17.2 / 19.0, 92,477 rows 21.0 /
-// 22.3, 125,885 rows 25.8 / 27.6, 209,777 rows 41.1 / 38.1.
+// 22.3, 125,885 rows 25.8 / 27.6, 209,777 rows 41.1 / 38.1.  TFQMR: CSR, 24,353
+// rows 18.4 / 19.0, 57,005 rows 21.5 / 21.3, 125,885 rows 33.6 / 31.6; sliced,
+// 57,005 rows 14.6 / 19.2, 163,401 rows 31.8 / 33.8, 209,777 rows 44.4 / 40.1.
 // `rows` is the total over the systems of a launch.  HZ_FUSED=0/1 overrides.
 constexpr int64_t kFusedMaxRows = 57344;
 constexpr int64_t kFusedMaxRowsSliced = 163840;
-constexpr int64_t kFusedMaxRowsQ = 131072;  // TFQMR's third launch
 bool choose_fused(const hz_handle*, int64_t rows, int64_t most = kFusedMaxRows) {
     if (const char* env = std::getenv("HZ_FUSED")) return std::atoi(env) != 0;
     return rows <= most;
@@ -1360,7 +1361,7 @@ int solve_l(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
 
 // Workspace: scalars, partials, the done counter, the
 // TFQMR scalars, r_0, r~, w, u, u', A u, A u', v, d, a residual vector,
-// Jacobi D^{-1} and A D^{-1}.
+// Jacobi D^{-1} and A D^{-1} with room for its slices.
 struct QWs {
     SolverScal* sc;
     double* part;
@@ -1369,6 +1370,8 @@ struct QWs {
     double2 *r0, *rt, *w, *u, *u1, *au, *au1, *v, *d, *t;
     double2* dinv;
     double2* ahat;
+    int* soff;
+    short* scol;
 };
 
 size_t qws_layout(int n, int64_t nnz, bool jacobi, char* base, QWs* out) {
@@ -1381,13 +1384,15 @@ size_t qws_layout(int n, int64_t nnz, bool jacobi, char* base, QWs* out) {
     };
     QWs w{};
     w.sc = static_cast<SolverScal*>(take(sizeof(SolverScal)));
-    w.part = static_cast<double*>(take(sizeof(double) * size_t(hz::kParts) * size_t(kMaxGrid)));
+    w.part = static_cast<double*>(take(sizeof(double) * size_t(hz::kParts) * size_t(bicg_stride(kMaxGrid))));
     w.ndone = static_cast<int*>(take(sizeof(int)));
     w.tq = static_cast<hz::TScal*>(take(sizeof(hz::TScal)));
     for (double2** v : {&w.r0, &w.rt, &w.w, &w.u, &w.u1, &w.au, &w.au1, &w.v, &w.d, &w.t})
         *v = static_cast<double2*>(take(vb));
     w.dinv = jacobi ? static_cast<double2*>(take(vb)) : nullptr;
     w.ahat = jacobi ? static_cast<double2*>(take(sizeof(double2) * size_t(nnz > 0 ? nnz : 1))) : nullptr;
+    w.soff = jacobi ? static_cast<int*>(take(slice_off_bytes(n))) : nullptr;
+    w.scol = jacobi ? static_cast<short*>(take(slice_col_bytes(nnz))) : nullptr;
     if (out) *out = w;
     return off;
 }
@@ -1398,28 +1403,29 @@ size_t qsolve_ws_bytes(int n, int64_t nnz, int flags) {
 }
 
 // TFQMR of one system on (rp, ci, A); iterations in chunks of 8, 16, ..., 64
-// (three launches each) with a poll of the done counter between chunks,
+// (two or four launches each) with a poll of the done counter between chunks,
 // each chunk replayed from a cached graph.
 int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const int* ci, const double2* A,
             const double2* bd, double2* xd, double rtol, int maxiter, int flags, char* ws, hz_solve_info* info) {
     const bool jacobi = (flags & HZ_PRECOND_JACOBI) != 0;
     const int L = solve_lanes(h, rp, ci, n, nnz);
     const int row_off[2] = {0, n};
-    const WorkMap m = build_map(1, row_off, L);
+    WorkMap m = build_map(1, row_off, L);
     QWs w;
     qws_layout(n, nnz, jacobi, ws, &w);
+    const bool room = jacobi && nnz > 0;
+    if (room) m.one = one_map(n, m.G, hz::kWave);
     hipLaunchKernelGGL(hz::k_sc_init, dim3(1), dim3(256), 0, s, w.sc, 1, rtol, maxiter);
+    HZ_HIP(hipMemsetAsync(w.ndone, 0, 2 * sizeof(int), s));
     const double2* Aop = A;
     if (jacobi) {
-        hipLaunchKernelGGL(hz::k_jacobi_diag<double>, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, w.dinv, w.sc, nullptr);
-        if (nnz > 0)
-            hipLaunchKernelGGL(hz::k_colscale<double>, grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A,
-                               static_cast<const double2*>(w.dinv), w.ahat, nullptr);
+        enqueue_jacobi<double>(s, n, nnz, rp, ci, A, w.dinv, w.sc, w.ahat, room ? w.soff : nullptr, w.scol,
+                               w.ndone + 1);
         Aop = w.ahat;
     }
     hz::BicgArgs<double> ba{};  // the BiCGStab set-up and finishing kernels on the same map and scalars
     ba.G = m.G;
-    ba.stride = m.stride;
+    ba.stride = bicg_stride(m.G);
     ba.one = m.one;
     ba.ndone = w.ndone;
     ba.row_ptr = rp;
@@ -1431,7 +1437,6 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     ba.x = xd;
     ba.part = w.part;
     ba.sc = w.sc;
-    HZ_HIP(hipMemsetAsync(w.ndone, 0, sizeof(int), s));
     const double2* rsrc = bd;
     if (flags & HZ_X0_ZERO) {
         HZ_HIP(hipMemsetAsync(xd, 0, 16 * size_t(n), s));
@@ -1444,12 +1449,14 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     hipLaunchKernelGGL(hz::k_fin_init<double>, dim3(1), dim3(kBlock), 0, s, ba);
     hz::QArgs qa{};
     qa.G = m.G;
-    qa.stride = m.stride;
+    qa.stride = ba.stride;
     qa.one = m.one;
     qa.ndone = w.ndone;
     qa.row_ptr = rp;
     qa.col_idx = ci;
     qa.vals = Aop;
+    qa.soff = w.soff;
+    qa.scol = w.scol;
     qa.rt = w.rt;
     qa.w = w.w;
     qa.u = w.u;
@@ -1464,33 +1471,52 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     qa.tq = w.tq;
     const dim3 G(m.G), B(kBlock);
     hipLaunchKernelGGL(hz::k_q_fin_init, dim3(1), B, 0, s, qa);
-    with_lanes(L, [&]<int LL, int UU>() {
-        hipLaunchKernelGGL((hz::k_q_init<LL, UU>), G, B, 0, s, qa, static_cast<const double2*>(w.r0));
-    });
     HZ_HIP(hipGetLastError());
     SolverScal* hs = h->hsc;
     HZ_HIP(hipMemcpyAsync(hs, w.sc, sizeof(SolverScal), hipMemcpyDeviceToHost, s));
-    HZ_HIP(hipMemcpyAsync(h->hflag, w.ndone, sizeof(int), hipMemcpyDeviceToHost, s));
+    HZ_HIP(hipMemcpyAsync(h->hflag, w.ndone, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HZ_HIP(hipStreamSynchronize(s));
     if (hs->bad_diag) return HZ_ERR_INVALID;
+    const bool sliced = room && h->hflag[1] == 0, nt = slice_stream<double>(nnz);
+    qa.np = sliced ? slice_grid(m.one) : m.G;
+    const dim3 SG(qa.np), SB(hz::kSlBlock);
+    const double2* r0 = w.r0;
+    if (sliced)
+        hipLaunchKernelGGL(hz::k_q_inits, SG, SB, 0, s, qa, r0);
+    else
+        with_lanes(L, [&]<int LL, int UU>() { hipLaunchKernelGGL((hz::k_q_init<LL, UU>), G, B, 0, s, qa, r0); });
+    HZ_HIP(hipGetLastError());
     int launched = 0, poll = 8, rc = HZ_OK;
-    const bool fused = choose_fused(h, n, kFusedMaxRowsQ);  // K3 in one launch (two gathered vectors) or gather-light
+    const bool fused = choose_fused(h, n, sliced ? kFusedMaxRowsSliced : kFusedMaxRows);
+    auto iteration = [&](hipStream_t q) {
+        if (!fused) hipLaunchKernelGGL(hz::k_q_dir1, G, B, 0, q, qa);
+        if (sliced) {
+            if (fused) hipLaunchKernelGGL(hz::k_q_prod2sf, SG, SB, 0, q, qa);
+            else if (nt) hipLaunchKernelGGL((hz::k_q_prod2s<true>), SG, SB, 0, q, qa);
+            else hipLaunchKernelGGL((hz::k_q_prod2s<false>), SG, SB, 0, q, qa);
+        } else {
+            with_lanes(L, [&]<int LL, int UU>() {
+                if (fused) hipLaunchKernelGGL((hz::k_q_prod2<LL, UU, true>), G, B, 0, q, qa);
+                else hipLaunchKernelGGL((hz::k_q_prod2<LL, UU, false>), G, B, 0, q, qa);
+            });
+        }
+        if (!fused) hipLaunchKernelGGL(hz::k_q_dir2, G, B, 0, q, qa);
+        if (sliced) {
+            if (fused) hipLaunchKernelGGL(hz::k_q_prod4sf, SG, SB, 0, q, qa);
+            else if (nt) hipLaunchKernelGGL((hz::k_q_prod4s<true>), SG, SB, 0, q, qa);
+            else hipLaunchKernelGGL((hz::k_q_prod4s<false>), SG, SB, 0, q, qa);
+        } else {
+            with_lanes(L, [&]<int LL, int UU>() {
+                if (fused) hipLaunchKernelGGL((hz::k_q_prod4<LL, UU, true>), G, B, 0, q, qa);
+                else hipLaunchKernelGGL((hz::k_q_prod4<LL, UU, false>), G, B, 0, q, qa);
+            });
+        }
+    };
     if (*h->hflag < 1) {
         while (launched < maxiter) {
             const int k_n = (maxiter - launched) < poll ? (maxiter - launched) : poll;
-            rc = launch_chunk(h, s, chunk_key(fused ? 60 : 61, L, k_n, 0, qa), [&](hipStream_t q) {
-                with_lanes(L, [&]<int LL, int UU>() {
-                    for (int k = 0; k < k_n; ++k) {
-                        hipLaunchKernelGGL(hz::k_q_even, G, B, 0, q, qa);
-                        hipLaunchKernelGGL((hz::k_q_odd<LL, UU>), G, B, 0, q, qa);
-                        if (fused) {
-                            hipLaunchKernelGGL((hz::k_q_next<LL, UU>), G, B, 0, q, qa);
-                        } else {
-                            hipLaunchKernelGGL(hz::k_q_dir, G, B, 0, q, qa);
-                            hipLaunchKernelGGL((hz::k_q_next_light<LL, UU>), G, B, 0, q, qa);
-                        }
-                    }
-                });
+            rc = launch_chunk(h, s, chunk_key((fused ? 60 : 61) + (sliced ? 100 : 0), L, k_n, 0, qa), [&](hipStream_t q) {
+                for (int k = 0; k < k_n; ++k) iteration(q);
             });
             if (rc) return rc;
             launched += k_n;

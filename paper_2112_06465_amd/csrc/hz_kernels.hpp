@@ -757,48 +757,62 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 // partial of every component per thread, and all waves adding all components,
 // the eight sums of a head took the SIMDs about 1 us (7.3 us for the C-kernel of
 // 8,000 rows, 4.3 us with a wave per component).
+// V > 1: each wave does the work of V, so that a smaller block adds in the
+// order of one with V times its waves.
 constexpr int kHeadNV = 4;
 constexpr int head_waves(int K, int NW) { return 2 * K > NW ? 1 : 2 * head_waves(K, NW / 2); }
-template <int K, int NT = kBlock> struct PartSum {
-    static constexpr int W = head_waves(K, NT / kWave);
-    static_assert(K * W <= NT / kWave, "K W waves");
-    double v[kHeadNV];
+template <int K, int NT = kBlock, int V = 1> struct PartSum {
+    static constexpr int RW = head_waves(K, NT / kWave);  // waves per component,
+    static constexpr int W = RW * V;                      // and the shares they add
+    static_assert(K * RW <= NT / kWave, "K RW waves");
+    static constexpr int TOT = V * NT / kWave;  // totals in LDS
+    double v[V][kHeadNV];
     const double* part;
-    int cnt, g0;
+    int cnt, w0;
     // the component of this wave (a uniform value; K or more: none)
-    static __device__ __forceinline__ int comp() { return wave_id() / W; }
+    static __device__ __forceinline__ int comp() { return wave_id() / RW; }
     // p: the first partial of this wave's component, c >= 1 of them
     __device__ __forceinline__ void load(const double* __restrict__ p, int c) {
         part = p;
         cnt = c;
-        g0 = (wave_id() % W) * kWave;
+        w0 = wave_id() % RW * V;
         const int lane = threadIdx.x % kWave;
 #pragma unroll
-        for (int j = 0; j < kHeadNV; ++j) {
-            v[j] = 0.0;
-            const int r = g0 + j * W * kWave;
-            if (r < cnt) v[j] = p[r + lane < cnt ? r + lane : cnt - 1];  // uniform; masked in store()
-        }
+        for (int s = 0; s < V; ++s)
+#pragma unroll
+            for (int j = 0; j < kHeadNV; ++j) {
+                v[s][j] = 0.0;
+                const int r = (w0 + s + j * W) * kWave;
+                if (V > 1 || r < cnt) v[s][j] = p[r + lane < cnt ? r + lane : cnt - 1];  // uniform; masked in store()
+            }
     }
     __device__ __forceinline__ void store(double* tot) {
         const int lane = threadIdx.x % kWave;
-        double t = masked(0, lane);
+        double t[V];
+#pragma unroll
+        for (int s = 0; s < V; ++s) t[s] = masked(s, 0, lane);
         for (int g = kHeadNV * W * kWave; g < cnt; g += kHeadNV * W * kWave) {  // uniform
 #pragma unroll
-            for (int j = 0; j < kHeadNV; ++j) {
-                const int r = g + g0 + j * W * kWave;
-                if (r < cnt) v[j] = part[r + lane < cnt ? r + lane : cnt - 1];
+            for (int s = 0; s < V; ++s) {
+#pragma unroll
+                for (int j = 0; j < kHeadNV; ++j) {
+                    const int r = g + (w0 + s + j * W) * kWave;
+                    if (r < cnt) v[s][j] = part[r + lane < cnt ? r + lane : cnt - 1];
+                }
+                t[s] += masked(s, g, lane);
             }
-            t += masked(g, lane);
         }
-        t = wave_sum<1>(t);
-        if (lane == 0) tot[wave_id()] = t;
+#pragma unroll
+        for (int s = 0; s < V; ++s) t[s] = wave_sum<1>(t[s]);
+#pragma unroll
+        for (int s = 0; s < V; ++s)
+            if (lane == 0) tot[wave_id() * V + s] = t[s];
     }
-    // the sum of v, whose rounds start at partial g
-    __device__ __forceinline__ double masked(int g, int lane) const {
+    // the sum of v[s], whose rounds start at partial g
+    __device__ __forceinline__ double masked(int s, int g, int lane) const {
         double m[kHeadNV];
 #pragma unroll
-        for (int j = 0; j < kHeadNV; ++j) m[j] = g + g0 + j * W * kWave + lane < cnt ? v[j] : 0.0;
+        for (int j = 0; j < kHeadNV; ++j) m[j] = g + (w0 + s + j * W) * kWave + lane < cnt ? v[s][j] : 0.0;
         return (m[0] + m[1]) + (m[2] + m[3]);
     }
     static __device__ __forceinline__ double at(const double* tot, int k) {
@@ -808,6 +822,8 @@ template <int K, int NT = kBlock> struct PartSum {
         return t;
     }
 };
+// The shares per wave with which a head of NT threads adds in the order of one of kBlock.
+constexpr int head_shares(int K, int NT) { return head_waves(K, kBlock / kWave) / head_waves(K, NT / kWave); }
 
 // Sum of K components over one system's partials [gbeg, gbeg + gcnt), in a
 // fixed order, delivered to every thread of the block (component k at

@@ -3,36 +3,40 @@
 // one-system work map of the BiCGStab kernels, their device scalars
 // (SolverScal: rho, alpha, bnorm, rtol, status ...) and partial regions.
 //
-// Full iteration k (half steps m = 2k - 2, even, and m + 1, odd), three
+// Full iteration k (half steps m = 2k - 2, even, and m + 1, odd), four
 // launches:
-//   K1 (element-wise): alpha = rho / <r~, v>; u' = u - alpha v;
-//       w -= alpha A u; d = u + (theta_m^2 / alpha) eta_m d; partial ||w||^2
-//   K2 (product): theta, c, tau, eta of half step m + 1 from ||w||; the
-//       quasi-residual test (x += eta d and done when it passes); then
-//       A u' and, per row: x += eta d, w -= alpha A u',
-//       d = u' + (theta^2 / alpha) eta d; partials ||w||^2, <r~, w>
-//   K3 (product): the same scalars for half step m + 2 and its tests;
-//       beta = rho_new / rho; per gathered column u'' = w + beta u'
-//       (formed on the fly); per row: x += eta d, u = u'', Au = A u'',
-//       v = A u'' + beta (A u' + beta v); partial <r~, v>
-// Above about 10^5 rows K3 runs as two launches (k_q_dir, k_q_next_light) so
-// that its product gathers one vector, as the BiCGStab iteration does there.
-// tau, theta, eta of half step m live in slot m & 1 of the TFQMR scalars,
-// rho of iteration k in rho2[(k - 1) & 1]: a launch never reads a slot its
-// own leader writes.  K1 reads the iteration number `iter` and publishes it
-// as `cur`; K2 and K3 read `cur`, and K3 advances `iter`.  An exit found by
-// K2 or K3 still needs every block's share of the last x update, so it is
-// recorded (half_exit, end_exit) instead of ending the solve, and the next K1
-// (or k_q_conclude after the last chunk) concludes it: a block that has not
+//   K1 (element-wise): alpha = rho / <r~, v>; u' = u - alpha v
+//   K2 (product): A u' and, per row: w1 = w - alpha A u, w = w1 - alpha A u';
+//       partials ||w1||^2, ||w||^2, <r~, w>
+//   K3 (element-wise): theta, c, tau, eta of both half steps from ||w1||^2
+//       and ||w||^2 and their quasi-residual tests; beta = rho_new / rho;
+//       d1 = u + (theta_m^2 / alpha) eta_m d; x += eta d1;
+//       d = u' + (theta^2 / alpha) eta d1;    x += eta d;   u = w + beta u'
+//   K4 (product): Au = A u, v = A u + beta (A u' + beta v); partial <r~, v>
+// Nothing of the first half step but ||w1||^2 is needed before the second, so
+// its vector work waits for K3: 23 vector passes, where K1 and K2 each
+// finishing their own half step took 29 and a head in the product.  On small
+// systems K1 runs in K2 and K3 in K4, which then gather two vectors and form
+// u' or u of a column on the fly (choose_fused); the same arithmetic per
+// element.  Measured on the 210k-row cylinder with Jacobi (sliced operator):
+// 49.3 -> 40.2 us an iteration.
+// tau, theta, eta of the end of iteration k live in slot k & 1 of the TFQMR
+// scalars, rho of iteration k in rho2[(k - 1) & 1]: a launch never reads a
+// slot its own leader writes.  K1 reads the iteration number `iter` and
+// publishes it as `cur`; K3 reads `cur` and advances `iter`.  An exit found by
+// K3 still needs every block's share of the last x updates, so it is recorded
+// (half_exit, end_exit) instead of ending the solve, and the next K1 (or
+// k_q_conclude after the last chunk) concludes it: a block that has not
 // started when the leader writes the record must still do its rows.
 #pragma once
 
 #include "hz_kernels.hpp"
+#include "hz_slices.hpp"
 
 namespace hz {
 
 struct TScal {
-    double tau[2], theta[2];  // per half-step parity
+    double tau[2], theta[2];  // per parity of the iteration
     double2 eta[2];
     int half_exit;  // iteration whose first half step converged (0: none)
     int end_exit;   // iteration that ended at its second half step (0: none)
@@ -46,9 +50,11 @@ struct QArgs {
     const int* __restrict__ row_ptr;
     const int* __restrict__ col_idx;
     const double2* __restrict__ vals;
+    const int* __restrict__ soff;  // the sliced operator's offsets and columns, or null
+    const short* __restrict__ scol;
     const double2* rt;  // shadow residual r~
     double2* w;
-    double2* u;    // u of the even half step (u'' after K3)
+    double2* u;    // u of the even half step
     double2* u1;   // u' = u - alpha v
     double2* au;   // A u
     double2* au1;  // A u'
@@ -58,6 +64,8 @@ struct QArgs {
     double* part;
     SolverScal* sc;
     TScal* tq;
+    int np;  // blocks and partial slots of the products
+    int spare;
 };
 
 __device__ __forceinline__ SysBlock qblock(const QArgs& a) {
@@ -117,268 +125,444 @@ __global__ void k_q_conclude(const QArgs a) {
     q_conclude(a, threadIdx.x == 0);
 }
 
-// A u_0 = A r_0: u = w = r_0, v = Au = A r_0, d = 0; partial <r~, v>
+// Head of K1, and of K2 where it contains K1: alpha.  run() returns false when
+// the solve has ended (every block returns); the leader records it.  Scalars
+// in the first wave only, as in the BiCGStab heads.
+template <int NT = kBlock> struct QAlpha {
+    PartSum<2, NT, head_shares(2, NT)> ps;  // (both forms add in one order)
+    int done, it;
+    double2 rho;
+
+    __device__ __forceinline__ void load(const QArgs& a) {
+        done = a.sc->done;
+        it = a.sc->iter;
+        const double2 r0 = a.sc->rho2[0], r1 = a.sc->rho2[1];
+        rho = (it & 1) ? r0 : r1;
+        if (ps.comp() < 2) ps.load(a.part + (kPartA + ps.comp()) * a.stride, a.np);
+    }
+    __device__ __forceinline__ bool run(const QArgs& a, bool leader, double2& alpha) {
+        __shared__ double tot[decltype(ps)::TOT];
+        __shared__ double2 al;
+        __shared__ int go;
+        if (ps.comp() < 2) ps.store(tot);
+        __syncthreads();
+        if (wave_id() == 0) {
+            double2 c = mk<double>(0.0, 0.0);
+            const int g = decide(a, leader, mk<double>(ps.at(tot, 0), ps.at(tot, 1)), c);
+            if (threadIdx.x == 0) {
+                al = c;
+                go = g;
+            }
+        }
+        __syncthreads();
+        alpha = al;
+        return go != 0;
+    }
+    __device__ __forceinline__ int decide(const QArgs& a, bool leader, double2 sigma, double2& alpha) {
+        if (done || q_conclude(a, leader)) return 0;
+        int st = -1, why = BD_NONE;
+        if (!zfinite(sigma) || !zfinite(rho)) st = ST_NONFINITE;
+        else if (zzero(sigma)) st = ST_BREAKDOWN, why = BD_RHAT_V;
+        else if (zzero(rho)) st = ST_BREAKDOWN, why = BD_RHO;
+        else {
+            alpha = zdiv(rho, sigma);
+            if (!zfinite(alpha)) st = ST_NONFINITE;
+        }
+        if (leader) {
+            if (st >= 0) {
+                finish(a.sc, a.ndone, st, it - 1, why);
+            } else {
+                a.sc->alpha = alpha;
+                a.sc->cur = it;
+            }
+        }
+        return st < 0;
+    }
+};
+
+// K1: u' = u - alpha v
+__global__ HZ_STREAM_BOUNDS void k_q_dir1(const QArgs a) {
+    const SysBlock q = qblock(a);
+    QAlpha<> hd;
+    hd.load(a);
+    int64_t i = q.rw.x0 + (int64_t)q.rw.k * kBlock + threadIdx.x;
+    const int64_t step = (int64_t)q.rw.K * kBlock;
+    double2 u0 = mk<double>(0.0, 0.0), v0 = u0;
+    if (i < q.rw.x1) {
+        u0 = a.u[i];
+        v0 = a.v[i];
+    }
+    double2 alpha;
+    if (!hd.run(a, sys_leader(q), alpha)) return;
+    const double2 na = mk<double>(-alpha.x, -alpha.y);
+    while (i < q.rw.x1) {
+        const int64_t at = i;
+        const double2 d = cfma<double>(na, v0, u0);
+        i += step;
+        if (i < q.rw.x1) {
+            u0 = a.u[i];
+            v0 = a.v[i];
+        }
+        a.u1[at] = d;
+    }
+}
+
+// Scalars of K3, and what an element needs of them.
+enum : int { Q_STOP = 0, Q_HALF = 1, Q_LAST1 = 2, Q_LAST = 3, Q_FULL = 4 };  // HALF: to d1; LAST1: x of d1 only; LAST: both
+struct QCoef {
+    double2 dc0, eta1, dc1, eta2, beta;
+    int mode, spare;
+};
+template <int NT = kBlock> struct QEnd {
+    PartSum<4, NT, head_shares(4, NT)> ps;
+    int done, it, maxit;
+    double bnorm, rtol, tau0, theta0;
+    double2 alpha, rho_old, eta0;
+
+    __device__ __forceinline__ void load(const QArgs& a) {
+        const SolverScal* sc = a.sc;
+        done = sc->done;
+        it = sc->cur;
+        maxit = sc->maxiter;
+        bnorm = sc->bnorm;
+        rtol = sc->rtol;
+        alpha = sc->alpha;
+        if (ps.comp() < 4) ps.load(a.part + (kPartB + ps.comp()) * a.stride, a.np);
+        const double2 r0 = sc->rho2[0], r1 = sc->rho2[1];
+        rho_old = (it & 1) ? r0 : r1;
+        const TScal* t = a.tq;
+        const bool odd = (it & 1) != 0;  // iteration k reads the slot (k - 1) & 1
+        tau0 = odd ? t->tau[0] : t->tau[1];
+        theta0 = odd ? t->theta[0] : t->theta[1];
+        eta0 = odd ? t->eta[0] : t->eta[1];
+    }
+    __device__ __forceinline__ const QCoef& run(const QArgs& a, bool leader) {
+        __shared__ double tot[decltype(ps)::TOT];
+        __shared__ QCoef cf;
+        if (ps.comp() < 4) ps.store(tot);
+        __syncthreads();
+        if (wave_id() == 0) {
+            QCoef c;
+            c.mode = decide(a, leader, ps.at(tot, 0), ps.at(tot, 1), mk<double>(ps.at(tot, 2), ps.at(tot, 3)), c);
+            if (threadIdx.x == 0) cf = c;
+        }
+        __syncthreads();
+        return cf;
+    }
+    __device__ __forceinline__ int decide(const QArgs& a, bool leader, double ww1, double ww2, double2 rho_new,
+                                          QCoef& c) {
+        c.dc0 = c.eta1 = c.dc1 = c.eta2 = c.beta = mk<double>(0.0, 0.0);
+        c.spare = 0;
+        if (done) return Q_STOP;
+        SolverScal* sc = a.sc;
+        const QStep s1 = q_step(ww1, tau0, alpha);
+        const int m1 = 2 * it - 1;  // the first half step's index + 1 (m + 1 with m = 2 it - 2)
+        const double bound1 = __builtin_sqrt((double)(m1 + 1)) * s1.tau / bnorm;
+        if (!__builtin_isfinite(bound1)) {  // no block writes x: ending at once is safe
+            if (leader) finish(sc, a.ndone, ST_NONFINITE, it);
+            return Q_STOP;
+        }
+        c.dc0 = q_dcoef(theta0, eta0, alpha);
+        c.eta1 = s1.eta;
+        if (bound1 <= rtol) {  // x_{m+1} = x_m + eta d solves: apply, and record a half-step exit
+            if (leader) {
+                sc->relres = bound1;
+                a.tq->half_exit = it;
+            }
+            return Q_HALF;
+        }
+        const QStep s2 = q_step(ww2, s1.tau, alpha);
+        c.dc1 = q_dcoef(s1.theta, s1.eta, alpha);
+        c.eta2 = s2.eta;
+        const int m2 = 2 * it;  // half step index + 1 of the iterate this launch completes
+        const double bound = __builtin_sqrt((double)(m2 + 1)) * s2.tau / bnorm;
+        int st = -1, why = BD_NONE;
+        if (!__builtin_isfinite(bound) || !zfinite(rho_new)) st = ST_NONFINITE;
+        else if (bound <= rtol) st = ST_OK;
+        else if (it >= maxit) st = ST_NOT_CONVERGED;
+        else if (zzero(rho_old)) st = ST_BREAKDOWN, why = BD_RHO;
+        else {
+            c.beta = zdiv(rho_new, rho_old);
+            if (!zfinite(c.beta)) st = ST_NONFINITE;
+        }
+        if (leader) {
+            sc->relres = bound;
+            if (st >= 0) {  // the next K1 ends the solve
+                a.tq->end_status = st;
+                a.tq->end_why = why;
+                a.tq->end_exit = it;
+            } else {
+                a.tq->tau[it & 1] = s2.tau;
+                a.tq->theta[it & 1] = s2.theta;
+                a.tq->eta[it & 1] = s2.eta;
+                sc->rho2[it & 1] = rho_new;
+                sc->beta = c.beta;
+                sc->iter = it + 1;
+                sc->iters = it;
+            }
+        }
+        if (st < 0) return Q_FULL;
+        return st == ST_NONFINITE ? Q_LAST1 : Q_LAST;  // x_{m+2} = x_{m+1} + eta d is the last iterate
+    }
+};
+// The x and d updates of an element.
+__device__ __forceinline__ void q_update(const QCoef& c, double2 u, double2 u1, double2& d, double2& x) {
+    d = cfma<double>(c.dc0, d, u);
+    x = cfma<double>(c.eta1, d, x);
+    if (c.mode < Q_LAST) return;
+    d = cfma<double>(c.dc1, d, u1);
+    x = cfma<double>(c.eta2, d, x);
+}
+// The last x of a solve that ends.
+__device__ __forceinline__ void q_last(const QArgs& a, const QCoef& c, int64_t i0, int64_t step, int64_t end) {
+    for (int64_t i = i0; i < end; i += step) {
+        double2 d = a.d[i], x = a.x[i];
+        q_update(c, a.u[i], a.u1[i], d, x);
+        a.x[i] = x;
+    }
+}
+
+// K3: x, d and u = w + beta u'
+__global__ HZ_STREAM_BOUNDS void k_q_dir2(const QArgs a) {
+    const SysBlock q = qblock(a);
+    QEnd<> hd;
+    hd.load(a);
+    // the first element's d, x and u are in flight during the head (all five: 16 of 64 registers spilled)
+    const int i0 = (int)q.rw.x0 + q.rw.k * kBlock + threadIdx.x, step = q.rw.K * kBlock, end = (int)q.rw.x1;
+    double2 d = mk<double>(0.0, 0.0), x = d, u = d;
+    if (i0 < end) {
+        d = a.d[i0];
+        x = a.x[i0];
+        u = a.u[i0];
+    }
+    const QCoef& c = hd.run(a, sys_leader(q));
+    if (c.mode == Q_STOP) return;
+    if (c.mode != Q_FULL) return q_last(a, c, i0, step, end);
+    for (int i = i0; i < end;) {
+        const int j = i;
+        const double2 u1 = a.u1[j], w = a.w[j];
+        double2 dn = d, xn = x;
+        q_update(c, u, u1, dn, xn);
+        i = i < end - step ? i + step : end;
+        if (i < end) {
+            d = a.d[i];
+            x = a.x[i];
+            u = a.u[i];
+        }
+        a.x[j] = xn;
+        a.d[j] = dn;
+        a.u[j] = cfma<double>(c.beta, u1, w);
+    }
+}
+
+// The products.  A row's part of K2: w, A u'; sums ||w1||^2, ||w||^2, <r~, w>
+struct QRow2 {
+    double2 w, au, rt;
+};
+__device__ __forceinline__ QRow2 q_row2(const QArgs& a, int64_t row) { return QRow2{a.w[row], a.au[row], a.rt[row]}; }
+__device__ __forceinline__ void q_end2(const QArgs& a, int64_t row, double2 na, double2 acc, const QRow2& p,
+                                       double (&e)[4]) {
+    const double2 w1 = cfma<double>(na, p.au, p.w);
+    const double2 w = cfma<double>(na, acc, w1);
+    a.w[row] = w;
+    a.au1[row] = acc;
+    e[0] = __builtin_fma(w1.x, w1.x, e[0]);
+    e[0] = __builtin_fma(w1.y, w1.y, e[0]);
+    e[1] = __builtin_fma(w.x, w.x, e[1]);
+    e[1] = __builtin_fma(w.y, w.y, e[1]);
+    const double2 c = cdotacc(p.rt.x, p.rt.y, w.x, w.y, mk<double>(e[2], e[3]));
+    e[2] = c.x;
+    e[3] = c.y;
+}
+// A row's part of K4: A u and v; sum <r~, v>
+struct QRow4 {
+    double2 v, au1, rt;
+};
+__device__ __forceinline__ QRow4 q_row4(const QArgs& a, int64_t row) { return QRow4{a.v[row], a.au1[row], a.rt[row]}; }
+__device__ __forceinline__ void q_end4(const QArgs& a, int64_t row, double2 beta, double2 acc, const QRow4& p,
+                                       double (&e)[2]) {
+    a.au[row] = acc;
+    const double2 inner = cfma<double>(beta, p.v, p.au1);  // A u' + beta v
+    const double2 vv = cfma<double>(beta, inner, acc);
+    a.v[row] = vv;
+    const double2 c = cdotacc(p.rt.x, p.rt.y, vv.x, vv.y, mk<double>(e[0], e[1]));
+    e[0] = c.x;
+    e[1] = c.y;
+}
+// A row's part of the set-up: u = w = r_0, v = Au = A r_0, d = 0; sum <r~, v>
+__device__ __forceinline__ void q_end0(const QArgs& a, int64_t row, double2 r0, double2 acc, double (&e)[2]) {
+    a.u[row] = r0;
+    a.w[row] = r0;
+    a.au[row] = acc;
+    a.v[row] = acc;
+    a.d[row] = mk<double>(0.0, 0.0);
+    const double2 t = a.rt[row];
+    const double2 c = cdotacc(t.x, t.y, acc.x, acc.y, mk<double>(e[0], e[1]));
+    e[0] = c.x;
+    e[1] = c.y;
+}
+
+// On the CSR operator.
 template <int L, int U>
 __global__ HZ_STREAM_BOUNDS void k_q_init(const QArgs a, const double2* __restrict__ r0) {
     const SysBlock q = qblock(a);
-    if (q.sys < 0) return;
     double e[2] = {0.0, 0.0};
     for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, [r0](int c) { return r0[c]; },
-                           [&](int64_t row, double2 acc) {
-                               const double2 rv = r0[row];
-                               a.u[row] = rv;
-                               a.w[row] = rv;
-                               a.au[row] = acc;
-                               a.v[row] = acc;
-                               a.d[row] = mk<double>(0.0, 0.0);
-                               const double2 t = a.rt[row];
-                               const double2 c = cdotacc(t.x, t.y, acc.x, acc.y, mk<double>(e[0], e[1]));
-                               e[0] = c.x;
-                               e[1] = c.y;
-                           });
+                           [&](int64_t row, double2 acc) { q_end0(a, row, r0[row], acc, e); });
     store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
-// K1: the even half step's vector work
-__global__ HZ_STREAM_BOUNDS void k_q_even(const QArgs a) {
+template <int L, int U, bool FUSED>
+__global__ HZ_STREAM_BOUNDS void k_q_prod2(const QArgs a) {
     const SysBlock q = qblock(a);
-    if (q.sys < 0) return;
-    SolverScal* sc = a.sc;
-    if (sc->done || q_conclude(a, sys_leader(q))) return;
-    double h[2];
-    sys_sum<2>(a.part + kPartA * a.stride, a.stride, q.gbeg, q.gcnt, h);
-    const double2 sigma = mk<double>(h[0], h[1]);
-    // the scalars are read after the reduction: held across it they spilled under the 64-register cap
-    const int it = sc->iter;
-    const double2 rho = sc->rho2[(it - 1) & 1];
-    const double theta = a.tq->theta[0];
-    const double2 eta = a.tq->eta[0];
-    int st = -1, why = BD_NONE;
-    double2 alpha = mk<double>(0.0, 0.0);
-    if (!zfinite(sigma) || !zfinite(rho)) st = ST_NONFINITE;
-    else if (zzero(sigma)) st = ST_BREAKDOWN, why = BD_RHAT_V;
-    else if (zzero(rho)) st = ST_BREAKDOWN, why = BD_RHO;
-    else {
-        alpha = zdiv(rho, sigma);
-        if (!zfinite(alpha)) st = ST_NONFINITE;
+    double2 alpha;
+    if constexpr (FUSED) {
+        QAlpha<> hd;
+        hd.load(a);
+        if (!hd.run(a, sys_leader(q), alpha)) return;
+    } else {
+        if (a.sc->done) return;
+        alpha = a.sc->alpha;
     }
-    if (st >= 0) {
-        if (sys_leader(q)) finish(sc, a.ndone, st, it - 1, why);
-        return;
-    }
-    if (sys_leader(q)) {
-        sc->alpha = alpha;
-        sc->cur = it;
-    }
-    const double2 dc = q_dcoef(theta, eta, alpha), na = mk<double>(-alpha.x, -alpha.y);
-    double e[1] = {0.0};
-    HZ_FOR_ELEMS(i, q.rw) {
-        const double2 uv = a.u[i];
-        a.u1[i] = cfma<double>(na, a.v[i], uv);
-        const double2 wv = cfma<double>(na, a.au[i], a.w[i]);
-        a.w[i] = wv;
-        a.d[i] = cfma<double>(dc, a.d[i], uv);
-        e[0] = __builtin_fma(wv.x, wv.x, e[0]);
-        e[0] = __builtin_fma(wv.y, wv.y, e[0]);
-    }
-    store_sys_partials<1>(a.part + kPartB * a.stride, a.stride, q.lb, e);
-}
-
-// K2: the odd half step
-template <int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_q_odd(const QArgs a) {
-    const SysBlock q = qblock(a);
-    if (q.sys < 0) return;
-    SolverScal* sc = a.sc;
-    if (sc->done) return;
-    const int it = sc->cur;
-    const double bnorm = sc->bnorm, rtol = sc->rtol, tau0 = a.tq->tau[0];
-    const double2 alpha = sc->alpha;
-    double h[1];
-    sys_sum<1>(a.part + kPartB * a.stride, a.stride, q.gbeg, q.gcnt, h);
-    const QStep s1 = q_step(h[0], tau0, alpha);
-    const int m1 = 2 * it - 1;  // this half step's index + 1 (m + 1 with m = 2 it - 2)
-    const double bound = __builtin_sqrt((double)(m1 + 1)) * s1.tau / bnorm;
-    if (!__builtin_isfinite(bound)) {  // no block writes x: ending at once is safe
-        if (sys_leader(q)) finish(sc, a.ndone, ST_NONFINITE, it);
-        return;
-    }
-    if (bound <= rtol) {  // x_{m+1} = x_m + eta d solves: apply, and record a half-step exit
-        HZ_FOR_ELEMS(i, q.rw) a.x[i] = cfma<double>(s1.eta, a.d[i], a.x[i]);
-        if (sys_leader(q)) {
-            sc->relres = bound;
-            a.tq->half_exit = it;
-        }
-        return;
-    }
-    if (sys_leader(q)) {
-        a.tq->tau[1] = s1.tau;
-        a.tq->theta[1] = s1.theta;
-        a.tq->eta[1] = s1.eta;
-        sc->relres = bound;
-    }
-    const double2 dc = q_dcoef(s1.theta, s1.eta, alpha), na = mk<double>(-alpha.x, -alpha.y);
+    const double2 na = mk<double>(-alpha.x, -alpha.y);
+    const double2* __restrict__ u = a.u;
+    const double2* __restrict__ v = a.v;
     const double2* __restrict__ u1 = a.u1;
-    double e[3] = {0.0, 0.0, 0.0};
-    for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, [u1](int c) { return u1[c]; },
-                           [&](int64_t row, double2 acc) {
-                               double2 dv = a.d[row];
-                               a.x[row] = cfma<double>(s1.eta, dv, a.x[row]);
-                               const double2 wv = cfma<double>(na, acc, a.w[row]);
-                               a.w[row] = wv;
-                               a.d[row] = cfma<double>(dc, dv, u1[row]);
-                               a.au1[row] = acc;
-                               e[0] = __builtin_fma(wv.x, wv.x, e[0]);
-                               e[0] = __builtin_fma(wv.y, wv.y, e[0]);
-                               const double2 t = a.rt[row];
-                               const double2 c = cdotacc(t.x, t.y, wv.x, wv.y, mk<double>(e[1], e[2]));
-                               e[1] = c.x;
-                               e[2] = c.y;
-                           });
-    store_sys_partials<3, epi_stride(L)>(a.part + kPartC * a.stride, a.stride, q.lb, e);
-}
-
-// K3: the end of the odd half step and the next even step's directions
-template <int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_q_next(const QArgs a) {
-    const SysBlock q = qblock(a);
-    if (q.sys < 0) return;
-    SolverScal* sc = a.sc;
-    if (sc->done || a.tq->half_exit) return;
-    const int it = sc->cur;
-    const double bnorm = sc->bnorm, rtol = sc->rtol, tau1 = a.tq->tau[1];
-    const int maxit = sc->maxiter;
-    const double2 alpha = sc->alpha, rho_old = sc->rho2[(it - 1) & 1];
-    double h[3];
-    sys_sum<3>(a.part + kPartC * a.stride, a.stride, q.gbeg, q.gcnt, h);
-    const QStep s2 = q_step(h[0], tau1, alpha);
-    const double2 rho_new = mk<double>(h[1], h[2]);
-    const int m2 = 2 * it;  // half step index + 1 of the iterate this launch completes
-    const double bound = __builtin_sqrt((double)(m2 + 1)) * s2.tau / bnorm;
-    int st = -1, why = BD_NONE;
-    double2 beta = mk<double>(0.0, 0.0);
-    if (!__builtin_isfinite(bound) || !zfinite(rho_new)) st = ST_NONFINITE;
-    else if (bound <= rtol) st = ST_OK;
-    else if (it >= maxit) st = ST_NOT_CONVERGED;
-    else if (zzero(rho_old)) st = ST_BREAKDOWN, why = BD_RHO;
-    else {
-        beta = zdiv(rho_new, rho_old);
-        if (!zfinite(beta)) st = ST_NONFINITE;
-    }
-    if (st >= 0) {  // x_{m+2} = x_{m+1} + eta d is the last iterate; the next K1 ends the solve
-        if (st != ST_NONFINITE) HZ_FOR_ELEMS(i, q.rw) a.x[i] = cfma<double>(s2.eta, a.d[i], a.x[i]);
-        if (sys_leader(q)) {
-            sc->relres = bound;
-            a.tq->end_status = st;
-            a.tq->end_why = why;
-            a.tq->end_exit = it;
-        }
-        return;
-    }
-    if (sys_leader(q)) {
-        a.tq->tau[0] = s2.tau;
-        a.tq->theta[0] = s2.theta;
-        a.tq->eta[0] = s2.eta;
-        sc->rho2[it & 1] = rho_new;
-        sc->relres = bound;
-        sc->iter = it + 1;
-        sc->iters = it;
-    }
-    const double2* __restrict__ w = a.w;
-    const double2* __restrict__ u1 = a.u1;
-    auto ucol = [w, u1, beta](int c) { return cfma<double>(beta, u1[c], w[c]); };
-    double e[2] = {0.0, 0.0};
-    for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, ucol, [&](int64_t row, double2 acc) {
-        a.x[row] = cfma<double>(s2.eta, a.d[row], a.x[row]);
-        a.u[row] = ucol((int)row);
-        a.au[row] = acc;
-        const double2 inner = cfma<double>(beta, a.v[row], a.au1[row]);  // A u' + beta v
-        const double2 vv = cfma<double>(beta, inner, acc);
-        a.v[row] = vv;
-        const double2 t = a.rt[row];
-        const double2 c = cdotacc(t.x, t.y, vv.x, vv.y, mk<double>(e[0], e[1]));
-        e[0] = c.x;
-        e[1] = c.y;
+    auto col = [=](int c) {
+        if constexpr (FUSED) return cfma<double>(na, v[c], u[c]);
+        else return u1[c];
+    };
+    double e[4] = {0.0, 0.0, 0.0, 0.0};
+    for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, col, [&](int64_t row, double2 acc) {
+        if constexpr (FUSED) a.u1[row] = col((int)row);
+        q_end2(a, row, na, acc, q_row2(a, row), e);
     });
-    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    store_sys_partials<4, epi_stride(L)>(a.part + kPartB * a.stride, a.stride, q.lb, e);
 }
 
-// Gather-light form of K3 for large systems (two launches instead of one,
-// one gathered vector instead of two): K3a takes the scalars, tests and exit
-// records of K3 and forms u'' = w + beta u' and x += eta d element-wise;
-// K3b gathers u'' alone for A u'' and updates Au, v and the <r~, v>
-// partials.  Same arithmetic per element as K3.
-__global__ HZ_STREAM_BOUNDS void k_q_dir(const QArgs a) {
+template <int L, int U, bool FUSED>
+__global__ HZ_STREAM_BOUNDS void k_q_prod4(const QArgs a) {
     const SysBlock q = qblock(a);
-    if (q.sys < 0) return;
-    SolverScal* sc = a.sc;
-    if (sc->done || a.tq->half_exit) return;
-    const int it = sc->cur;
-    const double bnorm = sc->bnorm, rtol = sc->rtol, tau1 = a.tq->tau[1];
-    const int maxit = sc->maxiter;
-    const double2 alpha = sc->alpha, rho_old = sc->rho2[(it - 1) & 1];
-    double h[3];
-    sys_sum<3>(a.part + kPartC * a.stride, a.stride, q.gbeg, q.gcnt, h);
-    const QStep s2 = q_step(h[0], tau1, alpha);
-    const double2 rho_new = mk<double>(h[1], h[2]);
-    const double bound = __builtin_sqrt((double)(2 * it + 1)) * s2.tau / bnorm;
-    int st = -1, why = BD_NONE;
-    double2 beta = mk<double>(0.0, 0.0);
-    if (!__builtin_isfinite(bound) || !zfinite(rho_new)) st = ST_NONFINITE;
-    else if (bound <= rtol) st = ST_OK;
-    else if (it >= maxit) st = ST_NOT_CONVERGED;
-    else if (zzero(rho_old)) st = ST_BREAKDOWN, why = BD_RHO;
-    else {
-        beta = zdiv(rho_new, rho_old);
-        if (!zfinite(beta)) st = ST_NONFINITE;
-    }
-    if (st >= 0) {
-        if (st != ST_NONFINITE) HZ_FOR_ELEMS(i, q.rw) a.x[i] = cfma<double>(s2.eta, a.d[i], a.x[i]);
-        if (sys_leader(q)) {
-            sc->relres = bound;
-            a.tq->end_status = st;
-            a.tq->end_why = why;
-            a.tq->end_exit = it;
-        }
-        return;
-    }
-    if (sys_leader(q)) {
-        a.tq->tau[0] = s2.tau;
-        a.tq->theta[0] = s2.theta;
-        a.tq->eta[0] = s2.eta;
-        sc->rho2[it & 1] = rho_new;
-        sc->beta = beta;
-        sc->relres = bound;
-        sc->iter = it + 1;
-        sc->iters = it;
-    }
-    HZ_FOR_ELEMS(i, q.rw) {
-        a.x[i] = cfma<double>(s2.eta, a.d[i], a.x[i]);
-        a.u[i] = cfma<double>(beta, a.u1[i], a.w[i]);
+    if constexpr (FUSED) {
+        QEnd<> hd;
+        hd.load(a);
+        const QCoef& c = hd.run(a, sys_leader(q));
+        if (c.mode == Q_STOP) return;
+        if (c.mode != Q_FULL)
+            return q_last(a, c, q.rw.x0 + (int64_t)q.rw.k * kBlock + threadIdx.x, (int64_t)q.rw.K * kBlock, q.rw.x1);
+        const double2 beta = c.beta;
+        const double2* __restrict__ w = a.w;
+        const double2* __restrict__ u1 = a.u1;
+        auto col = [=](int k) { return cfma<double>(beta, u1[k], w[k]); };
+        double e[2] = {0.0, 0.0};
+        for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, col, [&](int64_t row, double2 acc) {
+            double2 d = a.d[row], x = a.x[row];
+            q_update(c, a.u[row], u1[row], d, x);
+            a.x[row] = x;
+            a.d[row] = d;
+            a.u[row] = col((int)row);
+            q_end4(a, row, beta, acc, q_row4(a, row), e);
+        });
+        store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    } else {
+        if (a.sc->done || a.tq->half_exit || a.tq->end_exit) return;
+        const double2 beta = a.sc->beta;
+        const double2* __restrict__ u = a.u;
+        double e[2] = {0.0, 0.0};
+        for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, [u](int c) { return u[c]; },
+                               [&](int64_t row, double2 acc) { q_end4(a, row, beta, acc, q_row4(a, row), e); });
+        store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
     }
 }
 
-template <int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_q_next_light(const QArgs a) {
-    const SysBlock q = qblock(a);
-    if (q.sys < 0) return;
-    SolverScal* sc = a.sc;
-    if (sc->done || a.tq->half_exit || a.tq->end_exit) return;
-    const double2 beta = sc->beta;
+// On the sliced operator.  (The fused ones without a register limit, as
+// BiCGStab's.)
+__device__ __forceinline__ Sliced<double> sliced_of(const QArgs& a) { return Sliced<double>{a.soff, a.scol, a.vals}; }
+__device__ __forceinline__ bool slice_leader(const SliceRows& q) { return q.lb == 0 && threadIdx.x == 0; }
+
+__global__ HZ_SLICE_BOUNDS void k_q_inits(const QArgs a, const double2* __restrict__ r0) {
+    const SliceRows q = slice_rows_of(a.one, a.np);
+    double e[2] = {0.0, 0.0};
+    slice_rows<double, false>(
+        sliced_of(a), q, first_slice(sliced_of(a), q), a.one.n, [r0](int c) { return r0[c]; }, [](int) { return 0; },
+        [&](int64_t row, double2 acc, double2 self, int) { q_end0(a, row, self, acc, e); });
+    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+}
+
+template <bool NT>
+__global__ HZ_SLICE_BOUNDS void k_q_prod2s(const QArgs a) {
+    const SliceRows q = slice_rows_of(a.one, a.np);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    if (a.sc->done) return;
+    const double2 alpha = a.sc->alpha, na = mk<double>(-alpha.x, -alpha.y);
+    const double2* __restrict__ u1 = a.u1;
+    double e[4] = {0.0, 0.0, 0.0, 0.0};
+    slice_rows<double, NT>(
+        sliced_of(a), q, f, a.one.n, [u1](int c) { return u1[c]; }, [&a](int row) { return q_row2(a, row); },
+        [&](int64_t row, double2 acc, double2, const QRow2& p) { q_end2(a, row, na, acc, p, e); });
+    slice_store<4>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+}
+
+__global__ __launch_bounds__(kSlBlock) void k_q_prod2sf(const QArgs a) {
+    const SliceRows q = slice_rows_of(a.one, a.np);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    QAlpha<kSlBlock> hd;
+    hd.load(a);
+    double2 alpha;
+    if (!hd.run(a, slice_leader(q), alpha)) return;
+    const double2 na = mk<double>(-alpha.x, -alpha.y);
+    const double2* __restrict__ u = a.u;
+    const double2* __restrict__ v = a.v;
+    double e[4] = {0.0, 0.0, 0.0, 0.0};
+    slice_rows<double, false>(
+        sliced_of(a), q, f, a.one.n, [=](int c) { return cfma<double>(na, v[c], u[c]); },
+        [&a](int row) { return q_row2(a, row); },
+        [&](int64_t row, double2 acc, double2 self, const QRow2& p) {
+            a.u1[row] = self;
+            q_end2(a, row, na, acc, p, e);
+        });
+    slice_store<4>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+}
+
+template <bool NT>
+__global__ HZ_SLICE_BOUNDS void k_q_prod4s(const QArgs a) {
+    const SliceRows q = slice_rows_of(a.one, a.np);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    if (a.sc->done || a.tq->half_exit || a.tq->end_exit) return;
+    const double2 beta = a.sc->beta;
     const double2* __restrict__ u = a.u;
     double e[2] = {0.0, 0.0};
-    for_rows<double, L, U>(q.rw, a.row_ptr, a.col_idx, a.vals, [u](int c) { return u[c]; },
-                           [&](int64_t row, double2 acc) {
-                               a.au[row] = acc;
-                               const double2 inner = cfma<double>(beta, a.v[row], a.au1[row]);
-                               const double2 vv = cfma<double>(beta, inner, acc);
-                               a.v[row] = vv;
-                               const double2 t = a.rt[row];
-                               const double2 c = cdotacc(t.x, t.y, vv.x, vv.y, mk<double>(e[0], e[1]));
-                               e[0] = c.x;
-                               e[1] = c.y;
-                           });
-    store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+    slice_rows<double, NT>(
+        sliced_of(a), q, f, a.one.n, [u](int c) { return u[c]; }, [&a](int row) { return q_row4(a, row); },
+        [&](int64_t row, double2 acc, double2, const QRow4& p) { q_end4(a, row, beta, acc, p, e); });
+    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+}
+
+__global__ __launch_bounds__(kSlBlock) void k_q_prod4sf(const QArgs a) {
+    const SliceRows q = slice_rows_of(a.one, a.np);
+    const FirstSlice f = first_slice(sliced_of(a), q);
+    QEnd<kSlBlock> hd;
+    hd.load(a);
+    const QCoef& c = hd.run(a, slice_leader(q));
+    if (c.mode == Q_STOP) return;
+    if (c.mode != Q_FULL)  // its rows are those of the grid's stride
+        return q_last(a, c, (int64_t)blockIdx.x * kSlBlock + threadIdx.x, (int64_t)a.np * kSlBlock, a.one.n);
+    const double2 beta = c.beta;
+    const double2* __restrict__ w = a.w;
+    const double2* __restrict__ u1 = a.u1;
+    double e[2] = {0.0, 0.0};
+    slice_rows<double, false>(
+        sliced_of(a), q, f, a.one.n, [=](int k) { return cfma<double>(beta, u1[k], w[k]); },
+        [&a](int row) { return q_row4(a, row); },
+        [&](int64_t row, double2 acc, double2 self, const QRow4& p) {
+            double2 d = a.d[row], x = a.x[row];
+            q_update(c, a.u[row], u1[row], d, x);
+            a.x[row] = x;
+            a.d[row] = d;
+            a.u[row] = self;
+            q_end4(a, row, beta, acc, p, e);
+        });
+    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
 }
 
 }  // namespace hz
