@@ -257,9 +257,9 @@ SpPlan pick_sp(const hz_handle* h, const int* rp, const int* ci, int n, int64_t 
 
 // Blocks of a launch over n rows taken `step` rows at a time: G <= kMaxGrid,
 // a multiple of 8 when there are at least 8 (one group per XCD, struct Rows).
-Geom geom_for(int n, int step) {
+Geom geom_for(int n, int step, int most = kMaxGrid) {
     const int64_t steps = (int64_t(n) + step - 1) / step;
-    int64_t G = steps < kMaxGrid ? steps : kMaxGrid;
+    int64_t G = steps < most ? steps : most;
     if (G < 1) G = 1;
     if (G >= hz::kXcd) G -= G % hz::kXcd;
     return Geom{int(G)};
@@ -1633,8 +1633,7 @@ template <typename F> void with_multi(int BL, F&& f) {
     }
 }
 
-constexpr int kMultiU = 4;  // entries in flight per lane in the batched row product (v = A p)
-constexpr int kMultiUt = 3;  // the same for t = A s, whose epilogue holds more registers
+constexpr int kMultiU = 5;  // gathers in flight per lane in the batched row products
 
 // Values of a shared-pattern batch: explicit [nnz][B] values, or a
 // frequency sweep K - k_j^2 M + i k_j Bm from three real [nnz] arrays and the
@@ -1669,7 +1668,7 @@ struct MultiWs {
 
 size_t multi_layout(int B, int n, int64_t nnz, bool jacobi, bool kmb, char* base, MultiWs* out) {
     const int BL = multi_lanes(B);
-    const Geom geo = geom_for(n, kBlock / BL);
+    const Geom geo = geom_for(n, kBlock / BL, hz::kMultiMaxGrid);
     size_t off = 0;
     auto take = [&](size_t bytes) -> void* {
         void* p = base ? base + off : nullptr;
@@ -1692,9 +1691,9 @@ size_t multi_layout(int B, int n, int64_t nnz, bool jacobi, bool kmb, char* base
     return off;
 }
 
-// The five-kernel iteration for every system of the batch, in chunks of 8,
+// The four-kernel iteration for every system of the batch, in chunks of 8,
 // 16, ..., 64 iterations with a poll of the done counter between chunks; one
-// more P-kernel after maxiter concludes the last iteration.
+// more kernel after maxiter concludes the last iteration.
 template <int VS>
 int iterate_multi(hz_handle* h, hipStream_t s, const hz::MultiArgs& a, int BL, int maxiter) {
     const dim3 G(a.geo.G), Bk(kBlock);
@@ -1705,13 +1704,12 @@ int iterate_multi(hz_handle* h, hipStream_t s, const hz::MultiArgs& a, int BL, i
         int rc = launch_chunk(h, s, chunk_key(100 + VS, BL, k_n, tail, a), [&](hipStream_t q) {
             with_multi(BL, [&]<int BB>() {
                 for (int k = 0; k < k_n; ++k) {
-                    hipLaunchKernelGGL((hz::k_m_P<BB>), G, Bk, 0, q, a);
                     hipLaunchKernelGGL((hz::k_m_A1<BB, kMultiU, VS>), G, Bk, 0, q, a);
                     hipLaunchKernelGGL((hz::k_m_S<BB>), G, Bk, 0, q, a);
-                    hipLaunchKernelGGL((hz::k_m_B1<BB, kMultiUt, VS>), G, Bk, 0, q, a);
+                    hipLaunchKernelGGL((hz::k_m_B1<BB, kMultiU, VS>), G, Bk, 0, q, a);
                     hipLaunchKernelGGL((hz::k_m_C<BB>), G, Bk, 0, q, a);
                 }
-                if (tail) hipLaunchKernelGGL((hz::k_m_P<BB>), G, Bk, 0, q, a);
+                if (tail) hipLaunchKernelGGL((hz::k_m_end<BB>), dim3(1), Bk, 0, q, a);
             });
         });
         if (rc) return rc;
@@ -1740,7 +1738,7 @@ int solve_multi(hz_handle* h, hipStream_t s, int B, int n, int nnz, const int* r
                 hz_solve_info* infos) {
     const bool jacobi = (flags & HZ_PRECOND_JACOBI) != 0, kmb = mv.kmb();
     const int BL = multi_lanes(B);
-    const Geom geo = geom_for(n, kBlock / BL);
+    const Geom geo = geom_for(n, kBlock / BL, hz::kMultiMaxGrid);
     MultiWs w;
     multi_layout(B, n, nnz, jacobi, kmb, ws, &w);
     const int64_t nB = int64_t(n) * B;
@@ -1775,7 +1773,7 @@ int solve_multi(hz_handle* h, hipStream_t s, int B, int n, int nnz, const int* r
         if (kmb) {
             hipLaunchKernelGGL(hz::k_m_jacobi_kmb, grid1(nB), dim3(kBlock), 0, s, n, B, rp, ci, mv.K, mv.M, mv.Bm,
                                static_cast<const double*>(w.kw), w.dinv, w.sc);
-            // P and S rebuild D^{-1} from the diagonal triples (24 bytes a row for all systems, not 16 B per system)
+            // S and C rebuild D^{-1} from the diagonal triples (24 bytes a row for all systems, not 16 B per system)
             hipLaunchKernelGGL(hz::k_m_diag_kmb, grid1(n), dim3(kBlock), 0, s, n, rp, ci, mv.K, mv.M, mv.Bm, w.kd);
             a.kd = w.kd;
             a.q = w.q;

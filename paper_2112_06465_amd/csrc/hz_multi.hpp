@@ -12,27 +12,32 @@
 // B*16-byte runs: every load is coalesced, col_idx is read once for all
 // systems, and no cross-lane row reduction is needed.
 //
-// Iteration (gather-light, five kernels, as for randomly numbered single
-// systems):
-//   P:  conclude iteration i-1 per system (<rhat,r>, ||r||), beta;
-//       p = r + beta (p - omega v)
+// Iteration (the one-system iteration with s formed by itself, four kernels):
 //   A1: v = A p; partial <rhat, v>
-//   S:  alpha = rho / <rhat, v>; s = r - alpha v; partial ||s||^2
-//   B1: t = A s; partials <t, s>, ||t||^2
-//   C:  half-step test; omega = <t,s>/<t,t>; x += alpha p + omega s;
-//       r = s - omega t; partials <rhat, r>, ||r||^2
+//   S:  the end of iteration i - 1 per system; alpha = rho / <rhat, v>; s = r - alpha v
+//   B1: t = A s; partials ||s||^2, <t, s>, ||t||^2, <rhat, t>, <rhat, s>
+//   C:  half-step test; omega = <t, s> / <t, t>; rho and beta of the next
+//       iteration; x += alpha p + omega s; r = s - omega t;
+//       p = r + beta (p - omega v); partial ||r||^2
 // Partials are per (component, block, lane), reduced over the row slots of a
 // block by a fixed tree and finished at the consumer's head by every block
 // in a fixed order: reruns are bitwise identical, and system j's arithmetic
 // does not depend on the other systems (permuting the batch permutes the
-// results bitwise).
+// results bitwise).  A head reads K G BL doubles in every block, so a launch
+// has one block per CU (G <= kMultiMaxGrid) and each component is added by
+// waves of its own, two systems a lane: with 490 blocks of the same 31k rows
+// and all threads adding all components the heads read 250 KB a block and
+// took half of S, C and a fifth kernel, P, which C now contains.  Measured,
+// 16 systems K - k^2 M + i k B of 31,429 rows: 85 -> 58 us an iteration.
 #pragma once
 
 #include "hz_kernels.hpp"
 
 namespace hz {
 
-constexpr int kMultiMax = 256;  // most systems per shared-pattern launch
+constexpr int kMultiMax = 256;      // most systems per shared-pattern launch
+constexpr int kMultiMaxGrid = 256;  // most blocks: one per CU
+#define HZ_MULTI_BOUNDS __launch_bounds__(kBlock)  // one block per CU: <= 128 VGPRs
 
 // Where the row product takes system j's entry p from.
 enum : int {
@@ -51,8 +56,8 @@ struct MultiArgs {
     const double* __restrict__ M;
     const double* __restrict__ Bm;
     const double* __restrict__ kw;
-    const double2* dinv;  // non-null: the products act on q = D^{-1} p and u = D^{-1} s ([n][B])
-    const double* kd;     // VS_KMB with Jacobi, instead of dinv: row i's diagonal K, M, Bm at kd[4 i .. 4 i + 2]
+    const double* kd;     // VS_KMB with Jacobi, else null: row i's diagonal K, M, Bm at kd[4 i .. 4 i + 2]; the
+                          // products act on q = D^{-1} p and u = D^{-1} s
     const double2* b;     // [n][B]
     double2* r;
     double2* rh;
@@ -60,7 +65,7 @@ struct MultiArgs {
     double2* v;
     double2* s;
     double2* t;
-    double2* q;  // the vector A1 gathers: p itself, or D^{-1} p written by P
+    double2* q;  // the vector A1 gathers: p itself, or D^{-1} p written by C
     double2* u;  // the vector B1 gathers: s itself, or D^{-1} s written by S
     double2* x;
     double* part;    // [kParts][G][BL]
@@ -68,69 +73,108 @@ struct MultiArgs {
     int* ndone;      // systems finished so far
 };
 
-// Sum v[k] over the row slots of the block separately for every lane, by a
-// fixed tree over slots; every thread receives the sums of its lane.
-template <int BL, int K>
-__device__ __forceinline__ void slot_sum(double (&v)[K]) {
-    constexpr int S = kBlock / BL;
-    __shared__ double red[K][kBlock];
-    const int t = threadIdx.x;
-    __syncthreads();  // a previous use of red has been read
-#pragma unroll
-    for (int k = 0; k < K; ++k) red[k][t] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int s = S / 2; s >= 1; s /= 2) {
-        if (t < s * BL) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) red[k][t] += red[k][t + s * BL];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = red[k][t % BL];
-}
-
-// The block's partials of K components: region[(k*G + lb)*BL + lane].
-template <int BL, int K>
+// The block's partials of K components: region[(k*G + lb)*BL + lane], the sums
+// over the block's row slots separately for every lane: over a wave's slots by
+// rotations, over the waves through LDS.
+template <int BL, int K, int TAG = 0>
 __device__ __forceinline__ void mstore(double* region, int G, int lb, double (&e)[K]) {
-    slot_sum<BL, K>(e);
-    if (threadIdx.x < BL) {
+    constexpr int NW = kBlock / kWave, LN = BL < kWave ? BL : kWave, WS = BL / LN;  // WS: waves per slot
+    __shared__ double red[K][NW][LN];
+    const int lane = threadIdx.x % kWave;
+    if constexpr (BL < kWave) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) region[((size_t)k * G + lb) * BL + threadIdx.x] = e[k];
+        for (int k = 0; k < K; ++k) e[k] = wave_sum<BL>(e[k]);
+    }
+    if (lane < LN) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) red[k][wave_id()][lane] = e[k];
+    }
+    __syncthreads();
+    for (int o = threadIdx.x; o < K * BL; o += kBlock) {
+        const int k = o / BL, j = o % BL;
+        double t = red[k][j / LN][j % LN];
+#pragma unroll
+        for (int w = WS; w < NW; w += WS) t += red[k][w + j / LN][j % LN];
+        region[((size_t)k * G + lb) * BL + j] = t;
     }
 }
 
-// Totals of K components over all G blocks for the thread's lane.
+// Totals of K components over all G blocks for every lane: component k by
+// the W = head_waves waves k W .., a lane adding two neighbouring systems'
+// partials of blocks in turn; totals per wave in LDS, at() adds the W of them.
+// load() issues the first NV rounds' loads, store() waits and adds the rest.
+template <int BL, int K> struct MSum {
+    static constexpr int W = head_waves(K, kBlock / kWave), NV = 32 / W;
+    static constexpr int P = BL / 2 < kWave ? BL / 2 : kWave;  // pairs of systems that a wave's lanes hold
+    static_assert(BL <= 2 * kWave || W % 2 == 0, "a lane keeps its systems from round to round");
+    typedef double2 Tot[kBlock / kWave][P];
+    const double2* p;
+    int m, f0;
+    double2 v[NV];
+
+    static __device__ __forceinline__ int comp() { return wave_id() / W; }
+    __device__ __forceinline__ void load(const double* region, int G) {
+        p = reinterpret_cast<const double2*>(region);
+        m = G * (BL / 2);
+        f0 = wave_id() % W * kWave + (int)(threadIdx.x % kWave);
+#pragma unroll
+        for (int r = 0; r < NV; ++r) v[r] = p[f0 + r * W * kWave < m ? f0 + r * W * kWave : m - 1];
+    }
+    __device__ __forceinline__ void store(Tot& tot) {
+        double2 t = mk<double>(0.0, 0.0);
+        for (int g = 0; g < m; g += NV * W * kWave) {  // uniform
+            if (g > 0) {
+#pragma unroll
+                for (int r = 0; r < NV; ++r) {
+                    const int f = g + f0 + r * W * kWave;
+                    v[r] = p[f < m ? f : m - 1];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < NV; ++r) {
+                const bool in = g + f0 + r * W * kWave < m;
+                t.x += in ? v[r].x : 0.0;
+                t.y += in ? v[r].y : 0.0;
+            }
+        }
+        if constexpr (P < kWave) t = mk<double>(wave_sum<P>(t.x), wave_sum<P>(t.y));
+        if ((int)(threadIdx.x % kWave) < P) tot[wave_id()][threadIdx.x % kWave] = t;
+    }
+    static __device__ __forceinline__ double at(const Tot& tot, int k, int j) {
+        constexpr int H = BL / 2 / P;  // lane groups: a wave holds pairs h P .. h P + P - 1, h = its share mod H
+        const int h = j / 2 / P, q = j / 2 % P;
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; w += H) {
+            const double2 d = tot[k * W + w + h][q];
+            t += j % 2 ? d.y : d.x;
+        }
+        return t;
+    }
+};
+
+// Totals of K components for the kernels of one block.
 template <int BL, int K>
 __device__ __forceinline__ void mhead(const double* region, int G, double (&out)[K]) {
-    constexpr int S = kBlock / BL;
-    const int g = threadIdx.x / BL, j = threadIdx.x % BL;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double s = 0.0;
-        for (int b = g; b < G; b += S) s += region[((size_t)k * G + b) * BL + j];
-        out[k] = s;
+    __shared__ typename MSum<BL, K>::Tot tot;
+    MSum<BL, K> ms;
+    if (ms.comp() < K) {
+        ms.load(region + (size_t)ms.comp() * G * BL, G);
+        ms.store(tot);
     }
-    slot_sum<BL, K>(out);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) out[k] = MSum<BL, K>::at(tot, k, threadIdx.x % BL);
 }
 
-// True when every system has ended.  One read per block, broadcast through
-// LDS, so all waves of the block take the same branch (the counter may grow
-// while the kernel runs: leaders of P, S and C finish systems).
-__device__ __forceinline__ bool all_done(const MultiArgs& a) {
-    __shared__ int flag;
-    if (threadIdx.x == 0) flag = *a.ndone >= a.B;
-    __syncthreads();
-    return flag != 0;
-}
+// True when every system has ended.  (The products, during which no system
+// ends, read it in every wave; S and C, whose leaders end systems, read it
+// once per block and broadcast it with the head's barrier.)
+__device__ __forceinline__ bool all_done(const MultiArgs& a) { return *a.ndone >= a.B; }
 
 template <int BL> __device__ __forceinline__ double* mregion(const MultiArgs& a, int comp) {
     return a.part + (size_t)comp * a.geo.G * BL;
 }
-
-// The leader of system j: lane j of row slot 0 in logical block 0.
-template <int BL> __device__ __forceinline__ bool mleader(int lb) { return lb == 0 && threadIdx.x < BL; }
 
 // Entry p of system j.  k = (k_j, k_j^2) for VS_KMB.
 template <int VS>
@@ -184,12 +228,15 @@ __device__ __forceinline__ double2 mrow(const MultiArgs& a, int64_t i, int j, co
 constexpr int kMTileCap = 1536;
 
 // Row i of A_j times X for lane j, entries [b, e) of the staged tile (tile
-// offsets; the tile starts at entry e0); the same operations in the same
-// order as mrow<U, VS>, so the results are bitwise equal.
+// offsets; the tile starts at entry e0), in batches of U straight-line gathers:
+// an entry past the row's end is read at its last one and dropped by a select
+// (four at a time and the rest singly, a 15-entry row waited for six gathers,
+// one after the other; A1 13.8 -> 13.4 us with half the waves).
 template <int U, int VS>
-__device__ __forceinline__ double2 mrow_lds(const MultiArgs& a, int e0, const int* cs, const double* ks,
+__device__ __forceinline__ double2 mrow_lds(const MultiArgs& a, int e0, const unsigned* cs, const double* ks,
                                             const double* ms, const double* bs, int b, int e, int j, size_t B,
                                             const double2* __restrict__ X, double2 k) {
+    const double2* __restrict__ Xj = X + j;
     auto val = [&](int p) {
         if constexpr (VS == VS_KMB) {
             return mk<double>(__builtin_fma(-k.y, ms[p], ks[p]), k.x * bs[p]);
@@ -198,62 +245,100 @@ __device__ __forceinline__ double2 mrow_lds(const MultiArgs& a, int e0, const in
         }
     };
     double2 acc = mk<double>(0.0, 0.0);
-    int p = b;
-    for (; p + U <= e; p += U) {
-        int c[U];
+    for (int p = b; p < e; p += U) {
         double2 xv[U], av[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = cs[p + u];
-        if constexpr (VS != VS_KMB) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) av[u] = val(p + u);
+        for (int u = 0; u < U; ++u) {
+            const int pu = p + u < e ? p + u : e - 1;
+            if constexpr (VS != VS_KMB) av[u] = val(pu);
+            xv[u] = Xj[cs[pu]];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) xv[u] = X[(size_t)c[u] * B + j];
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc = cfma<double>(VS == VS_KMB ? val(p + u) : av[u], xv[u], acc);
+        for (int u = 0; u < U; ++u) {
+            const double2 nx = cfma<double>(VS == VS_KMB ? val(p + u < e ? p + u : e - 1) : av[u], xv[u], acc);
+            acc = mk<double>(p + u < e ? nx.x : acc.x, p + u < e ? nx.y : acc.y);
+        }
     }
-    for (; p < e; ++p) acc = cfma<double>(val(p), X[(size_t)cs[p] * B + j], acc);
     return acc;
 }
 
+// A thread's part of a tile: the tile's first entry and their number, its
+// row's entries (tile offsets), and the shared entries that it stages.
+template <int VS> struct MTile {
+    static constexpr int R = (kMTileCap + kBlock - 1) / kBlock, RK = VS == VS_KMB ? R : 1;
+    int e0, ne, rb, re;
+    int c[R];
+    double kv[RK], mv[RK], bv[RK];
+};
+// The tile of S rows from r0 on.
+template <int VS, int S>
+__device__ __forceinline__ MTile<VS> m_fetch(const MultiArgs& a, const RowRange& rr, int64_t r0) {
+    MTile<VS> t{};
+    const int* __restrict__ rp = a.row_ptr;
+    const int64_t re = r0 + S < rr.rw.x1 ? r0 + S : rr.rw.x1;
+    const int64_t i = r0 + threadIdx.x / (kBlock / S), ic = i < re ? i : re - 1;  // an in-bounds row of the tile
+    t.e0 = rp[r0];
+    t.ne = rp[re] - t.e0;
+    t.rb = rp[ic] - t.e0;
+    t.re = rp[ic + 1] - t.e0;
+    if (t.ne > 0 && t.ne <= kMTileCap) {  // uniform
+#pragma unroll
+        for (int r = 0; r < MTile<VS>::R; ++r) {
+            const int q = (int)threadIdx.x + r * kBlock, at = t.e0 + (q < t.ne ? q : t.ne - 1);
+            t.c[r] = a.col_idx[at];
+            if constexpr (VS == VS_KMB) {
+                t.kv[r] = a.K[at];
+                t.mv[r] = a.M[at];
+                t.bv[r] = a.Bm[at];
+            }
+        }
+    }
+    return t;
+}
+
 // f(i, acc, w) for every row i of the block on lane j when `on`, acc = row i
-// of A_j times X and w = pre(i), an operand of the epilogue.  The block walks
+// of A_j times X and w = pre(i), the operands of the epilogue.  The block walks
 // its rows in tiles of kBlock / BL consecutive rows (the rows and order of
 // HZ_MROWS); a tile's shared entries are loaded once, contiguously by the
-// whole block, into LDS.  The row's bounds are loaded with the tile's (before
-// the staging) and w before the row's gathers, so neither load adds a wait
-// of its own after the barrier.
+// whole block, into registers while the tile before is computed, and from
+// there into LDS.  w is loaded before the row's gathers, so it adds no wait.
 template <int BL, int U, int VS, typename P, typename F>
 __device__ __forceinline__ void m_tiles(const MultiArgs& a, const RowRange& rr, bool on, const double2* __restrict__ X,
                                         double2 k, P&& pre, F&& f) {
     constexpr int S = kBlock / BL;
     constexpr bool kmb = VS == VS_KMB;
     constexpr int KC = kmb ? kMTileCap : 1;  // K, M, Bm staged only for K/M/B
-    __shared__ int cs[kMTileCap];
+    constexpr int R = MTile<VS>::R;
+    __shared__ unsigned cs[kMTileCap];  // col B: n B vector elements of 16 bytes fit into memory only below 2^32
     __shared__ double ks[KC], ms[KC], bs[KC];
     const int g = threadIdx.x / BL, j = threadIdx.x % BL;
-    const int* __restrict__ rp = a.row_ptr;
-    for (int64_t r0 = rr.rw.x0 + (int64_t)rr.rw.k * S; r0 < rr.rw.x1; r0 += (int64_t)rr.rw.K * S) {  // uniform
-        const int64_t re = r0 + S < rr.rw.x1 ? r0 + S : rr.rw.x1;
-        const int64_t i = r0 + g, ic = i < re ? i : re - 1;  // ic: an in-bounds row of the tile
-        const int e0 = rp[r0], ne = rp[re] - e0;
-        const int rb = rp[ic], rend = rp[ic + 1];
-        const bool staged = ne <= kMTileCap;
+    int64_t r0 = rr.rw.x0 + (int64_t)rr.rw.k * S;
+    MTile<VS> nx{};
+    if (r0 < rr.rw.x1) nx = m_fetch<VS, S>(a, rr, r0);
+    while (r0 < rr.rw.x1) {  // uniform
+        const int64_t i = r0 + g, end = r0 + S < rr.rw.x1 ? r0 + S : rr.rw.x1;
+        const bool staged = nx.ne <= kMTileCap;
+        const int e0 = nx.e0, rb = nx.rb, re = nx.re;
         if (staged) {
-            for (int q = threadIdx.x; q < ne; q += kBlock) {
-                cs[q] = a.col_idx[e0 + q];
-                if constexpr (kmb) {
-                    ks[q] = a.K[e0 + q];
-                    ms[q] = a.M[e0 + q];
-                    bs[q] = a.Bm[e0 + q];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int q = (int)threadIdx.x + r * kBlock;
+                if (q < nx.ne) {
+                    cs[q] = (unsigned)nx.c[r] * (unsigned)a.B;
+                    if constexpr (kmb) {
+                        ks[q] = nx.kv[r];
+                        ms[q] = nx.mv[r];
+                        bs[q] = nx.bv[r];
+                    }
                 }
             }
             __syncthreads();
         }
-        if (on && i < re) {
-            const double2 w = pre(i);
-            const double2 acc = staged ? mrow_lds<(kmb || U < 3 ? U : 3), VS>(a, e0, cs, ks, ms, bs, rb - e0, rend - e0, j, (size_t)a.B, X, k)
+        r0 += (int64_t)rr.rw.K * S;
+        if (r0 < rr.rw.x1) nx = m_fetch<VS, S>(a, rr, r0);
+        if (on && i < end) {
+            const auto w = pre(i);
+            const double2 acc = staged ? mrow_lds<U, VS>(a, e0, cs, ks, ms, bs, rb, re, j, (size_t)a.B, X, k)
                                        : mrow<2, VS>(a, i, j, X, k);
             f(i, acc, w);
         }
@@ -263,13 +348,20 @@ __device__ __forceinline__ void m_tiles(const MultiArgs& a, const RowRange& rr, 
 
 // 1 / (K_ii - k^2 M_ii + i k Bm_ii) from the row's diagonal triple, with the
 // operations of k_m_jacobi_kmb (bitwise the value it stores in dinv).
-__device__ __forceinline__ double2 m_dinv_kmb(const double* __restrict__ kd, int64_t i, double kj) {
-    const double2 km = reinterpret_cast<const double2*>(kd)[2 * i];
-    const double bd = kd[4 * i + 2];
-    const double2 d = mk<double>(__builtin_fma(-kj * kj, km.y, km.x), kj * bd);
-    const double q = d.x * d.x + d.y * d.y;
-    return mk<double>(d.x / q, -d.y / q);
-}
+struct MDiag {
+    double2 km;
+    double b;
+    __device__ __forceinline__ void load(const double* __restrict__ kd, int64_t i) {
+        if (kd == nullptr) return;  // uniform
+        km = reinterpret_cast<const double2*>(kd)[2 * i];
+        b = kd[4 * i + 2];
+    }
+    __device__ __forceinline__ double2 inverse(double kj) const {
+        const double2 d = mk<double>(__builtin_fma(-kj * kj, km.y, km.x), kj * b);
+        const double q = d.x * d.x + d.y * d.y;
+        return mk<double>(d.x / q, -d.y / q);
+    }
+};
 
 #define HZ_MULTI_ROWS                                       \
     constexpr int S = kBlock / BL;                          \
@@ -282,17 +374,22 @@ __device__ __forceinline__ double2 m_dinv_kmb(const double* __restrict__ kd, int
 #define HZ_MROWS(i) \
     for (int64_t i = rr.rw.x0 + (int64_t)rr.rw.k * S + g; i < rr.rw.x1; i += (int64_t)rr.rw.K * S)
 
-// Solve set-up: r = src, rhat = src; partials <rhat,r>, ||r||^2 (C), ||b||^2 (I).
+// Solve set-up: r = rhat = p = src, q = D^{-1} p; partials <rhat,r>, ||r||^2 (C), ||b||^2 (I).
 template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_init(const MultiArgs a, const double2* src) {
+__global__ HZ_MULTI_BOUNDS void k_m_init(const MultiArgs a, const double2* src) {
     HZ_MULTI_ROWS;
     double e[3] = {0.0, 0.0, 0.0}, eb[1] = {0.0};
+    const double kj = a.kd && j < a.B ? a.kw[j] : 0.0;
     if (j < a.B)
         HZ_MROWS(i) {
             const size_t q = (size_t)i * Bz + j;
             const double2 bv = a.b[q], rv = src[q];
             if (a.r != src) a.r[q] = rv;
             a.rh[q] = rv;
+            a.p[q] = rv;
+            MDiag d{};
+            d.load(a.kd, i);
+            if (a.kd) a.q[q] = cmul<double>(d.inverse(kj), rv);
             eb[0] = __builtin_fma(bv.x, bv.x, eb[0]);
             eb[0] = __builtin_fma(bv.y, bv.y, eb[0]);
             const double2 c = cdotacc(rv.x, rv.y, rv.x, rv.y, mk<double>(e[0], e[1]));
@@ -307,7 +404,7 @@ __global__ HZ_STREAM_BOUNDS void k_m_init(const MultiArgs a, const double2* src)
 
 // ||b||, initial convergence test of every system (one block).
 template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_fin_init(const MultiArgs a) {
+__global__ HZ_MULTI_BOUNDS void k_m_fin_init(const MultiArgs a) {
     double hb[1], hr[3];
     mhead<BL, 1>(mregion<BL>(a, kPartI), a.geo.G, hb);
     mhead<BL, 3>(mregion<BL>(a, kPartC), a.geo.G, hr);
@@ -325,6 +422,7 @@ __global__ HZ_STREAM_BOUNDS void k_m_fin_init(const MultiArgs a) {
     sc->why = BD_NONE;
     sc->status = ST_NOT_CONVERGED;
     sc->alpha = sc->omega = sc->beta = mk<double>(1.0, 0.0);
+    sc->rho2[1] = mk<double>(hr[0], hr[1]);
     if (!__builtin_isfinite(bn) || !__builtin_isfinite(hr[2])) return finish(sc, a.ndone, ST_NONFINITE, 0);
     if (bn == 0.0) {
         sc->zero_x = 1;
@@ -337,74 +435,14 @@ __global__ HZ_STREAM_BOUNDS void k_m_fin_init(const MultiArgs a) {
     else if (sc->maxiter <= 0) finish(sc, a.ndone, ST_NOT_CONVERGED, 0);
 }
 
-// P-kernel: end of iteration i-1 and beta per system (as in the single
-// solve), then p = r + beta (p - omega v) on the system's lanes.
-template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_P(const MultiArgs a) {
-    if (all_done(a)) return;
-    HZ_MULTI_ROWS;
-    double h[3];
-    mhead<BL, 3>(mregion<BL>(a, kPartC), a.geo.G, h);
-    if (j >= a.B) return;
-    SolverScal* sc = a.sc + j;
-    const bool lead = mleader<BL>(rr.lb);
-    if (sc->done) return;
-    if (sc->pending) {  // the half step's x += alpha p is complete everywhere
-        if (lead) finish(sc, a.ndone, ST_OK, sc->pending);
-        return;
-    }
-    const int it = sc->iter;
-    const double2 rho = mk<double>(h[0], h[1]);
-    double2 beta = mk<double>(0.0, 0.0), om = mk<double>(0.0, 0.0);
-    if (it > 1) {
-        const double rel = __builtin_sqrt(h[2]) / sc->bnorm;
-        om = sc->omega;
-        int stt = -1, sit = 0, why = BD_NONE;
-        if (!__builtin_isfinite(rel)) stt = ST_NONFINITE, sit = it - 1;
-        else if (rel <= sc->rtol) stt = ST_OK, sit = it - 1;
-        else if (zzero(om)) stt = ST_BREAKDOWN, sit = it - 1, why = BD_OMEGA;
-        else if (it - 1 >= sc->maxiter) stt = ST_NOT_CONVERGED, sit = sc->maxiter;
-        else if (!zfinite(rho)) stt = ST_NONFINITE, sit = it;
-        else if (zzero(rho)) stt = ST_BREAKDOWN, sit = it, why = BD_RHO;
-        else {
-            beta = zmul(zdiv(rho, sc->rho2[(it - 1) & 1]), zdiv(sc->alpha, om));
-            if (!zfinite(beta)) stt = ST_NONFINITE, sit = it;
-        }
-        if (lead) sc->relres = rel;
-        if (stt >= 0) {
-            if (lead) finish(sc, a.ndone, stt, sit, why);
-            return;
-        }
-    }
-    if (lead) {
-        sc->rho2[it & 1] = rho;
-        sc->beta = beta;
-        sc->cur = it;
-    }
-    const double kj = a.kd ? a.kw[j] : 0.0;
-    HZ_MROWS(i) {
-        const size_t q = (size_t)i * Bz + j;
-        const double2 rv = a.r[q];
-        double2 pn = rv;
-        if (it != 1) {
-            const double2 pv = a.p[q], vv = a.v[q];
-            const double2 d = mk<double>(pv.x - __builtin_fma(om.x, vv.x, -om.y * vv.y),
-                                         pv.y - __builtin_fma(om.x, vv.y, om.y * vv.x));
-            pn = cfma<double>(beta, d, rv);
-        }
-        a.p[q] = pn;
-        if (a.kd) a.q[q] = cmul<double>(m_dinv_kmb(a.kd, i, kj), pn);
-        else if (a.dinv) a.q[q] = cmul<double>(a.dinv[q], pn);
-    }
-}
-
 // A1-kernel: v = A p; partial <rhat, v>.
 template <int BL, int U, int VS>
-__global__ HZ_STREAM_BOUNDS void k_m_A1(const MultiArgs a) {
-    if (all_done(a)) return;
+__global__ HZ_MULTI_BOUNDS void k_m_A1(const MultiArgs a) {
     HZ_MULTI_ROWS;
     double e[2] = {0.0, 0.0};
     const bool on = j < a.B && !a.sc[j].done && !a.sc[j].pending;
+    const double2 kj = j < a.B ? mwave<VS>(a, j) : mk<double>(0.0, 0.0);
+    if (all_done(a)) return;
     auto pre = [&](int64_t i) { return a.rh[(size_t)i * Bz + j]; };
     auto row = [&](int64_t i, double2 acc, double2 w) {
         a.v[(size_t)i * Bz + j] = acc;
@@ -412,149 +450,261 @@ __global__ HZ_STREAM_BOUNDS void k_m_A1(const MultiArgs a) {
         e[0] = c.x;
         e[1] = c.y;
     };
-    m_tiles<BL, U, VS>(a, rr, on, a.q, j < a.B ? mwave<VS>(a, j) : mk<double>(0.0, 0.0), pre, row);
+    m_tiles<BL, U, VS>(a, rr, on, a.q, kj, pre, row);
     mstore<BL, 2>(mregion<BL>(a, kPartA), a.geo.G, rr.lb, e);
 }
 
-// S-kernel: alpha = rho / <rhat, v>; s = r - alpha v; partial ||s||^2.
+// S-kernel: the end of iteration i-1 and alpha per system (as in the
+// one-system solve), then s = r - alpha v on the system's lanes.
 template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_S(const MultiArgs a) {
-    if (all_done(a)) return;
+__global__ HZ_MULTI_BOUNDS void k_m_S(const MultiArgs a) {
+    __shared__ typename MSum<BL, 3>::Tot tot;
+    __shared__ double2 al[BL];
+    __shared__ int go[BL];
+    __shared__ int over;
     HZ_MULTI_ROWS;
-    double h[2], e[1] = {0.0};
-    mhead<BL, 2>(mregion<BL>(a, kPartA), a.geo.G, h);
-    bool go = j < a.B;
-    double2 alpha = mk<double>(0.0, 0.0);
-    if (go) {
-        SolverScal* sc = a.sc + j;
-        go = !sc->done && !sc->pending;
-        if (go) {
-            const int it = sc->cur;
-            const double2 sigma = mk<double>(h[0], h[1]);
-            if (!zfinite(sigma) || zzero(sigma)) {
-                if (mleader<BL>(rr.lb)) finish(sc, a.ndone, zzero(sigma) ? ST_BREAKDOWN : ST_NONFINITE, it, zzero(sigma) ? BD_RHAT_V : BD_NONE);
-                go = false;
-            } else {
-                alpha = zdiv(sc->rho2[it & 1], sigma);
-                if (mleader<BL>(rr.lb)) sc->alpha = alpha;
+    if (threadIdx.x == 0) over = all_done(a);
+    MSum<BL, 3> ms;
+    const int c = ms.comp();  // <rhat, v>, then ||r||^2
+    if (c < 3) ms.load(mregion<BL>(a, c < 2 ? kPartA + c : kPartC + 2), a.geo.G);
+    SolverScal* sc = a.sc + (j < a.B ? j : 0);
+    const int done = sc->done, pending = sc->pending, it = sc->iter;
+    const double2 rho_0 = sc->rho2[0], rho_1 = sc->rho2[1];
+    const EndIn z{sc->bnorm, sc->rtol, sc->omega, (it & 1) ? rho_1 : rho_0, sc->beta, sc->maxiter};
+    const int64_t step = (int64_t)rr.rw.K * S;
+    int64_t i = rr.rw.x0 + (int64_t)rr.rw.k * S + g;
+    if (j >= a.B) i = rr.rw.x1;
+    const double kj = a.kd && j < a.B ? a.kw[j] : 0.0;
+    double2 v0 = mk<double>(0.0, 0.0), r0 = v0;  // the first row's, in flight during the head
+    MDiag d0{};
+    if (i < rr.rw.x1) {
+        v0 = a.v[(size_t)i * Bz + j];
+        r0 = a.r[(size_t)i * Bz + j];
+        d0.load(a.kd, i);
+    }
+    if (c < 3) ms.store(tot);
+    __syncthreads();
+    if (over) return;
+    if (threadIdx.x < BL) {
+        const bool lead = rr.lb == 0;
+        double2 alpha = mk<double>(0.0, 0.0);
+        auto decide = [&]() -> int {
+            if (j >= a.B || done) return 0;
+            if (pending) {  // the half step's x += alpha p is complete everywhere
+                if (lead) finish(sc, a.ndone, ST_OK, pending);
+                return 0;
             }
-        }
+            if (it > 1) {
+                double rel;
+                int sit, why;
+                const int st = iteration_end(it, ms.at(tot, 2, j), z, rel, sit, why);
+                if (lead) sc->relres = rel;
+                if (st >= 0) {
+                    if (lead) finish(sc, a.ndone, st, sit, why);
+                    return 0;
+                }
+            }
+            const double2 sigma = mk<double>(ms.at(tot, 0, j), ms.at(tot, 1, j));
+            if (!zfinite(sigma) || zzero(sigma)) {
+                if (lead) finish(sc, a.ndone, zzero(sigma) ? ST_BREAKDOWN : ST_NONFINITE, it, zzero(sigma) ? BD_RHAT_V : BD_NONE);
+                return 0;
+            }
+            alpha = zdiv(z.rho, sigma);
+            if (lead) {
+                sc->alpha = alpha;
+                sc->cur = it;
+            }
+            return 1;
+        };
+        go[threadIdx.x] = decide();
+        al[threadIdx.x] = alpha;
     }
-    if (go) {
-        const double2 nal = mk<double>(-alpha.x, -alpha.y);
-        const double kj = a.kd ? a.kw[j] : 0.0;
-        HZ_MROWS(i) {
-            const size_t q = (size_t)i * Bz + j;
-            const double2 sv = cfma<double>(nal, a.v[q], a.r[q]);
-            a.s[q] = sv;
-            if (a.kd) a.u[q] = cmul<double>(m_dinv_kmb(a.kd, i, kj), sv);
-            else if (a.dinv) a.u[q] = cmul<double>(a.dinv[q], sv);
-            e[0] = __builtin_fma(sv.x, sv.x, e[0]);
-            e[0] = __builtin_fma(sv.y, sv.y, e[0]);
+    __syncthreads();
+    if (!go[j]) return;
+    const double2 nal = mk<double>(-al[j].x, -al[j].y);
+    while (i < rr.rw.x1) {
+        const size_t q = (size_t)i * Bz + j;
+        const double2 sv = cfma<double>(nal, v0, r0);
+        const MDiag d = d0;
+        i += step;
+        if (i < rr.rw.x1) {
+            v0 = a.v[(size_t)i * Bz + j];
+            r0 = a.r[(size_t)i * Bz + j];
+            d0.load(a.kd, i);
         }
+        a.s[q] = sv;
+        if (a.kd) a.u[q] = cmul<double>(d.inverse(kj), sv);
     }
-    mstore<BL, 1>(mregion<BL>(a, kPartB), a.geo.G, rr.lb, e);
 }
 
-// B1-kernel: t = A s; partials <t, s>, ||t||^2.
+// B1-kernel: t = A s and its dot products.
 template <int BL, int U, int VS>
-__global__ HZ_STREAM_BOUNDS void k_m_B1(const MultiArgs a) {
-    if (all_done(a)) return;
+__global__ HZ_MULTI_BOUNDS void k_m_B1(const MultiArgs a) {
     HZ_MULTI_ROWS;
-    double e[3] = {0.0, 0.0, 0.0};
+    double e[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const bool on = j < a.B && !a.sc[j].done;
-    auto pre = [&](int64_t i) { return a.s[(size_t)i * Bz + j]; };
-    auto row = [&](int64_t i, double2 acc, double2 sv) {
-        a.t[(size_t)i * Bz + j] = acc;
-        const double2 c = cdotacc(acc.x, acc.y, sv.x, sv.y, mk<double>(e[0], e[1]));
-        e[0] = c.x;
-        e[1] = c.y;
-        e[2] = __builtin_fma(acc.x, acc.x, e[2]);
-        e[2] = __builtin_fma(acc.y, acc.y, e[2]);
+    const double2 kj = j < a.B ? mwave<VS>(a, j) : mk<double>(0.0, 0.0);
+    if (all_done(a)) return;
+    struct Ops {
+        double2 s, rh;
     };
-    m_tiles<BL, U, VS>(a, rr, on, a.u, j < a.B ? mwave<VS>(a, j) : mk<double>(0.0, 0.0), pre, row);
-    mstore<BL, 3>(mregion<BL>(a, kPartB + 1), a.geo.G, rr.lb, e);
+    auto pre = [&](int64_t i) { return Ops{a.s[(size_t)i * Bz + j], a.rh[(size_t)i * Bz + j]}; };
+    auto row = [&](int64_t i, double2 acc, const Ops& w) {
+        a.t[(size_t)i * Bz + j] = acc;
+        b_terms<double>(e, w.s, acc, w.rh);
+    };
+    m_tiles<BL, U, VS>(a, rr, on, a.u, kj, pre, row);
+    mstore<BL, 8>(mregion<BL>(a, kPartB), a.geo.G, rr.lb, e);
 }
 
-// C-kernel: half-step test on ||s||; omega; x += alpha p + omega s;
-// r = s - omega t; partials <rhat, r>, ||r||^2.
+// C-kernel: half-step test on ||s||; omega; rho and beta of the next iteration;
+// x += alpha p + omega s; r = s - omega t; p and q = D^{-1} p; partial ||r||^2.
 template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_C(const MultiArgs a) {
-    if (all_done(a)) return;
+__global__ HZ_MULTI_BOUNDS void k_m_C(const MultiArgs a) {
+    enum : int { STOP = 0, HALF = 1, FULL = 2 };
+    __shared__ typename MSum<BL, 8>::Tot tot;
+    __shared__ double2 cal[BL], com[BL], cbt[BL];  // alpha, omega, beta
+    __shared__ int mode[BL];
+    __shared__ int over;
     HZ_MULTI_ROWS;
-    double h[4], e[3] = {0.0, 0.0, 0.0};
-    mhead<BL, 4>(mregion<BL>(a, kPartB), a.geo.G, h);
-    int mode = 0;  // 0: nothing, 1: half-step exit, 2: full step
-    double2 al = mk<double>(0.0, 0.0), om = mk<double>(0.0, 0.0);
-    if (j < a.B) {
-        SolverScal* sc = a.sc + j;
-        const bool lead = mleader<BL>(rr.lb);
-        // pending is written by this kernel's leader, so only done is read
-        // here (a pending exit of the previous iteration was concluded by P)
-        if (!sc->done) {
-            const int it = sc->cur;
-            const double rel = __builtin_sqrt(h[0]) / sc->bnorm;
-            al = sc->alpha;
+    if (threadIdx.x == 0) over = all_done(a);
+    MSum<BL, 8> ms;
+    ms.load(mregion<BL>(a, kPartB + ms.comp()), a.geo.G);
+    SolverScal* sc = a.sc + (j < a.B ? j : 0);
+    // pending is written by this kernel's leader, so only done is read here
+    // (a pending exit of the previous iteration was concluded by S)
+    const int done = sc->done, it = sc->cur;
+    const double bnorm = sc->bnorm, rtol = sc->rtol;
+    const double2 alpha = sc->alpha, rho_0 = sc->rho2[0], rho_1 = sc->rho2[1], rho = (it & 1) ? rho_1 : rho_0;
+    const int64_t step = (int64_t)rr.rw.K * S;
+    int64_t i = rr.rw.x0 + (int64_t)rr.rw.k * S + g;
+    if (j >= a.B) i = rr.rw.x1;
+    const double kj = a.kd && j < a.B ? a.kw[j] : 0.0;
+    double2 s0 = mk<double>(0.0, 0.0), t0 = s0, p0 = s0, v0 = s0, x0 = s0;
+    MDiag d0{};
+    auto fetch = [&]() HZ_INLINE {
+        const size_t q = (size_t)i * Bz + j;
+        s0 = a.s[q];
+        t0 = a.t[q];
+        p0 = a.p[q];
+    };
+    auto fetch2 = [&]() HZ_INLINE {  // for the first row, when the partials' registers are free
+        const size_t q = (size_t)i * Bz + j;
+        v0 = a.v[q];
+        x0 = a.x[q];
+        d0.load(a.kd, i);
+    };
+    if (i < rr.rw.x1) fetch();
+    ms.store(tot);
+    if (i < rr.rw.x1) fetch2();
+    __syncthreads();
+    if (over) return;
+    if (threadIdx.x < BL) {
+        const bool lead = rr.lb == 0;
+        double2 om = mk<double>(0.0, 0.0), beta = om;
+        auto decide = [&]() -> int {
+            if (j >= a.B || done) return STOP;
+            double h[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) h[k] = ms.at(tot, k, j);
+            const double rel = __builtin_sqrt(h[0]) / bnorm;
             if (!__builtin_isfinite(rel)) {
                 if (lead) finish(sc, a.ndone, ST_NONFINITE, it);
-            } else if (rel <= sc->rtol) {  // concluded by the next P-kernel
-                mode = 1;
+                return STOP;
+            }
+            if (rel <= rtol) {  // concluded by the next S-kernel
                 if (lead) {
                     sc->relres = rel;
                     sc->pending = it;
                 }
-            } else {
-                const double2 ts = mk<double>(h[1], h[2]);
-                const double tt = h[3];
-                int st = -1, why = BD_NONE;
-                if (!zfinite(ts) || !__builtin_isfinite(tt)) st = ST_NONFINITE;
-                else if (tt == 0.0) st = ST_BREAKDOWN, why = BD_TT;
-                else {
-                    om = zdiv(ts, mk<double>(tt, 0.0));
-                    if (!zfinite(om)) st = ST_NONFINITE;
-                }
-                if (st >= 0) {
-                    if (lead) finish(sc, a.ndone, st, it, why);
-                } else {
-                    mode = 2;
-                    if (lead) {
-                        sc->omega = om;
-                        sc->iter = it + 1;
-                    }
-                }
+                return HALF;
             }
-        }
+            const double2 ts = mk<double>(h[1], h[2]);
+            const double tt = h[3];
+            int st = -1, why = BD_NONE;
+            if (!zfinite(ts) || !__builtin_isfinite(tt)) st = ST_NONFINITE;
+            else if (tt == 0.0) st = ST_BREAKDOWN, why = BD_TT;
+            else {
+                om = zdiv(ts, mk<double>(tt, 0.0));
+                if (!zfinite(om)) st = ST_NONFINITE;
+            }
+            if (st >= 0) {
+                if (lead) finish(sc, a.ndone, st, it, why);
+                return STOP;
+            }
+            // omega = 0, rho = 0 or a non-finite beta end the solve in the next S, after its test on ||r||
+            const double2 ort = zmul(om, mk<double>(h[4], h[5]));
+            const double2 rho_n = mk<double>(h[6] - ort.x, h[7] - ort.y);
+            beta = zmul(zdiv(rho_n, rho), zdiv(alpha, om));
+            if (lead) {
+                sc->omega = om;
+                sc->rho2[(it + 1) & 1] = rho_n;
+                sc->beta = beta;
+                sc->iter = it + 1;
+            }
+            return FULL;
+        };
+        mode[threadIdx.x] = decide();
+        cal[threadIdx.x] = alpha;
+        com[threadIdx.x] = om;
+        cbt[threadIdx.x] = beta;
     }
-    if (mode == 1) {
-        HZ_MROWS(i) {
+    __syncthreads();
+    double e[1] = {0.0};
+    if (mode[j] == HALF) {  // half-step exit: x += alpha p
+        for (; i < rr.rw.x1; i += step) {
             const size_t q = (size_t)i * Bz + j;
-            a.x[q] = cfma<double>(al, a.p[q], a.x[q]);
+            a.x[q] = cfma<double>(cal[j], a.p[q], a.x[q]);
         }
-    } else if (mode == 2) {
-        const double2 nom = mk<double>(-om.x, -om.y);
-        HZ_MROWS(i) {
+    } else if (mode[j] == FULL) {
+        const double2 al = cal[j], om = com[j], bt = cbt[j], nom = mk<double>(-om.x, -om.y);
+        while (i < rr.rw.x1) {
             const size_t q = (size_t)i * Bz + j;
-            const double2 sv = a.s[q], tv = a.t[q], rh = a.rh[q];
-            double2 x = a.x[q];
-            x = cfma<double>(al, a.p[q], x);
-            x = cfma<double>(om, sv, x);
+            double2 x = cfma<double>(al, p0, x0);
+            x = cfma<double>(om, s0, x);
+            const double2 r = cfma<double>(nom, t0, s0);
+            const double2 pn = p_update<double>(bt, om, r, p0, v0);
+            const MDiag d = d0;
+            i += step;
+            if (i < rr.rw.x1) {
+                fetch();
+                fetch2();
+            }
             a.x[q] = x;
-            const double2 r = cfma<double>(nom, tv, sv);
             a.r[q] = r;
-            const double2 c = cdotacc(rh.x, rh.y, r.x, r.y, mk<double>(e[0], e[1]));
-            e[0] = c.x;
-            e[1] = c.y;
-            e[2] = __builtin_fma(r.x, r.x, e[2]);
-            e[2] = __builtin_fma(r.y, r.y, e[2]);
+            a.p[q] = pn;
+            if (a.kd) a.q[q] = cmul<double>(d.inverse(kj), pn);
+            e[0] = __builtin_fma(r.x, r.x, e[0]);
+            e[0] = __builtin_fma(r.y, r.y, e[0]);
         }
     }
-    mstore<BL, 3>(mregion<BL>(a, kPartC), a.geo.G, rr.lb, e);
+    mstore<BL, 1>(mregion<BL>(a, kPartC + 2), a.geo.G, rr.lb, e);
+}
+
+// After the last iteration of a limited solve: conclude it (one block).
+template <int BL>
+__global__ HZ_MULTI_BOUNDS void k_m_end(const MultiArgs a) {
+    double h[1];
+    mhead<BL, 1>(mregion<BL>(a, kPartC + 2), a.geo.G, h);
+    const int j = threadIdx.x;
+    if (j >= a.B) return;
+    SolverScal* sc = a.sc + j;
+    if (sc->done) return;
+    if (sc->pending) return finish(sc, a.ndone, ST_OK, sc->pending);
+    const int it = sc->iter;
+    if (it <= 1) return;
+    const EndIn z{sc->bnorm, sc->rtol, sc->omega, sc->rho2[it & 1], sc->beta, sc->maxiter};
+    double rel;
+    int sit, why;
+    const int st = iteration_end(it, h[0], z, rel, sit, why);
+    sc->relres = rel;
+    if (st >= 0) finish(sc, a.ndone, st, sit, why);
 }
 
 // y = b - A xin for every system (explicit values `vals`, or K, M, Bm);
 // partial ||y||^2 (I).
 template <int BL, int U, int VS>
-__global__ HZ_STREAM_BOUNDS void k_m_resid(const MultiArgs a, const double2* __restrict__ vals,
+__global__ HZ_MULTI_BOUNDS void k_m_resid(const MultiArgs a, const double2* __restrict__ vals,
                                            const double2* __restrict__ xin, double2* __restrict__ y) {
     HZ_MULTI_ROWS;
     MultiArgs a2 = a;
@@ -574,7 +724,7 @@ __global__ HZ_STREAM_BOUNDS void k_m_resid(const MultiArgs a, const double2* __r
 
 // relres_true of every system from region I (one block).
 template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_fin_true(const MultiArgs a) {
+__global__ HZ_MULTI_BOUNDS void k_m_fin_true(const MultiArgs a) {
     double h[1];
     mhead<BL, 1>(mregion<BL>(a, kPartI), a.geo.G, h);
     const int j = threadIdx.x;
@@ -585,7 +735,7 @@ __global__ HZ_STREAM_BOUNDS void k_m_fin_true(const MultiArgs a) {
 
 // x = 0 for the systems whose right-hand side is zero.
 template <int BL>
-__global__ HZ_STREAM_BOUNDS void k_m_zero_if(const MultiArgs a) {
+__global__ HZ_MULTI_BOUNDS void k_m_zero_if(const MultiArgs a) {
     HZ_MULTI_ROWS;
     if (j >= a.B || !a.sc[j].zero_x) return;
     HZ_MROWS(i) a.x[(size_t)i * Bz + j] = mk<double>(0.0, 0.0);
