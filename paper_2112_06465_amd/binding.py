@@ -28,6 +28,10 @@ _hlock = threading.Lock()
 
 def handle(device: torch.device | int | None = None) -> int:
     """Per-device library handle, created on first use with that device current."""
+    if type(device) is torch.device:  # a tensor's device, already seen: no lock (a handle lives as long as the process)
+        h = _handles.get(device.index)
+        if h is not None:
+            return h
     if device is None:
         idx = torch.cuda.current_device()
     else:
@@ -49,11 +53,20 @@ def handle(device: torch.device | int | None = None) -> int:
     return h
 
 
+# The raw current stream of a device, without the Stream object (0.2 us against 1.6).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(dev: torch.device) -> int:
+    if _raw_stream is not None and dev.index is not None:
+        return _raw_stream(dev.index)
     return torch.cuda.current_stream(dev).cuda_stream
 
 
 def _need(t: torch.Tensor, name: str, dtype, dev=None):
+    # the passing case in one expression; what it refuses is told apart below
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and (dev is None or t.device == dev) and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
