@@ -205,10 +205,11 @@ int pick_lanes(const hz_handle* h, const int* rp, const int* ci, int n, int64_t 
 // The lane count of a one-system FP64 solve: pick_lanes, except that a
 // matrix whose values exceed half of the 256 MB Infinity Cache (so that every
 // product streams them from HBM) runs the block-tile row loop (L = 1) unless
-// HZ_SPMV_LANES or the autotuner decided for these arrays.  Measured on the
-// 291 MB cabin: 241 against 254 us per BiCGStab iteration, 490 against 556 ms
-// for TFQMR to 1e-10; on the 49 MB cylinder, which stays in the cache, vector
-// rows are faster (48 against 63 us), and complex64 products stay on rows.
+// HZ_SPMV_LANES or the autotuner decided for these arrays.  (Products on CSR
+// only: a Jacobi solve's sliced operator has its own.)  Measured on the 291 MB
+// cabin before the iteration was four kernels: 241 against 254 us per BiCGStab
+// iteration; on the 49 MB cylinder, which stays in the cache, vector rows are
+// faster (48 against 63 us), and complex64 products stay on rows.
 constexpr int64_t kTileSolveBytes = int64_t(128) << 20;
 int solve_lanes(const hz_handle* h, const int* rp, const int* ci, int n, int64_t nnz) {
     bool decided = std::getenv("HZ_SPMV_LANES") != nullptr;
@@ -989,7 +990,8 @@ int level_order(hz_handle* h, hipStream_t s, int n, const int* rp, const int* ci
     for (int L = 1; L <= last; ++L) {
         const int first = off[L], m = off[L + 1] - off[L];
         if (m <= 0) continue;
-        hipLaunchKernelGGL(hz::k_cm_keys, grid1(m), dim3(kBlock), 0, s, m,
+        hipLaunchKernelGGL(hz::k_cm_keys, dim3(unsigned((int64_t(m) * hz::kCmLanes + hz::kCmBlock - 1) / hz::kCmBlock)),
+                           dim3(hz::kCmBlock), 0, s, m,
                            static_cast<const int*>(w.bylevel) + first, rp, ci, static_cast<const int*>(w.level), L,
                            static_cast<const int*>(inv), n, w.ck, w.cv);
         tb = w.tmp_bytes;
@@ -1014,7 +1016,7 @@ int permute_csr(hipStream_t s, int n, int nnz, const int* rp, const int* ci, con
     if (nnz > 0) {
         hipLaunchKernelGGL(hz::k_perm_fill, grid1(int64_t(n) * 8), dim3(kBlock), 0, s, n, rp, ci, v, perm, inv,
                            static_cast<const int*>(rp2), ci2, v2);
-        hipLaunchKernelGGL(hz::k_row_sort<double2>, grid1(n), dim3(kBlock), 0, s, n, static_cast<const int*>(rp2), ci2, v2);
+        hipLaunchKernelGGL(hz::k_row_sort<double2>, hz::row_sort_grid(n), dim3(hz::kSortBlock), 0, s, n, static_cast<const int*>(rp2), ci2, v2);
     }
     HZ_HIP(hipGetLastError());
     return HZ_OK;
@@ -3039,7 +3041,7 @@ int zbicgstab_adjoint(hz_handle* h, hz_stream stream, int n, int nnz, const int*
         hipLaunchKernelGGL(hz::k_scan_1block, dim3(1), dim3(1024), 0, s, n + 1, a.t_rp);
         HZ_HIP(hipMemcpyAsync(a.fill, a.t_rp, sizeof(int) * size_t(n), hipMemcpyDeviceToDevice, s));
         hipLaunchKernelGGL(hz::k_tr_scatter, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, a.fill, a.t_ci, a.t_vals);
-        hipLaunchKernelGGL(hz::k_row_sort<double2>, grid1(n), dim3(kBlock), 0, s, n, static_cast<const int*>(a.t_rp), a.t_ci,
+        hipLaunchKernelGGL(hz::k_row_sort<double2>, hz::row_sort_grid(n), dim3(hz::kSortBlock), 0, s, n, static_cast<const int*>(a.t_rp), a.t_ci,
                            a.t_vals);
         HZ_HIP(hipGetLastError());
         rc = solve_single(h, s, n, nnz, a.t_rp, a.t_ci, a.t_vals, g, lam, rtol, maxiter, sflags, a.solve, info);
@@ -3104,7 +3106,7 @@ int zbicgstab_adjoint_batched(hz_handle* h, hz_stream stream, int nsys, int n, i
         hipLaunchKernelGGL(hz::k_scan_1block, dim3(1), dim3(1024), 0, s, n + 1, a.t_rp);
         HZ_HIP(hipMemcpyAsync(a.fill, a.t_rp, sizeof(int) * size_t(n), hipMemcpyDeviceToDevice, s));
         hipLaunchKernelGGL(hz::k_tr_scatter_idx, grid1(n), dim3(kBlock), 0, s, n, rp, ci, a.fill, a.t_ci, a.t_src);
-        hipLaunchKernelGGL(hz::k_row_sort<int>, grid1(n), dim3(kBlock), 0, s, n, static_cast<const int*>(a.t_rp),
+        hipLaunchKernelGGL(hz::k_row_sort<int>, hz::row_sort_grid(n), dim3(hz::kSortBlock), 0, s, n, static_cast<const int*>(a.t_rp),
                            a.t_ci, a.t_src);
         if (nnz > 0)
             hipLaunchKernelGGL(hz::k_m_conj_vals, grid1(int64_t(nnz) * nsys), dim3(kBlock), 0, s, int64_t(nnz), nsys,

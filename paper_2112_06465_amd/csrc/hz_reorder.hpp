@@ -50,12 +50,20 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(int n, const int* __restri
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         if (level[i] != L) continue;
-        for (int p = rp[i]; p < rp[i + 1]; ++p) {
-            const int j = ci[p];
-            if (level[j] < 0) {
-                level[j] = L + 1;
-                grew = 1;
-            }
+        // eight neighbours at a time, their loads in flight together (one by one: 16 us a step on the cabin, 7.8 so)
+        const int end = rp[i + 1];
+        for (int p = rp[i]; p < end; p += 8) {
+            int j[8], lv[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) j[u] = ci[p + u < end ? p + u : end - 1];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) lv[u] = level[j[u]];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (lv[u] < 0) {
+                    level[j[u]] = L + 1;
+                    grew = 1;
+                }
         }
     }
     if (__syncthreads_or(grew) && threadIdx.x == 0) {
@@ -95,23 +103,30 @@ __global__ __launch_bounds__(kBlock) void k_level_starts(int n, const unsigned* 
 
 // Cuthill-McKee keys of the m nodes of level L (given in index order): the
 // smallest new position pos[u] of a neighbour u on level L - 1 (n when there
-// is none), shifted left by 8, plus the degree capped at 255.
-__global__ __launch_bounds__(kBlock) void k_cm_keys(int m, const int* __restrict__ nodes, const int* __restrict__ rp,
-                                                    const int* __restrict__ ci, const int* __restrict__ level, int L,
-                                                    const int* __restrict__ pos, int n,
-                                                    unsigned long long* __restrict__ key, int* __restrict__ val) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= m) return;
-    const int v = nodes[i];
+// is none), shifted left by 8, plus the degree capped at 255.  A level is small
+// (5,000 nodes of the cabin's 1.24 M), so a node has kCmLanes lanes, a
+// neighbour each (a thread per node: 37 us a level, 4.4 so).
+constexpr int kCmLanes = 16, kCmBlock = 256;
+__global__ __launch_bounds__(kCmBlock) void k_cm_keys(int m, const int* __restrict__ nodes, const int* __restrict__ rp,
+                                                      const int* __restrict__ ci, const int* __restrict__ level, int L,
+                                                      const int* __restrict__ pos, int n,
+                                                      unsigned long long* __restrict__ key, int* __restrict__ val) {
+    const int64_t i = ((int64_t)blockIdx.x * kCmBlock + threadIdx.x) / kCmLanes;
+    if (i >= m) return;  // whole groups of lanes
+    const int v = nodes[i], beg = rp[v], end = rp[v + 1];
     int pmin = n;
-    for (int p = rp[v]; p < rp[v + 1]; ++p) {
+    for (int p = beg + (int)(threadIdx.x % kCmLanes); p < end; p += kCmLanes) {
         const int u = ci[p];
-        if (level[u] == L - 1) {
-            const int q = pos[u];
-            pmin = q < pmin ? q : pmin;
-        }
+        const int lv = level[u], q = pos[u];  // q of a node not yet placed is dropped
+        pmin = lv == L - 1 && q < pmin ? q : pmin;
     }
-    const int deg = rp[v + 1] - rp[v];
+#pragma unroll
+    for (int d = 1; d < kCmLanes; d *= 2) {
+        const int o = __shfl_xor(pmin, d);
+        pmin = o < pmin ? o : pmin;
+    }
+    if (threadIdx.x % kCmLanes != 0) return;
+    const int deg = end - beg;
     key[i] = ((unsigned long long)pmin << 8) | (unsigned long long)(deg < 255 ? deg : 255);
     val[i] = v;
 }
