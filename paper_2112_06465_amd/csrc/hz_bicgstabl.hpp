@@ -29,9 +29,9 @@
 //           r_0 -= sum_j gamma_j r_j; u_0 -= sum_j gamma_j u_j;
 //           partials <r~, r_0>, ||r_0||^2
 // A solve that ends inside a cycle leaves x with the steps that were complete
-// (k_l_late).  Measured, l = 8 on the 260k-row cabin: a cycle 505 -> 344 us,
+// (k_l_late).  Measured, l = 8 on the 260k-row cabin: a cycle 505 -> 337 us,
 // U and R 11.5 -> 5.2 us, gram 19.5 -> 16, mr 22 -> 10, update 15 with the
-// catching up, the products 15 -> 13 us on the sliced operator.
+// catching up, the products 15 -> 12.6 us on the sliced operator.
 // ("A" is the column-scaled matrix under Jacobi, as for BiCGStab.)  rho of
 // global step s = (cycle - 1) l + j lives in rho2[s & 1]: the U-launch of
 // step s reads slot (s - 1) & 1 and writes slot s & 1, which no block of the
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kSpBlock) void k_l_At(const LArgs a) {
     store_sys_partials<2, kTileLanes, 0, kSpBlock>(a.part + a.reg * a.stride, a.stride, q.lb, e);
 }
 
-// and on the sliced operator (15 -> 13 us on the 260k-row cabin).
+// and on the sliced operator (15 -> 12.6 us on the 260k-row cabin).
 template <bool NT>
 __global__ HZ_SLICE_BOUNDS void k_l_As(const LArgs a) {
     const SliceRows q = slice_rows_of(a.one, a.np);

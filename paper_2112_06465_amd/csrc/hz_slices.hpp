@@ -16,8 +16,8 @@
 // The diagonal of A D^{-1} is 1 and is left out, and columns are 16-bit
 // offsets from the slice's first row: 18 bytes for 13.6 entries a row of the
 // P1 meshes plus 1.6-3.2 % padding, instead of 20 bytes for 14.6 entries.
-// Measured: v = A p with its dot product on the 1.24 M-row cabin 82.3 -> 66 us
-// (5.9 TB/s of 390 MB), on the 210k-row cylinder 12.7 -> 9 us.
+// Measured: v = A p with its dot product on the 1.24 M-row cabin 82.3 -> 70 us
+// (5.6 TB/s of 390 MB), on the 210k-row cylinder 12.7 -> 11.3 us.
 //
 // A matrix is not sliced when a column is more than 32,767 rows from its
 // slice, a row has no diagonal, or the padding exceeds the room (irregular
@@ -27,8 +27,8 @@
 // kernels; an asynchronous solve launches both and each returns unless the
 // word is its own (`both`).
 //
-// A row is summed in batches of its entries as stored, added to the diagonal
-// in turn; a padded slot is a zero value at the row's own column.  Batches of slots are
+// A row's entries are summed in the order they are stored, every other one of
+// a batch in a chain of its own, and added to the diagonal; a padded slot is a zero value at the row's own column.  Batches of slots are
 // straight-line (a slot past the slice's width reads its last slot and is
 // dropped by a uniform branch): with the loads themselves behind uniform
 // branches the compiler spilled 60 registers and the product took twice as
@@ -159,15 +159,17 @@ template <bool NT, typename P> __device__ __forceinline__ auto ld_if(const P* p)
 }
 
 // A slice's row sums in batches of U slots, all of a batch's loads issued
-// before any is used, each batch summed by itself: with one chain over the
-// row BiCGstab(8), whose residual drifts by what its products round, ended at
-// a true residual of 3e-11 on the 260k-row cabin (mean of eight systems)
-// instead of 1.5e-11, the tile loop's.  (Issuing the next batch's loads with a batch's gathers
-// gained nothing where it fitted the registers, complex64, and spilled in
-// FP64.)
+// before any is used, in two chains that start at zero, added to the diagonal
+// at the end: with one chain from the diagonal on, BiCGstab(8), whose residual
+// drifts by what its products round, ended at a true residual of 3e-11 on the
+// 260k-row cabin (mean of eight systems) instead of 1.4e-11 (1.8e-11 with the
+// tile loop's sums); a sum per batch drifts as little and took 1-4 % longer.
+// (Issuing the next batch's loads with a batch's gathers gained nothing where
+// it fitted the registers, complex64, and spilled in FP64.)
 template <typename T, int U, bool NT, typename Op>
 __device__ __forceinline__ cx<T> slice_sum(const short* __restrict__ cp, const cx<T>* __restrict__ vp, int base, int w,
                                            cx<T> acc, Op op) {
+    cx<T> even = mk<T>(T(0), T(0)), odd = even;
     for (int k0 = 0; k0 < w; k0 += U) {  // uniform
         short c[U];
         cx<T> v[U], g[U];
@@ -177,13 +179,14 @@ __device__ __forceinline__ cx<T> slice_sum(const short* __restrict__ cp, const c
         for (int u = 0; u < U; ++u) v[u] = ld_if<NT>(vp + (k0 + u < w ? k0 + u : w - 1) * kWave);
 #pragma unroll
         for (int u = 0; u < U; ++u) g[u] = op(base + c[u]);
-        cx<T> b = cmul<T>(v[0], g[0]);
 #pragma unroll
-        for (int u = 1; u < U; ++u)
-            if (k0 + u < w) b = cfma<T>(v[u], g[u], b);  // uniform
-        acc = cx<T>{acc.x + b.x, acc.y + b.y};
+        for (int u = 0; u < U; ++u) {
+            if (k0 + u >= w) continue;  // uniform
+            if (u % 2 == 0) even = cfma<T>(v[u], g[u], even);
+            else odd = cfma<T>(v[u], g[u], odd);
+        }
     }
-    return acc;
+    return mk<T>(acc.x + (even.x + odd.x), acc.y + (even.y + odd.y));
 }
 
 // The offset and width of a wave's first slice, loaded ahead of a kernel's head.

@@ -1,7 +1,8 @@
-// The two row products of the gather-light BiCGStab iteration (Section 7:
-// v = A p with <rhat, v>, and t = A s with <t, s> and ||t||^2) in the
-// standalone product's tile form, for one large system (BiCGstab(l)'s two
-// products, with the same structure, are in hz_bicgstabl.hpp).
+// The two row products of the BiCGStab iteration (Section 7: v = A p with
+// <rhat, v>, and t = A s with its dot products) in the standalone product's
+// tile form, for one large system in CSR: without Jacobi, or with a matrix
+// that is not sliced (BiCGstab(l)'s product, with the same structure, is in
+// hz_bicgstabl.hpp).
 //
 // The solver's other kernels run 1024-thread blocks, at most kMaxGrid of
 // them, and under their 64-VGPR budget a product could not hold its results
@@ -9,8 +10,8 @@
 // loads (one in-order counter tracks both).  These kernels run each logical
 // block of the solver's map as F = sol_subs(G) blocks of kSpBlock threads
 // (half the waves per CU at most, twice the registers per wave) through
-// tile_loop with its LDS ring: the epilogue operands of each row (rhat, or s and rhat) are loaded with the
-// tile's matrix entries and the row's terms go into the block's dot products
+// tile_loop with its LDS ring: the epilogue operands of each row (rhat, or s
+// and rhat) are loaded with the tile's matrix entries and the row's terms go into the block's dot products
 // as soon as the tile is summed, while the totals v (or t) are held for kHold
 // tiles and stored when the ring is flushed.  Sub-block j of logical block lb
 // takes 64-row tiles j, j + F K, ... of its group's rows, and writes its

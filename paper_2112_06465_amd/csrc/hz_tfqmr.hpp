@@ -19,7 +19,7 @@
 // systems K1 runs in K2 and K3 in K4, which then gather two vectors and form
 // u' or u of a column on the fly (choose_fused); the same arithmetic per
 // element.  Measured on the 210k-row cylinder with Jacobi (sliced operator):
-// 49.3 -> 40.2 us an iteration.
+// 49.3 -> 38.7 us an iteration.
 // tau, theta, eta of the end of iteration k live in slot k & 1 of the TFQMR
 // scalars, rho of iteration k in rho2[(k - 1) & 1]: a launch never reads a
 // slot its own leader writes.  K1 reads the iteration number `iter` and
