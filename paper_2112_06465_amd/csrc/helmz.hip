@@ -1456,8 +1456,9 @@ int solve_q(hz_handle* h, hipStream_t s, int n, int nnz, const int* rp, const in
     if (flags & HZ_X0_ZERO) {
         HZ_HIP(hipMemsetAsync(xd, 0, 16 * size_t(n), s));
     } else {
+        // with the caller's matrix: the scaled one may be stored in slices
+        launch_sys_resid<double>(L, m, ba, A, xd, w.t, s);
         if (jacobi) hipLaunchKernelGGL(hz::k_diag_apply<double>, grid1(n), dim3(kBlock), 0, s, n, w.dinv, xd, 1);
-        launch_sys_resid<double>(L, m, ba, Aop, xd, w.t, s);
         rsrc = w.t;
     }
     hipLaunchKernelGGL(hz::k_init<double>, dim3(m.G), dim3(kBlock), 0, s, ba, rsrc);

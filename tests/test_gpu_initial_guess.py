@@ -56,11 +56,12 @@ def solver(hz, name):
             return x, hz.read_info(info)
 
         return run
-    return {"bicgstab": hz.zbicgstab_solve, "bicgstabl": hz.zbicgstabl_solve, "mixed": hz.zbicgstab_solve_mixed}[name]
+    return {"bicgstab": hz.zbicgstab_solve, "bicgstabl": hz.zbicgstabl_solve, "tfqmr": hz.ztfqmr_solve,
+            "mixed": hz.zbicgstab_solve_mixed}[name]
 
 
 @pytest.mark.parametrize("kind", ["sliced", "far", "renumbered"])
-@pytest.mark.parametrize("name", ["bicgstab", "async", "bicgstabl", "mixed"])
+@pytest.mark.parametrize("name", ["bicgstab", "async", "bicgstabl", "tfqmr", "mixed"])
 def test_guess_under_jacobi(hz, name, kind):
     if name == "async" and kind == "renumbered":
         pytest.skip("the asynchronous solve does not renumber")
