@@ -17,6 +17,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <limits>
 #include <type_traits>
 #include <stdint.h>
 
@@ -1420,7 +1421,9 @@ __global__ __launch_bounds__(kBlock) void k_zero_if(const BicgArgs<T> a) {
 
 // dinv_i = 1 / A_ii (the last diagonal entry of the row); flags a missing or
 // zero diagonal and, with no != null, what the sliced operator cannot hold: a
-// column too far from the row's slice, or a row without a diagonal.
+// column too far from the row's slice, a row without a diagonal, or one whose
+// reciprocal is not its inverse (|A_ii|^2 a NaN, or outside the normal range),
+// so that the diagonal of A D^{-1} is not 1.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_jacobi_diag(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                         const cx<T>* __restrict__ vals, cx<T>* __restrict__ dinv,
@@ -1445,6 +1448,8 @@ __global__ __launch_bounds__(kBlock) void k_jacobi_diag(int n, const int* __rest
         return;
     }
     const T q = d.x * d.x + d.y * d.y;
+    using lim = std::numeric_limits<T>;
+    if (no != nullptr && !(q >= lim::min() && q <= lim::max())) *no = 1;
     dinv[i] = mk<T>(d.x / q, -d.y / q);
 }
 

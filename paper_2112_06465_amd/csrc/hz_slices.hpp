@@ -20,8 +20,9 @@
 // (5.6 TB/s of 390 MB), on the 210k-row cylinder 12.7 -> 11.3 us.
 //
 // A matrix is not sliced when a column is more than 32,767 rows from its
-// slice, a row has no diagonal, or the padding exceeds the room (irregular
-// rows): the set-up kernels find that on the device and leave it in the word
+// slice, a row has no diagonal or one without a proper reciprocal
+// (k_jacobi_diag), or the padding exceeds the room (irregular rows): the
+// set-up kernels find that on the device and leave it in the word
 // after the done-counter (slice_no).  The host of a synchronous solve reads
 // it with the set-up's other results and launches one family of product
 // kernels; an asynchronous solve launches both and each returns unless the
