@@ -601,7 +601,7 @@ void enqueue_jacobi(hipStream_t s, int n, int nnz, const int* rp, const int* ci,
     if (room) {
         const int ns = (n + hz::kWave - 1) / hz::kWave;
         const dim3 G((n + hz::kSlBlock - 1) / hz::kSlBlock), B(hz::kSlBlock);
-        hipLaunchKernelGGL(hz::k_slice_width, G, B, 0, s, n, rp, soff);
+        hipLaunchKernelGGL(hz::k_slice_width, G, B, 0, s, n, rp, soff, no);
         hipLaunchKernelGGL(hz::k_slice_scan, dim3(1), dim3(kBlock), 0, s, ns, soff, int64_t(nnz), no);
         hipLaunchKernelGGL((hz::k_slice_fill<TO>), G, B, 0, s, n, rp, ci, A, d, static_cast<const int*>(soff), out,
                            scol, static_cast<const int*>(no));

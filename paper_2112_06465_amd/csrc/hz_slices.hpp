@@ -47,17 +47,26 @@ constexpr int kSlWaves = kSlBlock / kWave;
 
 // ------------------------------------------------------------------ set-up
 
-// off[s + 1] = slots of slice s: 64 x (longest row - 1), off[0] = 0
-__global__ __launch_bounds__(kSlBlock) void k_slice_width(int n, const int* __restrict__ rp, int* __restrict__ off) {
+// off[s + 1] = slots of slice s: 64 x (longest row - 1), off[0] = 0.  A row of
+// more than kSlLongest entries beside the diagonal repeats columns (16 bits
+// tell 65,536 apart) and is not sliced: *no = 1.  So a slice has at most 2^22
+// slots, which an int holds (64 x an arbitrary row length it does not).
+constexpr int kSlLongest = 1 << 16;
+__global__ __launch_bounds__(kSlBlock) void k_slice_width(int n, const int* __restrict__ rp, int* __restrict__ off,
+                                                          int* no) {
     const int64_t i = (int64_t)blockIdx.x * kSlBlock + threadIdx.x;
     int len = i < n ? rp[i + 1] - rp[i] - 1 : 0;
+    if (len > kSlLongest) {
+        *no = 1;  // every writer stores 1
+        len = kSlLongest;
+    }
 #pragma unroll
     for (int s = 1; s < kWave; s *= 2) {
         const int o = __shfl_xor(len, s);
         len = len > o ? len : o;
     }
     if (i == 0) off[0] = 0;
-    if (i < n && threadIdx.x % kWave == 0) off[i / kWave + 1] = kWave * len;  // i / 64 < 2^25
+    if (i < n && threadIdx.x % kWave == 0) off[i / kWave + 1] = kWave * (len > 0 ? len : 0);  // i / 64 < 2^25
 }
 
 // In-place inclusive scan of off[1 .. ns] by one block; *no = 1 if the slots
