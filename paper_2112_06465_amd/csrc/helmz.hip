@@ -1002,10 +1002,7 @@ int level_order(hz_handle* h, hipStream_t s, int n, const int* rp, const int* ci
     for (int L = 1; L <= last; ++L) {
         const int first = off[L], m = off[L + 1] - off[L];
         if (m <= 0) continue;
-        hipLaunchKernelGGL(hz::k_cm_keys, dim3(unsigned((int64_t(m) * hz::kCmLanes + hz::kCmBlock - 1) / hz::kCmBlock)),
-                           dim3(hz::kCmBlock), 0, s, m,
-                           static_cast<const int*>(w.bylevel) + first, rp, ci, static_cast<const int*>(w.level), L,
-                           static_cast<const int*>(inv), n, w.ck, w.cv);
+        hz::cm_keys(s, m, w.bylevel + first, rp, ci, w.level, L, inv, n, w.ck, w.cv);
         tb = w.tmp_bytes;
         HZ_HIP(rocprim::radix_sort_pairs(w.tmp, tb, static_cast<const unsigned long long*>(w.ck), w.ck2,
                                          static_cast<const int*>(w.cv), perm + first, unsigned(m), 0u, kbits, s));
@@ -1028,7 +1025,7 @@ int permute_csr(hipStream_t s, int n, int nnz, const int* rp, const int* ci, con
     if (nnz > 0) {
         hipLaunchKernelGGL(hz::k_perm_fill, grid1(int64_t(n) * 8), dim3(kBlock), 0, s, n, rp, ci, v, perm, inv,
                            static_cast<const int*>(rp2), ci2, v2);
-        hipLaunchKernelGGL(hz::k_row_sort<double2>, hz::row_sort_grid(n), dim3(hz::kSortBlock), 0, s, n, static_cast<const int*>(rp2), ci2, v2);
+        hz::row_sort(s, n, rp2, ci2, v2);
     }
     HZ_HIP(hipGetLastError());
     return HZ_OK;
@@ -3055,8 +3052,7 @@ int zbicgstab_adjoint(hz_handle* h, hz_stream stream, int n, int nnz, const int*
         hipLaunchKernelGGL(hz::k_scan_1block, dim3(1), dim3(1024), 0, s, n + 1, a.t_rp);
         HZ_HIP(hipMemcpyAsync(a.fill, a.t_rp, sizeof(int) * size_t(n), hipMemcpyDeviceToDevice, s));
         hipLaunchKernelGGL(hz::k_tr_scatter, grid1(n), dim3(kBlock), 0, s, n, rp, ci, A, a.fill, a.t_ci, a.t_vals);
-        hipLaunchKernelGGL(hz::k_row_sort<double2>, hz::row_sort_grid(n), dim3(hz::kSortBlock), 0, s, n, static_cast<const int*>(a.t_rp), a.t_ci,
-                           a.t_vals);
+        hz::row_sort(s, n, a.t_rp, a.t_ci, a.t_vals);
         HZ_HIP(hipGetLastError());
         rc = solve_single(h, s, n, nnz, a.t_rp, a.t_ci, a.t_vals, g, lam, rtol, maxiter, sflags, a.solve, info);
         if (rc < 0) return rc;
@@ -3120,8 +3116,7 @@ int zbicgstab_adjoint_batched(hz_handle* h, hz_stream stream, int nsys, int n, i
         hipLaunchKernelGGL(hz::k_scan_1block, dim3(1), dim3(1024), 0, s, n + 1, a.t_rp);
         HZ_HIP(hipMemcpyAsync(a.fill, a.t_rp, sizeof(int) * size_t(n), hipMemcpyDeviceToDevice, s));
         hipLaunchKernelGGL(hz::k_tr_scatter_idx, grid1(n), dim3(kBlock), 0, s, n, rp, ci, a.fill, a.t_ci, a.t_src);
-        hipLaunchKernelGGL(hz::k_row_sort<int>, hz::row_sort_grid(n), dim3(hz::kSortBlock), 0, s, n, static_cast<const int*>(a.t_rp),
-                           a.t_ci, a.t_src);
+        hz::row_sort(s, n, a.t_rp, a.t_ci, a.t_src);
         if (nnz > 0)
             hipLaunchKernelGGL(hz::k_m_conj_vals, grid1(int64_t(nnz) * nsys), dim3(kBlock), 0, s, int64_t(nnz), nsys,
                                static_cast<const int*>(a.t_src), A, a.t_vals);

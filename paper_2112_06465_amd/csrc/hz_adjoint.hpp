@@ -110,11 +110,14 @@ __global__ __launch_bounds__(kBlock) void k_tr_scatter_idx(int n, const int* __r
 // there; longer rows are sorted by insertion, by one lane.  (Insertion in
 // every row, a thread per row, took 3.1 ms on the 1.24 M-row cabin and 0.28 ms
 // on 92k rows; 0.18 and 0.027 so.)
-constexpr int kSortLanes = 16, kSortBlock = 256;
+// A launch holds fewer than 2^32 threads, 2^28 rows of 16 lanes: row_sort
+// launches kSortRows rows at a time, from row j0 on.  (A loop over rows in the
+// kernel took 9 % longer on 1 M rows of 15.)
+constexpr int kSortLanes = 16, kSortBlock = 256, kSortRows = 1 << 24;
 template <typename V>
-__global__ __launch_bounds__(kSortBlock) void k_row_sort(int n, const int* __restrict__ trp, int* tci, V* tv) {
+__global__ __launch_bounds__(kSortBlock) void k_row_sort(int n, int j0, const int* __restrict__ trp, int* tci, V* tv) {
     constexpr int E = 4;
-    const int64_t j = ((int64_t)blockIdx.x * kSortBlock + threadIdx.x) / kSortLanes;
+    const int64_t j = j0 + ((int64_t)blockIdx.x * kSortBlock + threadIdx.x) / kSortLanes;
     const int lane = threadIdx.x % kSortLanes;
     const int lo = j < n ? trp[j] : 0, len = j < n ? trp[j + 1] - lo : 0;
     const bool byrank = len <= E * kSortLanes;
@@ -163,7 +166,13 @@ __global__ __launch_bounds__(kSortBlock) void k_row_sort(int n, const int* __res
         tv[k + 1] = a;
     }
 }
-inline dim3 row_sort_grid(int n) { return dim3(unsigned(((int64_t)n * kSortLanes + kSortBlock - 1) / kSortBlock)); }
+template <typename V> void row_sort(hipStream_t s, int n, const int* trp, int* tci, V* tv) {
+    for (int64_t j0 = 0; j0 < n; j0 += kSortRows) {
+        const int64_t rows = n - j0 < kSortRows ? n - j0 : kSortRows;
+        hipLaunchKernelGGL(k_row_sort<V>, dim3(unsigned((rows * kSortLanes + kSortBlock - 1) / kSortBlock)),
+                           dim3(kSortBlock), 0, s, n, int(j0), trp, tci, tv);
+    }
+}
 
 // out = conj(in); in and out may be the same array
 __global__ __launch_bounds__(kBlock) void k_conj(int n, const double2* in, double2* out) {

@@ -105,13 +105,14 @@ __global__ __launch_bounds__(kBlock) void k_level_starts(int n, const unsigned* 
 // smallest new position pos[u] of a neighbour u on level L - 1 (n when there
 // is none), shifted left by 8, plus the degree capped at 255.  A level is small
 // (5,000 nodes of the cabin's 1.24 M), so a node has kCmLanes lanes, a
-// neighbour each (a thread per node: 37 us a level, 4.4 so).
-constexpr int kCmLanes = 16, kCmBlock = 256;
-__global__ __launch_bounds__(kCmBlock) void k_cm_keys(int m, const int* __restrict__ nodes, const int* __restrict__ rp,
-                                                      const int* __restrict__ ci, const int* __restrict__ level, int L,
+// neighbour each (a thread per node: 37 us a level, 4.4 so).  A launch holds
+// fewer than 2^32 threads: cm_keys launches kCmNodes nodes at a time, from i0 on.
+constexpr int kCmLanes = 16, kCmBlock = 256, kCmNodes = 1 << 24;
+__global__ __launch_bounds__(kCmBlock) void k_cm_keys(int m, int i0, const int* __restrict__ nodes,
+                                                      const int* __restrict__ rp, const int* __restrict__ ci, const int* __restrict__ level, int L,
                                                       const int* __restrict__ pos, int n,
                                                       unsigned long long* __restrict__ key, int* __restrict__ val) {
-    const int64_t i = ((int64_t)blockIdx.x * kCmBlock + threadIdx.x) / kCmLanes;
+    const int64_t i = i0 + ((int64_t)blockIdx.x * kCmBlock + threadIdx.x) / kCmLanes;
     if (i >= m) return;  // whole groups of lanes
     const int v = nodes[i], beg = rp[v], end = rp[v + 1];
     int pmin = n;
@@ -129,6 +130,15 @@ __global__ __launch_bounds__(kCmBlock) void k_cm_keys(int m, const int* __restri
     const int deg = end - beg;
     key[i] = ((unsigned long long)pmin << 8) | (unsigned long long)(deg < 255 ? deg : 255);
     val[i] = v;
+}
+
+inline void cm_keys(hipStream_t s, int m, const int* nodes, const int* rp, const int* ci, const int* level, int L,
+                    const int* pos, int n, unsigned long long* key, int* val) {
+    for (int64_t i0 = 0; i0 < m; i0 += kCmNodes) {
+        const int64_t count = m - i0 < kCmNodes ? m - i0 : kCmNodes;
+        hipLaunchKernelGGL(k_cm_keys, dim3(unsigned((count * kCmLanes + kCmBlock - 1) / kCmBlock)), dim3(kCmBlock), 0, s,
+                           m, int(i0), nodes, rp, ci, level, L, pos, n, key, val);
+    }
 }
 
 // pos[order[i]] = first + i for the m nodes just placed
