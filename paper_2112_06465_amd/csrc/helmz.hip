@@ -23,6 +23,7 @@
 #include "hz_spmv.hpp"
 #include "hz_soltile.hpp"
 #include "hz_slices.hpp"
+#include "hz_either.hpp"
 #include "hz_bicgstabl.hpp"
 #include "hz_tfqmr.hpp"
 #include "hz_formats.hpp"
@@ -406,9 +407,17 @@ int enqueue_far_count(hz_handle* h, hipStream_t s, int n, const int* rp, const i
 // 22.3, 125,885 rows 25.8 / 27.6, 209,777 rows 41.1 / 38.1.  TFQMR: CSR, 24,353
 // rows 18.4 / 19.0, 57,005 rows 21.5 / 21.3, 125,885 rows 33.6 / 31.6; sliced,
 // 57,005 rows 14.6 / 19.2, 163,401 rows 31.8 / 33.8, 209,777 rows 44.4 / 40.1.
+// Complex64 (mixed solves) has the same lines: CSR, 31,429 rows 15.6 / 17.2,
+// 67,689 rows 24.6 / 22.4; sliced, 108,945 rows 20.0 / 21.2, 163,401 rows 24.0 /
+// 24.3, 209,777 rows 28.3 / 28.2.  An asynchronous solve on vector rows, where
+// the two give the same bits, is fused up to 131,072 rows in CSR too: it runs its
+// limit of iterations, and those past the end take 4.9 us in three launches and
+// 6.5 in four, against 24.7 / 22.3 (67,689 rows) and 31.8 / 28.9 (108,945 rows)
+// before it.
 // `rows` is the total over the systems of a launch.  HZ_FUSED=0/1 overrides.
 constexpr int64_t kFusedMaxRows = 57344;
 constexpr int64_t kFusedMaxRowsSliced = 163840;
+constexpr int64_t kFusedMaxRowsAsync = 131072;
 bool choose_fused(const hz_handle*, int64_t rows, int64_t most = kFusedMaxRows) {
     if (const char* env = std::getenv("HZ_FUSED")) return std::atoi(env) != 0;
     return rows <= most;
@@ -624,7 +633,7 @@ template <typename T> bool slice_stream(int64_t nnz) { return int64_t(sizeof(cx<
 enum ProdForm : int {
     PF_CSR = 0,     // on the CSR operator (vector rows or tiles)
     PF_SLICED = 1,  // on the sliced operator
-    PF_BOTH = 2     // both, each of which runs if the operator is its own (asynchronous solves)
+    PF_EITHER = 2   // on the one that the operator has, chosen on the device (asynchronous solves)
 };
 
 // The gather-light CSR products of a one-system solve on the block-tile row
@@ -641,56 +650,64 @@ struct IterPlan {
 };
 
 template <typename T>
-IterPlan iter_plan(const hz_handle* h, const WorkMap& m, int L, int n, ProdForm form, int64_t nnz) {
-    const bool fused = choose_fused(h, n);
-    return IterPlan{L, fused, sub_products<T>(m, L, fused), choose_fused(h, n, kFusedMaxRowsSliced),
-                    slice_stream<T>(nnz), form};
+IterPlan iter_plan(const hz_handle* h, const WorkMap& m, int L, int n, ProdForm form, int64_t nnz, bool async = false) {
+    // (an asynchronous solve's fused sliced product holds byte offsets of vector elements in 32 bits)
+    const bool may = !async || n < (1 << 28);
+    const bool fused = may && choose_fused(h, n, async && L > 1 ? kFusedMaxRowsAsync : kFusedMaxRows);
+    const bool fused_s = may && choose_fused(h, n, kFusedMaxRowsSliced);
+    return IterPlan{L, fused, sub_products<T>(m, L, fused), fused_s, slice_stream<T>(nnz), form};
 }
 
 // The kernels' arguments under a plan: the products' blocks and partial slots.
 template <typename T> hz::BicgArgs<T> iteration_args(const WorkMap& m, hz::BicgArgs<T> a, const IterPlan& ip) {
     a.pf = ip.sub ? hz::sol_subs(m.G) : 1;
-    a.both = ip.form == PF_BOTH;
-    a.s_csr = a.both && ip.fused_s;
+    a.either = ip.form == PF_EITHER;
+    a.s_csr = a.either && ip.fused_s;
     const int csr = a.pf * m.G;
     a.sg = m.nsys == 1 ? slice_grid(m.one) : 0;
+    a.sv = hz::either_share(a.sg);
     a.np = ip.form == PF_CSR ? csr : (ip.form == PF_SLICED ? a.sg : std::max(csr, a.sg));
     return a;
 }
 
 // One iteration on stream q: A, B, C with s formed in B (fused), or A, S, B, C.
-// (Both families: the sliced one may be fused where the CSR one is not, never
+// (Either form: the sliced one may be fused where the CSR one is not, never
 // the reverse, and the S-kernel is then for the CSR one only.)
-template <typename T, int LL, int UU>
+template <typename T, int LL, int UU, bool PAST = false>
 void enqueue_iteration(hipStream_t q, const WorkMap& m, const hz::BicgArgs<T>& a, const IterPlan& ip) {
-    const dim3 G(m.G), B(kBlock);
-    const bool csr = ip.form != PF_SLICED, sl = ip.form != PF_CSR;
-    const dim3 SG(a.sg), SB(hz::kSlBlock);
-    if (csr) {
-        if (ip.sub)
-            hipLaunchKernelGGL((hz::k_bicg_At<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
-        else
-            hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU>), G, B, 0, q, a);
-    }
-    if (sl) {
+    const dim3 G(m.G), B(kBlock), SG(a.sg), SB(hz::kSlBlock), TG(a.pf * m.G), TB(hz::kSpBlock);
+    if (ip.form == PF_SLICED) {  // (never asynchronous)
         if (ip.nt) hipLaunchKernelGGL((hz::k_bicg_As<T, true>), SG, SB, 0, q, a);
         else hipLaunchKernelGGL((hz::k_bicg_As<T, false>), SG, SB, 0, q, a);
+        if (ip.fused_s) {
+            hipLaunchKernelGGL((hz::k_bicg_SBs<T>), SG, SB, 0, q, a);
+        } else {
+            hipLaunchKernelGGL((hz::k_bicg_S<T>), G, B, 0, q, a);
+            if (ip.nt) hipLaunchKernelGGL((hz::k_bicg_Bs<T, true>), SG, SB, 0, q, a);
+            else hipLaunchKernelGGL((hz::k_bicg_Bs<T, false>), SG, SB, 0, q, a);
+        }
+    } else if (ip.form == PF_CSR) {
+        if (ip.sub) hipLaunchKernelGGL((hz::k_bicg_At<T, PAST>), TG, TB, 0, q, a);
+        else hipLaunchKernelGGL((hz::k_bicg_A<T, LL, UU, PAST>), G, B, 0, q, a);
+        if (ip.fused) {
+            hipLaunchKernelGGL((hz::k_bicg_SB<T, LL, UU, PAST>), G, B, 0, q, a);
+        } else {
+            hipLaunchKernelGGL((hz::k_bicg_S<T, PAST>), G, B, 0, q, a);
+            if (ip.sub) hipLaunchKernelGGL((hz::k_bicg_Bt<T, PAST>), TG, TB, 0, q, a);
+            else hipLaunchKernelGGL((hz::k_bicg_B<T, LL, UU, PAST>), G, B, 0, q, a);
+        }
+    } else if constexpr (PAST) {
+        const dim3 XG(hz::either_grid(m.one, a.sg, a.sv, m.G)), XT(hz::either_grid(m.one, a.sg, 1, a.pf * m.G));
+        if (ip.sub) hipLaunchKernelGGL((hz::k_bicg_Atx<T>), XT, TB, 0, q, a);
+        else hipLaunchKernelGGL((hz::k_bicg_Ax<T, LL, UU>), XG, B, 0, q, a);
+        if (!ip.fused) hipLaunchKernelGGL((hz::k_bicg_S<T, PAST>), G, B, 0, q, a);
+        if (ip.fused) hipLaunchKernelGGL((hz::k_bicg_SBx<T, LL, UU>), XG, B, 0, q, a);
+        else if (ip.sub && ip.fused_s) hipLaunchKernelGGL((hz::k_bicg_Btx<T, true>), XT, TB, 0, q, a);
+        else if (ip.sub) hipLaunchKernelGGL((hz::k_bicg_Btx<T, false>), XT, TB, 0, q, a);
+        else if (ip.fused_s) hipLaunchKernelGGL((hz::k_bicg_Bx<T, LL, UU, true>), XG, B, 0, q, a);
+        else hipLaunchKernelGGL((hz::k_bicg_Bx<T, LL, UU, false>), XG, B, 0, q, a);
     }
-    if ((csr && !ip.fused) || (sl && !ip.fused_s)) hipLaunchKernelGGL((hz::k_bicg_S<T>), G, B, 0, q, a);
-    if (csr) {
-        if (ip.fused)
-            hipLaunchKernelGGL((hz::k_bicg_SB<T, LL, UU>), G, B, 0, q, a);
-        else if (ip.sub)
-            hipLaunchKernelGGL((hz::k_bicg_Bt<T>), dim3(a.pf * m.G), dim3(hz::kSpBlock), 0, q, a);
-        else
-            hipLaunchKernelGGL((hz::k_bicg_B<T, LL, UU>), G, B, 0, q, a);
-    }
-    if (sl) {
-        if (ip.fused_s) hipLaunchKernelGGL((hz::k_bicg_SBs<T>), SG, SB, 0, q, a);
-        else if (ip.nt) hipLaunchKernelGGL((hz::k_bicg_Bs<T, true>), SG, SB, 0, q, a);
-        else hipLaunchKernelGGL((hz::k_bicg_Bs<T, false>), SG, SB, 0, q, a);
-    }
-    hipLaunchKernelGGL((hz::k_bicg_C<T>), G, B, 0, q, a);
+    hipLaunchKernelGGL((hz::k_bicg_C<T, PAST>), G, B, 0, q, a);
 }
 
 // The iteration loop of BiCGStab on the (possibly column-scaled) matrix in
@@ -707,7 +724,8 @@ int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>
     while (launched < maxiter) {
         const int k_n = (maxiter - launched) < poll ? (maxiter - launched) : poll;
         const bool tail = launched + k_n == maxiter;
-        const int family = (ip.fused ? 1 : 2) + (sizeof(T) == 4 ? 10 : 0) + 1000 * ip.form + (ip.fused_s ? 5000 : 0);
+        const int family = (ip.fused ? 1 : 2) + (sizeof(T) == 4 ? 10 : 0) + 1000 * ip.form + (ip.fused_s ? 5000 : 0) +
+                           (poll_done ? 0 : 10000);
         auto chunk = [&](auto&& record) {
             if (graphs) return launch_chunk(h, s, chunk_key(family, L, k_n, tail, a), record);
             record(s);  // direct launches: no graph is captured or instantiated (nothing allocated)
@@ -715,7 +733,15 @@ int iterate(hz_handle* h, hipStream_t s, const WorkMap& m, const hz::BicgArgs<T>
         };
         int rc = chunk([&](hipStream_t q) {
             with_lanes(L, [&]<int LL, int UU>() {
-                for (int k = 0; k < k_n; ++k) enqueue_iteration<T, LL, UU>(q, m, a, ip);
+                for (int k = 0; k < k_n; ++k) {
+                    if constexpr (std::is_same_v<T, double>) {
+                        if (!poll_done) {
+                            enqueue_iteration<T, LL, UU, true>(q, m, a, ip);
+                            continue;
+                        }
+                    }
+                    enqueue_iteration<T, LL, UU>(q, m, a, ip);
+                }
             });
             if (tail) hipLaunchKernelGGL((hz::k_bicg_end<T>), dim3(m.nsys), dim3(kBlock), 0, q, a);
         });
@@ -818,7 +844,7 @@ int solve_fp64(hz_handle* h, hipStream_t s, int nsys, const int* row_off, int nn
     hipLaunchKernelGGL(hz::k_fin_init<double>, dim3(nsys), dim3(kBlock), 0, s, a);
     HZ_HIP(hipGetLastError());
     if (async) {
-        rc = iterate<double>(h, s, m, a, iter_plan<double>(h, m, L, n, w.soff ? PF_BOTH : PF_CSR, nnz),
+        rc = iterate<double>(h, s, m, a, iter_plan<double>(h, m, L, n, w.soff ? PF_EITHER : PF_CSR, nnz, true),
                              maxiter, false, !direct);
         if (rc) return rc;
         hipLaunchKernelGGL(hz::k_zero_if<double>, dim3(m.G), dim3(kBlock), 0, s, a);

@@ -293,7 +293,7 @@ __global__ HZ_SLICE_BOUNDS void k_l_As(const LArgs a) {
             e[0] = c.x;
             e[1] = c.y;
         });
-    slice_store<2>(a.part + a.reg * a.stride + q.lb, a.stride, e);
+    slice_store<2>(a.part + a.reg * a.stride, a.stride, q.lb, e);
 }
 
 // An element's r_0 .. r_{l-1} and u_0 .. u_{l-1}, as their own steps left

@@ -599,6 +599,7 @@ struct alignas(256) SolverScal {
     int bad_diag;  // Jacobi requested with a zero diagonal entry
     int pending;   // half-step exit taken in iteration `pending`; the next first kernel concludes
     int why;       // for a breakdown: which scalar vanished (BD_*)
+    int closed;    // 1 once an A-kernel has seen done (asynchronous solves; past_end)
 };
 
 enum : int { ST_OK = 0, ST_NOT_CONVERGED = 1, ST_BREAKDOWN = 2, ST_NONFINITE = 3 };
@@ -644,11 +645,11 @@ template <typename T> struct BicgArgs {
     int stride;  // partial component stride (>= np)
     int pf = 1;  // product blocks per block of the map (sol_subs(G) when the products run as sub-blocks)
     OneMap one;
-    int np = 0;    // one system: partial slots that the products write (regions A and B)
-    int sg = 0;    // blocks of the sliced products
-    int both = 0;  // both families of product kernels are launched: run only on the operator's own form
-    int s_csr = 0;  // the S-kernel runs for the CSR operator only (both families, the sliced one fused)
-    int spare = 0;
+    int np = 0;      // one system: partial slots that the products write (regions A and B)
+    int sg = 0;      // blocks of the sliced products
+    int either = 0;  // the products choose the operator's form on the device
+    int sv = 1;      // blocks of the sliced form that one block of theirs stands for
+    int s_csr = 0;   // the S-kernel runs for the CSR operator only (either form, the sliced one fused)
     // (no padding bytes: the graph cache compares these structs bytewise)
     const BlockMap* bmap;
     const SysMap* smap;
@@ -719,15 +720,11 @@ template <typename T> __device__ __forceinline__ int prod_parts(const BicgArgs<T
 }
 // The word after the done-counter: 1 if the operator is not sliced.
 __device__ __forceinline__ int* slice_no(int* ndone) { return ndone + 1; }
-// Whether a CSR product kernel has nothing to do, the operator being sliced.
-template <typename A> __device__ __forceinline__ bool not_csr(const A& a) {
-    return a.both != 0 && *slice_no(a.ndone) == 0;
-}
-// A product of `cnt` blocks where both families are launched: zeros to the
-// slots past its own that the readers also add.
+// A product of `cnt` blocks where either form may run: zeros to the slots past
+// its own that the readers also add.
 template <typename A>
-__device__ __forceinline__ void zero_slots(const A& a, int region, int K, int lb, int cnt) {
-    if (a.both == 0 || threadIdx.x != 0) return;
+__device__ __forceinline__ void zero_slots(const A& a, int region, int K, int lb, int cnt, bool first) {
+    if (a.either == 0 || !first) return;
     for (int g = lb + cnt; g < a.np; g += cnt)
         for (int k = 0; k < K; ++k) a.part[(region + k) * a.stride + g] = 0.0;
 }
@@ -1070,16 +1067,34 @@ template <typename T> __global__ HZ_STREAM_BOUNDS void k_bicg_end(const BicgArgs
     if (st >= 0) finish(sc, a.ndone, st, sit, why);
 }
 
+// PAST kernels (asynchronous solves) first ask whether the solve's end lies
+// behind them: such a call launches its limit of iterations, most of them past
+// the end as a rule, and a block with loads in flight stays until they return.
+// An iteration past the end takes 4.8 us in three launches (up to 131,072
+// rows) and 6.5 us in four; without the question, and with one launch for each
+// form of a product, 9.3 to 18 us.  In a synchronous solve, which stops within a
+// chunk, the question costs 0.2 us of a small iteration.  (`done` would not do:
+// S, SB and C set it themselves, and waves that return on it would be missing
+// at the barriers of waves that have read it before.)
+template <bool PAST, typename T> __device__ __forceinline__ bool past_end(const BicgArgs<T>& a) {
+    if constexpr (PAST) return a.sc->closed != 0;
+    else return false;
+}
+// Whether an A-kernel, which is no part of deciding the end, has nothing to do.
+template <bool PAST> __device__ __forceinline__ bool ended(SolverScal* sc, bool leader) {
+    const int done = sc->done;
+    if (PAST && done != 0 && leader) sc->closed = 1;
+    return done != 0 || sc->pending != 0;
+}
+
 // v = A p; partial <rhat, v>
-template <typename T, int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_bicg_A(const BicgArgs<T> a) {
+template <typename T, int L, int U, bool PAST> __device__ __forceinline__ void bicg_A(const BicgArgs<T>& a) {
     const SysBlock q = sys_block(a);
     if (q.sys < 0) return;
     FirstRow<T, 0> f;
     first_row<T, L, 0>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
-    const SolverScal* sc = a.sc + q.sys;
-    if (sc->done || sc->pending || not_csr(a)) return;
-    zero_slots(a, kPartA, 2, q.lb, a.G);
+    if (ended<PAST>(a.sc + q.sys, sys_leader(q))) return;
+    zero_slots(a, kPartA, 2, q.lb, a.G, threadIdx.x == 0);
     const cx<T>* __restrict__ p = a.p;
     cx<T>* __restrict__ v = a.v;
     const cx<T>* __restrict__ rh = a.rh;
@@ -1095,12 +1110,17 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_A(const BicgArgs<T> a) {
         [rh](int64_t row) { return rh[row]; });
     store_sys_partials<2, epi_stride(L)>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
+template <typename T, int L, int U, bool PAST = false>
+__global__ HZ_STREAM_BOUNDS void k_bicg_A(const BicgArgs<T> a) {
+    if (!past_end<PAST>(a)) bicg_A<T, L, U, PAST>(a);
+}
 
 // s = r - alpha v
-template <typename T>
+template <typename T, bool PAST = false>
 __global__ HZ_STREAM_BOUNDS void k_bicg_S(const BicgArgs<T> a) {
+    if (past_end<PAST>(a)) return;
     const SysBlock q = sys_block(a);
-    if (q.sys < 0 || (a.s_csr && not_csr(a))) return;
+    if (q.sys < 0 || (a.s_csr && *slice_no(a.ndone) == 0)) return;
     AlphaHead<> hd;
     hd.load(a, q);
     const cx<T>* __restrict__ v = a.v;
@@ -1150,14 +1170,13 @@ template <typename T> struct BRow {
 };
 
 // t = A s and its dot products
-template <typename T, int L, int U>
-__global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
+template <typename T, int L, int U> __device__ __forceinline__ void bicg_B(const BicgArgs<T>& a) {
     const SysBlock q = sys_block(a);
     if (q.sys < 0) return;
     FirstRow<T, 0> f;
     first_row<T, L, 0>(f, q.rw, a.row_ptr, a.col_idx, a.vals);
-    if (a.sc[q.sys].done || not_csr(a)) return;
-    zero_slots(a, kPartB, 8, q.lb, a.G);
+    if (a.sc[q.sys].done) return;
+    zero_slots(a, kPartB, 8, q.lb, a.G, threadIdx.x == 0);
     const cx<T>* __restrict__ sv = a.s;
     const cx<T>* __restrict__ rh = a.rh;
     cx<T>* __restrict__ tv = a.t;
@@ -1171,15 +1190,18 @@ __global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
         [sv, rh](int64_t row) { return BRow<T>{sv[row], rh[row]}; });
     store_sys_partials<8, epi_stride(L)>(a.part + kPartB * a.stride, a.stride, q.lb, e);
 }
+template <typename T, int L, int U, bool PAST = false>
+__global__ HZ_STREAM_BOUNDS void k_bicg_B(const BicgArgs<T> a) {
+    if (!past_end<PAST>(a)) bicg_B<T, L, U>(a);
+}
 
 // The same with the S-kernel's head: s = r - alpha v is formed for every
 // gathered column and stored.  One block per CU: the head, the prefetched
 // entries and eight sums need more than the 64 registers of two.
-template <typename T, int L, int U>
-__global__ __launch_bounds__(kBlock) void k_bicg_SB(const BicgArgs<T> a) {
+template <typename T, int L, int U> __device__ __forceinline__ void bicg_SB(const BicgArgs<T>& a) {
     const SysBlock q = sys_block(a);
-    if (q.sys < 0 || not_csr(a)) return;
-    zero_slots(a, kPartB, 8, q.lb, a.G);
+    if (q.sys < 0) return;
+    zero_slots(a, kPartB, 8, q.lb, a.G, threadIdx.x == 0);
     AlphaHead<> hd;
     hd.load(a, q);
     FirstRow<T, U> f;
@@ -1204,6 +1226,10 @@ __global__ __launch_bounds__(kBlock) void k_bicg_SB(const BicgArgs<T> a) {
         [=](int64_t row) { return BRow<T>{scol((int)row), rh[row]}; });
     store_sys_partials<8, epi_stride(L)>(a.part + kPartB * a.stride, a.stride, q.lb, e);
 }
+template <typename T, int L, int U, bool PAST = false>
+__global__ __launch_bounds__(kBlock) void k_bicg_SB(const BicgArgs<T> a) {
+    if (!past_end<PAST>(a)) bicg_SB<T, L, U>(a);
+}
 
 // p_{i+1} = r_{i+1} + beta (p_i - omega v_i)
 template <typename T>
@@ -1212,12 +1238,13 @@ __device__ __forceinline__ cx<T> p_update(cx<T> bt, cx<T> omt, cx<T> rc, cx<T> p
     return cfma<T>(bt, d, rc);
 }
 
-template <typename T>
+template <typename T, bool PAST = false>
 __global__ HZ_STREAM_BOUNDS void k_bicg_C(const BicgArgs<T> a) {
     enum : int { STOP = 0, HALF = 1, FULL = 2 };
     __shared__ double tot[kBlock / kWave];
     __shared__ double2 coef[3];  // alpha, omega, beta
     __shared__ int mode;
+    if (past_end<PAST>(a)) return;
     const SysBlock q = sys_block(a);
     if (q.sys < 0) return;
     SolverScal* sc = a.sc + q.sys;
@@ -1382,6 +1409,7 @@ __global__ __launch_bounds__(kBlock) void k_fin_init(const BicgArgs<T> a) {
     sc->zero_x = 0;
     sc->iters = 0;
     sc->pending = 0;
+    sc->closed = 0;
     sc->why = BD_NONE;
     sc->status = ST_NOT_CONVERGED;
     sc->alpha = sc->omega = sc->beta = mk<double>(1.0, 0.0);

@@ -24,9 +24,9 @@
 // (k_jacobi_diag), or the padding exceeds the room (irregular rows): the
 // set-up kernels find that on the device and leave it in the word
 // after the done-counter (slice_no).  The host of a synchronous solve reads
-// it with the set-up's other results and launches one family of product
-// kernels; an asynchronous solve launches both and each returns unless the
-// word is its own (`both`).
+// it with the set-up's other results and launches one form's product kernels;
+// an asynchronous solve's contain both forms and read the word themselves
+// (hz_either.hpp).
 //
 // A row's entries are summed in the order they are stored, every other one of
 // a batch in a chain of its own, and added to the diagonal; a padded slot is a zero value at the row's own column.  Batches of slots are
@@ -147,19 +147,27 @@ template <typename T> struct Sliced {
 
 // The rows of a block of a launch of `sg` sliced product blocks over the
 // one-system map: group x's blocks take its slices four at a time in turn.
+// A kernel of TB > kSlBlock threads does the work of V <= TB / kSlBlock such
+// blocks in each of its own (lb < 0: threads beyond, and past the group's last).
 struct SliceRows {
     int lb;              // the block's partial slot
     int64_t s, step, s1; // this wave's first slice, the step, the group's end
 };
-__device__ __forceinline__ SliceRows slice_rows_of(const OneMap& one, int sg) {
+template <int TB = kSlBlock> __device__ __forceinline__ SliceRows slice_rows_of(const OneMap& one, int sg, int V = 1) {
+    constexpr bool many = TB > kSlBlock;
     SliceRows q;
-    const int b = blockIdx.x, x = one.groups == kXcd ? b % kXcd : 0, k = one.groups == kXcd ? b / kXcd : b;
+    const int b = blockIdx.x, x = one.groups == kXcd ? b % kXcd : 0, v = many ? wave_id() / kSlWaves : 0;
+    const int k = (one.groups == kXcd ? b / kXcd : b) * (many ? V : 1) + v;
     const int K = sg / one.groups;
     const int64_t x0 = (int64_t)x * one.gr, x1 = x0 + one.gr < one.n ? x0 + one.gr : one.n;
     q.lb = x * K + k;
-    q.s = x0 / kWave + (int64_t)k * kSlWaves + wave_id();
+    q.s = x0 / kWave + (int64_t)k * kSlWaves + wave_id() % kSlWaves;
     q.step = (int64_t)K * kSlWaves;
     q.s1 = (x1 + kWave - 1) / kWave;
+    if (many && (v >= V || k >= K)) {
+        q.lb = -1;
+        q.s = q.s1;
+    }
     return q;
 }
 
@@ -245,24 +253,30 @@ __device__ __forceinline__ void slice_rows(const Sliced<T>& m, const SliceRows& 
     }
 }
 
-// The block's totals of K doubles to out[k * stride], summed through LDS (the
-// values of 256 threads per component, then one wave per component at a time):
-// with every row in a lane of its own the wave butterflies of eight sums would
-// take about 1 us of the SIMDs.
-template <int K>
-__device__ __forceinline__ void slice_store(double* __restrict__ out, int stride, double (&e)[K]) {
-    __shared__ double l[K][kSlBlock];
-    const int lane = threadIdx.x % kWave, w = wave_id();
+// The block's totals of K doubles to slot lb of each component, summed through
+// LDS (the values of 256 threads per component, then one wave per component at
+// a time): with every row in a lane of its own the wave butterflies of eight
+// sums would take about 1 us of the SIMDs.  PASS components at a time are in
+// LDS; TB > kSlBlock: for each of a thread block's blocks.
+template <int K, int TB = kSlBlock, int PASS = K>
+__device__ __forceinline__ void slice_store(double* __restrict__ part, int stride, int lb, double (&e)[K]) {
+    constexpr int V = TB / kSlBlock;
+    __shared__ double l[V][PASS][kSlBlock];
+    const int lane = threadIdx.x % kWave, w = wave_id() % kSlWaves, v = V > 1 ? wave_id() / kSlWaves : 0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) l[k][threadIdx.x] = e[k];
-    __syncthreads();
+    for (int p0 = 0; p0 < K; p0 += PASS) {
+        if (p0 > 0) __syncthreads();  // l may be rewritten
 #pragma unroll
-    for (int k0 = 0; k0 < K; k0 += kSlWaves) {
-        const int k = k0 + w;
-        if (k < K) {
-            const double* p = l[k] + lane;
-            const double t = wave_sum<1>((p[0] + p[kWave]) + (p[2 * kWave] + p[3 * kWave]));
-            if (lane == 0) out[k * stride] = t;
+        for (int k = p0; k < p0 + PASS && k < K; ++k) l[v][k - p0][threadIdx.x % kSlBlock] = e[k];
+        __syncthreads();
+#pragma unroll
+        for (int k0 = p0; k0 < p0 + PASS && k0 < K; k0 += kSlWaves) {
+            const int k = k0 + w;
+            if (k < K && k < p0 + PASS && (V == 1 || lb >= 0)) {
+                const double* p = l[v][k - p0] + lane;
+                const double t = wave_sum<1>((p[0] + p[kWave]) + (p[2 * kWave] + p[3 * kWave]));
+                if (lane == 0) part[k * stride + lb] = t;
+            }
         }
     }
 }
@@ -272,19 +286,16 @@ __device__ __forceinline__ void slice_store(double* __restrict__ out, int stride
 template <typename T> __device__ __forceinline__ Sliced<T> sliced_of(const BicgArgs<T>& a) {
     return Sliced<T>{a.soff, a.scol, a.vals};
 }
-// Whether a sliced product kernel has nothing to do.
-template <typename A> __device__ __forceinline__ bool not_sliced(const A& a) {
-    return a.both != 0 && *slice_no(a.ndone) != 0;
-}
+// The first thread of a block (zero_slots).
+__device__ __forceinline__ bool slice_first(const SliceRows& q) { return threadIdx.x % kSlBlock == 0 && q.lb >= 0; }
 
 // v = A p; partial <rhat, v>
-template <typename T, bool NT>
-__global__ HZ_SLICE_BOUNDS void k_bicg_As(const BicgArgs<T> a) {
-    const SliceRows q = slice_rows_of(a.one, a.sg);
+template <typename T, bool NT, bool PAST = false, int TB = kSlBlock, int PASS = 2>
+__device__ __forceinline__ void bicg_As(const BicgArgs<T>& a) {
+    const SliceRows q = slice_rows_of<TB>(a.one, a.sg, a.sv);
     const FirstSlice f = first_slice(sliced_of(a), q);
-    const SolverScal* sc = a.sc;
-    if (sc->done || sc->pending || not_sliced(a)) return;
-    zero_slots(a, kPartA, 2, q.lb, a.sg);
+    if (ended<PAST>(a.sc, q.lb == 0 && threadIdx.x == 0)) return;
+    zero_slots(a, kPartA, 2, q.lb, a.sg, slice_first(q));
     const cx<T>* __restrict__ p = a.p;
     const cx<T>* __restrict__ rh = a.rh;
     cx<T>* __restrict__ v = a.v;
@@ -297,16 +308,20 @@ __global__ HZ_SLICE_BOUNDS void k_bicg_As(const BicgArgs<T> a) {
             e[0] = c.x;
             e[1] = c.y;
         });
-    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+    slice_store<2, TB, PASS>(a.part + kPartA * a.stride, a.stride, q.lb, e);
+}
+template <typename T, bool NT>
+__global__ HZ_SLICE_BOUNDS void k_bicg_As(const BicgArgs<T> a) {
+    bicg_As<T, NT>(a);
 }
 
 // t = A s and its dot products
-template <typename T, bool NT>
-__global__ HZ_SLICE_BOUNDS void k_bicg_Bs(const BicgArgs<T> a) {
-    const SliceRows q = slice_rows_of(a.one, a.sg);
+template <typename T, bool NT, int TB = kSlBlock, int PASS = 8>
+__device__ __forceinline__ void bicg_Bs(const BicgArgs<T>& a) {
+    const SliceRows q = slice_rows_of<TB>(a.one, a.sg, a.sv);
     const FirstSlice f = first_slice(sliced_of(a), q);
-    if (a.sc->done || not_sliced(a)) return;
-    zero_slots(a, kPartB, 8, q.lb, a.sg);
+    if (a.sc->done) return;
+    zero_slots(a, kPartB, 8, q.lb, a.sg, slice_first(q));
     const cx<T>* __restrict__ sv = a.s;
     const cx<T>* __restrict__ rh = a.rh;
     cx<T>* __restrict__ tv = a.t;
@@ -317,18 +332,31 @@ __global__ HZ_SLICE_BOUNDS void k_bicg_Bs(const BicgArgs<T> a) {
             tv[row] = acc;
             b_terms<T>(e, s, acc, w);
         });
-    slice_store<8>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+    slice_store<8, TB, PASS>(a.part + kPartB * a.stride, a.stride, q.lb, e);
+}
+template <typename T, bool NT>
+__global__ HZ_SLICE_BOUNDS void k_bicg_Bs(const BicgArgs<T> a) {
+    bicg_Bs<T, NT>(a);
+}
+
+// p[i]; N32: by a byte offset of 32 bits (i below 2^32 / sizeof), one register
+// an address, for the kernels that may have no more than 128 of them (64-bit
+// addresses of two vectors' gathers take a batch of 7 to 136).  Where there is
+// no such limit 64-bit ones are 1 % faster.
+template <bool N32, typename P> __device__ __forceinline__ P& at(P* __restrict__ p, int i) {
+    if constexpr (!N32) return p[i];
+    using B = std::conditional_t<std::is_const_v<P>, const char, char>;
+    return *reinterpret_cast<P*>(reinterpret_cast<B*>(p) + (unsigned)i * (unsigned)sizeof(P));
 }
 
 // The same with the S-kernel's head, s formed for every gathered column and stored.
 // (No register limit: it gathers two vectors, and runs on systems that do not
 // fill the chip; 9 spilled registers cost 1.5 us.)
-template <typename T>
-__global__ __launch_bounds__(kSlBlock) void k_bicg_SBs(const BicgArgs<T> a) {
-    const SliceRows q = slice_rows_of(a.one, a.sg);
+template <typename T, bool N32 = false, int TB = kSlBlock, int PASS = 8>
+__device__ __forceinline__ void bicg_SBs(const BicgArgs<T>& a) {
+    const SliceRows q = slice_rows_of<TB>(a.one, a.sg, a.sv);
     const FirstSlice f = first_slice(sliced_of(a), q);
-    if (not_sliced(a)) return;
-    zero_slots(a, kPartB, 8, q.lb, a.sg);
+    zero_slots(a, kPartB, 8, q.lb, a.sg, slice_first(q));
     SysBlock sb{};
     sb.sys = 0;
     sb.local = q.lb;
@@ -346,13 +374,18 @@ __global__ __launch_bounds__(kSlBlock) void k_bicg_SBs(const BicgArgs<T> a) {
     cx<T>* __restrict__ tv = a.t;
     double e[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     slice_rows<T, false>(
-        sliced_of(a), q, f, a.one.n, [=](int c) { return cfma<T>(nal, v[c], r[c]); }, [rh](int row) { return rh[row]; },
+        sliced_of(a), q, f, a.one.n, [=](int c) { return cfma<T>(nal, at<N32>(v, c), at<N32>(r, c)); },
+        [rh](int row) { return at<N32>(rh, row); },
         [&](int64_t row, cx<T> acc, cx<T> s, cx<T> w) {
-            sv[row] = s;
-            tv[row] = acc;
+            at<N32>(sv, (int)row) = s;
+            at<N32>(tv, (int)row) = acc;
             b_terms<T>(e, s, acc, w);
         });
-    slice_store<8>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+    slice_store<8, TB, PASS>(a.part + kPartB * a.stride, a.stride, q.lb, e);
+}
+template <typename T>
+__global__ __launch_bounds__(kSlBlock) void k_bicg_SBs(const BicgArgs<T> a) {
+    bicg_SBs<T>(a);
 }
 
 }  // namespace hz

@@ -34,13 +34,11 @@ __host__ __device__ constexpr int sol_subs(int G) {
     return f < 2 ? 2 : (f > 4 ? 4 : f);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kSpBlock) void k_bicg_At(const BicgArgs<T> a) {
+template <typename T, bool PAST> __device__ __forceinline__ void bicg_At(const BicgArgs<T>& a) {
     const SysBlock q = map_block(a.one, a.bmap, a.smap, a.G, a.pf, blockIdx.x);
     if (q.sys < 0) return;
-    const SolverScal* sc = a.sc + q.sys;
-    if (sc->done || sc->pending || not_csr(a)) return;
-    zero_slots(a, kPartA, 2, q.lb, a.pf * a.G);
+    if (ended<PAST>(a.sc + q.sys, sys_leader(q))) return;
+    zero_slots(a, kPartA, 2, q.lb, a.pf * a.G, threadIdx.x == 0);
     const cx<T>* __restrict__ p = a.p;
     cx<T>* __restrict__ v = a.v;
     const cx<T>* __restrict__ rh = a.rh;
@@ -56,12 +54,16 @@ __global__ __launch_bounds__(kSpBlock) void k_bicg_At(const BicgArgs<T> a) {
     store_sys_partials<2, kTileLanes, 0, kSpBlock>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kSpBlock) void k_bicg_Bt(const BicgArgs<T> a) {
+template <typename T, bool PAST = false>
+__global__ __launch_bounds__(kSpBlock) void k_bicg_At(const BicgArgs<T> a) {
+    if (!past_end<PAST>(a)) bicg_At<T, PAST>(a);
+}
+
+template <typename T> __device__ __forceinline__ void bicg_Bt(const BicgArgs<T>& a) {
     const SysBlock q = map_block(a.one, a.bmap, a.smap, a.G, a.pf, blockIdx.x);
     if (q.sys < 0) return;
-    if (a.sc[q.sys].done || not_csr(a)) return;
-    zero_slots(a, kPartB, 8, q.lb, a.pf * a.G);
+    if (a.sc[q.sys].done) return;
+    zero_slots(a, kPartB, 8, q.lb, a.pf * a.G, threadIdx.x == 0);
     const cx<T>* __restrict__ sv = a.s;
     const cx<T>* __restrict__ rh = a.rh;
     cx<T>* __restrict__ tv = a.t;
@@ -72,6 +74,10 @@ __global__ __launch_bounds__(kSpBlock) void k_bicg_Bt(const BicgArgs<T> a) {
         [&](int64_t, cx<T> acc, BRow<T> m) { b_terms<T>(e, m.s, acc, m.w); },
         [tv](int64_t row, cx<T> acc) { tv[row] = acc; });
     store_sys_partials<8, kTileLanes, 0, kSpBlock>(a.part + kPartB * a.stride, a.stride, q.lb, e);
+}
+template <typename T, bool PAST = false>
+__global__ __launch_bounds__(kSpBlock) void k_bicg_Bt(const BicgArgs<T> a) {
+    if (!past_end<PAST>(a)) bicg_Bt<T>(a);
 }
 
 }  // namespace hz

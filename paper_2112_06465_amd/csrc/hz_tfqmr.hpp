@@ -486,7 +486,7 @@ __global__ HZ_SLICE_BOUNDS void k_q_inits(const QArgs a, const double2* __restri
     slice_rows<double, false>(
         sliced_of(a), q, first_slice(sliced_of(a), q), a.one.n, [r0](int c) { return r0[c]; }, [](int) { return 0; },
         [&](int64_t row, double2 acc, double2 self, int) { q_end0(a, row, self, acc, e); });
-    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+    slice_store<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 template <bool NT>
@@ -500,7 +500,7 @@ __global__ HZ_SLICE_BOUNDS void k_q_prod2s(const QArgs a) {
     slice_rows<double, NT>(
         sliced_of(a), q, f, a.one.n, [u1](int c) { return u1[c]; }, [&a](int row) { return q_row2(a, row); },
         [&](int64_t row, double2 acc, double2, const QRow2& p) { q_end2(a, row, na, acc, p, e); });
-    slice_store<4>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+    slice_store<4>(a.part + kPartB * a.stride, a.stride, q.lb, e);
 }
 
 __global__ __launch_bounds__(kSlBlock) void k_q_prod2sf(const QArgs a) {
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(kSlBlock) void k_q_prod2sf(const QArgs a) {
             a.u1[row] = self;
             q_end2(a, row, na, acc, p, e);
         });
-    slice_store<4>(a.part + kPartB * a.stride + q.lb, a.stride, e);
+    slice_store<4>(a.part + kPartB * a.stride, a.stride, q.lb, e);
 }
 
 template <bool NT>
@@ -535,7 +535,7 @@ __global__ HZ_SLICE_BOUNDS void k_q_prod4s(const QArgs a) {
     slice_rows<double, NT>(
         sliced_of(a), q, f, a.one.n, [u](int c) { return u[c]; }, [&a](int row) { return q_row4(a, row); },
         [&](int64_t row, double2 acc, double2, const QRow4& p) { q_end4(a, row, beta, acc, p, e); });
-    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+    slice_store<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 __global__ __launch_bounds__(kSlBlock) void k_q_prod4sf(const QArgs a) {
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(kSlBlock) void k_q_prod4sf(const QArgs a) {
             a.u[row] = self;
             q_end4(a, row, beta, acc, p, e);
         });
-    slice_store<2>(a.part + kPartA * a.stride + q.lb, a.stride, e);
+    slice_store<2>(a.part + kPartA * a.stride, a.stride, q.lb, e);
 }
 
 }  // namespace hz
