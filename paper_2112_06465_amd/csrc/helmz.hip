@@ -612,12 +612,11 @@ void enqueue_jacobi(hipStream_t s, int n, int nnz, const int* rp, const int* ci,
         const dim3 G((n + hz::kSlBlock - 1) / hz::kSlBlock), B(hz::kSlBlock);
         hipLaunchKernelGGL(hz::k_slice_width, G, B, 0, s, n, rp, soff, no);
         hipLaunchKernelGGL(hz::k_slice_scan, dim3(1), dim3(kBlock), 0, s, ns, soff, int64_t(nnz), no);
-        hipLaunchKernelGGL((hz::k_slice_fill<TO>), G, B, 0, s, n, rp, ci, A, d, static_cast<const int*>(soff), out,
+        hipLaunchKernelGGL((hz::k_slice_fill<TO>), G, B, 0, s, n, nnz, rp, ci, A, d, static_cast<const int*>(soff), out,
                            scol, static_cast<const int*>(no));
+    } else if (nnz > 0) {
+        hipLaunchKernelGGL((hz::k_colscale<TO>), grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A, d, out);
     }
-    if (nnz > 0)
-        hipLaunchKernelGGL((hz::k_colscale<TO>), grid1(nnz), dim3(kBlock), 0, s, int64_t(nnz), ci, A, d, out,
-                           room ? static_cast<const int*>(no) : nullptr);
 }
 
 // Blocks of a sliced product over the one-system map.

@@ -1482,13 +1482,11 @@ __global__ __launch_bounds__(kBlock) void k_jacobi_diag(int n, const int* __rest
 }
 
 // out_p = vals_p * dinv[col_p]   (column scaling A D^{-1}, rounded to TO for
-// the complex64 iteration); with no != null only if the operator is not sliced
+// the complex64 iteration)
 template <typename TO>
 __global__ __launch_bounds__(kBlock) void k_colscale(int64_t nnz, const int* __restrict__ ci,
                                                      const double2* __restrict__ vals,
-                                                     const double2* __restrict__ dinv, cx<TO>* __restrict__ out,
-                                                     const int* no) {
-    if (no != nullptr && *no == 0) return;
+                                                     const double2* __restrict__ dinv, cx<TO>* __restrict__ out) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= nnz) return;
     const double2 a = cmul<double>(vals[p], dinv[ci[p]]);
