@@ -131,13 +131,17 @@ enum { HZ_SPMV_FORM_ROWS = 0, HZ_SPMV_FORM_TILES = 1 };
  * (the untuned choice unless another is more than 3 % faster) are
  * recorded in the handle for this (row_ptr, col_idx, n, nnz), and later
  * products and solves on the same handle with the same index arrays use
- * them (results change only by summation order).  Without tuning, the
+ * them (results change only by summation order).  A one-system solve under
+ * Jacobi whose operator is stored in slices (even rows, columns within 32,767
+ * rows) multiplies by it one lane per row, and uses the lane count for its
+ * residuals only.  Without tuning, the
  * solver kernels use vector rows with the smallest power of two L not below
  * half the mean row length (block tiles for a one-system FP64 solve whose
  * values exceed 128 MiB), and the standalone product uses block tiles when
- * the mean row length is at most 16 entries, else vector rows with that L.  Writes the solver lane count to *lanes, and, where the pointers
- * are not NULL, the standalone form to *form (HZ_SPMV_FORM_*) and its lane
- * count to *form_lanes (host memory).  y is overwritten with A x.
+ * the mean row length is at most 16 entries, else vector rows with that L.
+ * Writes the solver lane count to *lanes, and, where the pointers are not
+ * NULL, the standalone form to *form (HZ_SPMV_FORM_*) and its lane count to
+ * *form_lanes (host memory).  y is overwritten with A x.
  * Synchronises the stream.  The environment variables HZ_SPMV_LANES (a lane
  * count) and HZ_SPMV_FORM ("rows" or "tiles"), when set, override the rule
  * and the tuned choices.
@@ -219,14 +223,14 @@ int zbicgstab_solve(hz_handle *handle, hz_stream stream, int n, int nnz, const i
  * zbicgstab_solve_async: the same solve with nothing on the host waiting for
  * the stream (Section 7's iteration control kept on the device): every
  * launch of up to maxiter iterations is enqueued in chunks of 64 (kernels
- * after the exit return at entry, a few microseconds each, so maxiter should
- * be near the expected count), and the result is written by a kernel to
+ * after the exit return at entry, 5 to 7 microseconds an iteration, so maxiter
+ * should be near the expected count), and the result is written by a kernel to
  * info_dev, a device hz_solve_info (8-byte aligned), when the stream reaches
  * it.  b, x, ws and info_dev must stay valid until then.  One system, FP64,
  * caller's numbering: HZ_REORDER, HZ_VALIDATE and HZ_RELIABLE are invalid,
  * renumbering never happens (workspace as for zbicgstab_solve with
- * HZ_NO_REORDER).  The launch map is written into ws by a kernel, so the
- * call allocates nothing and never waits; iteration graphs cached by the
+ * HZ_NO_REORDER).  x is that of the synchronous solve bit for bit.  The call
+ * allocates nothing and never waits; iteration graphs cached by the
  * handle are evicted only after their last launch has completed.  A zero
  * diagonal under Jacobi is reported as info_dev->status =
  * HZ_ERR_INVALID.  Returns HZ_OK once enqueued, or an argument error.

@@ -519,8 +519,9 @@ size_t slice_col_bytes(int64_t nnz) { return align_up(sizeof(short) * size_t(nnz
 // The size is never less than that of eight vectors and ten partial regions,
 // which callers' limits (the static scratch's among them) have been set by.
 // A one-system Jacobi solve may slice its operator where the offsets and
-// columns fit into what that leaves (up to about 15.9 entries a row from
-// 12,000 rows on), or with `grow`.
+// columns fit into what that leaves (nnz <= 16 n - n / 32 - 16,384: 14.6
+// entries a row at 12,000 rows, 15.8 at 100,000, 15.9 from 230,000 on), or with
+// `grow`.
 template <typename T>
 size_t ws_layout(int n, int64_t nnz, bool jacobi, int nsys, int G, char* base, SolveWs* out, bool grow = false) {
     const size_t vb = align_up(sizeof(cx<T>) * size_t(n > 0 ? n : 1));
